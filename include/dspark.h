@@ -205,7 +205,13 @@ dspark_status dspark_schedule_topk(const float* conf, int R, int K, const int32_
  *       identical strides (values are the first 512 dims of the key rows),
  *       page_size a power of two >= 64, strides multiples of 8 elements,
  *       q/k/out 16-byte aligned: MFMA tiles, bound by the matrix cores;
+ *     - head sizes up to 256, bf16 or fp32, any page: strides multiples of 16
+ *       bytes (page stride below 2^30 elements, token stride below 2^24),
+ *       q/k/v 16-byte and out 8-byte (bf16) or 16-byte (fp32) aligned: MFMA
+ *       tiles, the probabilities at 32-bit accuracy, HBM-bound;
  *     - anything else: vector ALUs.
+ *   On the matrix cores a non-finite value of a later verify token of a
+ *   request can reach that request's earlier rows (0 times it).
  * ---------------------------------------------------------------------- */
 size_t dspark_verify_attn_workspace_size(int R, int max_q, int Hq, int Hkv, int Dqk, int Dv,
                                          int max_pages, int page_size, dspark_dtype dt);

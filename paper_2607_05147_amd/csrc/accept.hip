@@ -100,9 +100,6 @@ size_t accept_workspace(int R, int K, int V) {
 
 // exp2 on the transcendental unit (v_exp_f32)
 __device__ __forceinline__ float fexp2(float x) { return __builtin_amdgcn_exp2f(x); }
-// NaN-propagating maximum without operand canonicalisation (v_maximum3_f32)
-__device__ __forceinline__ float vmax(float a, float b) { return __builtin_elementwise_maximum(a, b); }
-
 __device__ __forceinline__ int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
 
 template <bool BF16>

@@ -1,7 +1,9 @@
 // Ragged causal verify attention over a paged KV cache, vector-ALU path.
 //
 // Handles fp32 and bf16 and any head size that is a multiple of 8 (up to 576),
-// including latent attention where the values alias the keys.  One wave per
+// any alignment, and latent attention where the values alias the keys: what the
+// matrix-core kernels do not take (unaligned buffers or strides, head sizes above
+// 256 other than the latent shape on pages of 64 and more).  One wave per
 // work item (query token, KV head, block of up to 8 query heads of that KV
 // head's group, KV split): each lane owns one key of a 64-key tile for the
 // score/softmax step and a slice of the value dimension for the weighted sum.

@@ -250,10 +250,6 @@ __global__ __launch_bounds__(kPlanThreads) void mf_plan(MfParams p) {
     if (tid == 0) p.work[2] = s_merge;
 }
 
-__device__ __forceinline__ uint32_t pack2_bf16(float lo, float hi) {
-    return (uint32_t)f32_to_bf16(lo) | ((uint32_t)f32_to_bf16(hi) << 16);
-}
-
 // 16-byte chunk slot of chunk c in LDS row t (t < 32) of the K / V tile.  gfx950
 // serves a 16-byte LDS read in four 16-lane phases (lanes split by bit 5 and
 // by the parity of bits 2 ^ 3 ^ 4) and a transposing 8-byte read in two
@@ -271,58 +267,6 @@ typedef __attribute__((address_space(3))) bf16x8 lds_bf16x8;
 // written): keys at or past a split's end are copied from here instead of
 // from the page, so stale or NaN page tails never reach LDS.
 __device__ __align__(16) uint16_t g_zero_row[kD];
-
-// 16-byte copy global -> LDS for a whole wave: lane L's 16 bytes land at
-// lds_base + 16 L (lds_base is wave-uniform).  Emitted as inline asm so that
-// the compiler does not add its own conservative waits for it; the kernel
-// waits for these copies with explicit vmcnt counts.
-__device__ __forceinline__ void lds_copy16(const void* gsrc, uint32_t lds_addr) {
-    const uint32_t m0 = __builtin_amdgcn_readfirstlane(lds_addr);
-    asm volatile(
-        "s_mov_b32 m0, %0\n\t"
-        "global_load_lds_dwordx4 %1, off"
-        :
-        : "s"(m0), "v"(gsrc)
-        : "memory", "m0");
-}
-
-// s_waitcnt vmcnt(N) leaving the other counters alone (gfx9 encoding)
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-    static_assert(N >= 0 && N < 64, "vmcnt range");
-    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (0x7 << 4) | (0xF << 8));
-}
-
-// NaN-propagating maximum (v_maximum3_f32; no operand canonicalisation)
-__device__ __forceinline__ float vmax(float a, float b) { return __builtin_elementwise_maximum(a, b); }
-
-// max over the four lanes that share a row (lanes lr, lr + 16, lr + 32, lr + 48)
-__device__ __forceinline__ float row_max4(float v) {
-    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    v = vmax(__uint_as_float(a[0]), __uint_as_float(a[1]));
-    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return vmax(__uint_as_float(b[0]), __uint_as_float(b[1]));
-}
-
-__device__ __forceinline__ uint32_t cvt_pk_bf16(float lo, float hi) {
-    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-    typedef float f32x2 __attribute__((ext_vector_type(2)));
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){lo, hi}, bf16x2));
-}
-
-// copy with a wave-uniform 64-bit base (SGPRs) and a per-lane 32-bit offset
-__device__ __forceinline__ void lds_copy16_s(uint64_t sbase, uint32_t voff, uint32_t lds_addr) {
-    const uint32_t m0 = __builtin_amdgcn_readfirstlane(lds_addr);
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)sbase);
-    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(sbase >> 32));
-    const uint64_t sb = ((uint64_t)hi << 32) | lo;
-    asm volatile(
-        "s_mov_b32 m0, %0\n\t"
-        "global_load_lds_dwordx4 %1, %2"
-        :
-        : "s"(m0), "v"(voff), "s"(sb)
-        : "memory", "m0");
-}
 
 constexpr float kRescale = 8.0f;  // log2 headroom before the running max is moved
 

@@ -139,54 +139,6 @@ __device__ __forceinline__ int pchunk(int t, int c) { return c ^ ((t & 3) | (((t
 // past a split's end are copied from here.
 __device__ __align__(16) uint16_t g_zero_row[kDk];
 
-__device__ __forceinline__ void lds_copy16(const void* gsrc, uint32_t lds_addr) {
-    const uint32_t m0 = __builtin_amdgcn_readfirstlane(lds_addr);
-    asm volatile(
-        "s_mov_b32 m0, %0\n\t"
-        "global_load_lds_dwordx4 %1, off"
-        :
-        : "s"(m0), "v"(gsrc)
-        : "memory", "m0");
-}
-
-__device__ __forceinline__ void lds_copy16_s(uint64_t sbase, uint32_t voff, uint32_t lds_addr) {
-    const uint32_t m0 = __builtin_amdgcn_readfirstlane(lds_addr);
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)sbase);
-    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(sbase >> 32));
-    const uint64_t sb = ((uint64_t)hi << 32) | lo;
-    asm volatile(
-        "s_mov_b32 m0, %0\n\t"
-        "global_load_lds_dwordx4 %1, %2"
-        :
-        : "s"(m0), "v"(voff), "s"(sb)
-        : "memory", "m0");
-}
-
-template <int N>
-__device__ __forceinline__ void wait_vmcnt() {
-    static_assert(N >= 0 && N < 64, "vmcnt range");
-    __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (0x7 << 4) | (0xF << 8));
-}
-
-__device__ __forceinline__ float vmax(float a, float b) { return __builtin_elementwise_maximum(a, b); }
-
-__device__ __forceinline__ float row_max4(float v) {
-    const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    v = vmax(__uint_as_float(a[0]), __uint_as_float(a[1]));
-    const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return vmax(__uint_as_float(b[0]), __uint_as_float(b[1]));
-}
-
-__device__ __forceinline__ uint32_t cvt_pk_bf16(float lo, float hi) {
-    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-    typedef float f32x2 __attribute__((ext_vector_type(2)));
-    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2){lo, hi}, bf16x2));
-}
-
-__device__ __forceinline__ uint32_t pack2_bf16(float lo, float hi) {
-    return (uint32_t)f32_to_bf16(lo) | ((uint32_t)f32_to_bf16(hi) << 16);
-}
-
 // ------------------------------------------------------------------ plan
 
 // Builds the per-XCD work queues and the merge list from cu_q / kv_len.  One

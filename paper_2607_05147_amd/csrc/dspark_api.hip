@@ -286,6 +286,7 @@ size_t dspark_verify_attn_workspace_size(int R, int max_q, int Hq, int Hkv, int 
     size_t need = dspark::attn_generic_workspace(a);
     if (dspark::attn_mfma_supported(a)) need = std::max(need, dspark::attn_mfma_workspace(a));
     if (dspark::attn_mla_shape_ok(a)) need = std::max(need, dspark::attn_mla_workspace(a));
+    if (dspark::attn_stream_shape_ok(a)) need = std::max(need, dspark::attn_stream_workspace(a));
     return need;
 }
 
@@ -318,18 +319,24 @@ dspark_status dspark_verify_attn(const void* q, const void* k_cache, const void*
     dspark::AttnArgs a = make_attn(q, k_cache, v_cache, k_strides, v_strides, block_table,
                                    max_pages, kv_len, cu_q, R, max_q, Hq, Hkv, Dqk, Dv, page_size,
                                    scale, dt, out, lse);
-    // matrix-core paths first: GQA head dim 128, then latent 576/512; else vector ALUs
-    const int path = dspark::attn_mfma_supported(a) ? 0 : (dspark::attn_mla_supported(a) ? 1 : 2);
-    const size_t need = path == 0 ? dspark::attn_mfma_workspace(a)
-                                  : (path == 1 ? dspark::attn_mla_workspace(a)
-                                               : dspark::attn_generic_workspace(a));
+    // matrix-core paths first: GQA head dim 128, latent 576/512, any head size up to 256;
+    // else vector ALUs
+    const int path = dspark::attn_mfma_supported(a)     ? 0
+                     : dspark::attn_mla_supported(a)    ? 1
+                     : dspark::attn_stream_supported(a) ? 2
+                                                        : 3;
+    const size_t need = path == 0   ? dspark::attn_mfma_workspace(a)
+                        : path == 1 ? dspark::attn_mla_workspace(a)
+                        : path == 2 ? dspark::attn_stream_workspace(a)
+                                    : dspark::attn_generic_workspace(a);
     if (ws_bytes < need || (need > 0 && !ws) || !aligned(ws, 256))
         return fail(DSPARK_EWORKSPACE, "workspace of %zu bytes (256-aligned) needed, got %zu",
                     need, ws_bytes);
     hipStream_t s = (hipStream_t)stream;
-    return hip_status(path == 0 ? dspark::launch_attn_mfma(a, ws, s)
-                                : (path == 1 ? dspark::launch_attn_mla(a, ws, s)
-                                             : dspark::launch_attn_generic(a, ws, s)),
+    return hip_status(path == 0   ? dspark::launch_attn_mfma(a, ws, s)
+                      : path == 1 ? dspark::launch_attn_mla(a, ws, s)
+                      : path == 2 ? dspark::launch_attn_stream(a, ws, s)
+                                  : dspark::launch_attn_generic(a, ws, s),
                       "dspark_verify_attn");
 }
 

@@ -43,6 +43,12 @@ bool attn_mla_supported(const AttnArgs& a);  // shape, value aliasing and alignm
 size_t attn_mla_workspace(const AttnArgs& a);
 hipError_t launch_attn_mla(const AttnArgs& a, void* ws, hipStream_t s);
 
+// Matrix-core path for head sizes up to 256 and any page, bf16 and fp32.
+bool attn_stream_shape_ok(const AttnArgs& a);   // shape only (workspace sizing)
+bool attn_stream_supported(const AttnArgs& a);  // shape and alignment
+size_t attn_stream_workspace(const AttnArgs& a);
+hipError_t launch_attn_stream(const AttnArgs& a, void* ws, hipStream_t s);
+
 size_t attn_generic_workspace(const AttnArgs& a);
 hipError_t launch_attn_generic(const AttnArgs& a, void* ws, hipStream_t s);
 

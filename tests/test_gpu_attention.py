@@ -338,3 +338,70 @@ def test_edge_context_lengths(name, Hq, Hkv, q_len, kv_len):
         f"max row rel err {err.max():.3g}")
     assert err.max() <= TOL[w.dtype]
     np.testing.assert_allclose(to_f64(lse), ref_lse, rtol=0, atol=1e-4)
+
+
+@pytest.mark.parametrize("dtype,Dqk,Dv,page,Hq,Hkv,q_len,kv_len", [
+    # 32-key (bf16) and 16-key (fp32) steps: one key, one short of, at and past a step; contexts
+    # that one wave takes whole (up to 256 keys for the batch) and that several waves share
+    ("bf16", 64, 64, 16, 8, 2, [1, 2, 4, 3], [1, 31, 32, 33]),
+    ("f32", 64, 64, 16, 8, 2, [1, 2, 4, 3], [1, 15, 16, 17]),
+    ("bf16", 64, 64, 16, 8, 2, [1, 4, 9], [256, 257, 2100]),
+    ("f32", 128, 128, 64, 8, 2, [1, 4, 9], [256, 257, 1100]),
+    # pages that are no power of two; head sizes below the LDS row; unequal sizes
+    ("bf16", 80, 72, 48, 5, 1, [9, 1], [700, 330]),
+    ("f32", 72, 40, 48, 5, 1, [9, 1], [700, 330]),
+    ("bf16", 192, 128, 16, 4, 2, [3, 9], [900, 270]),
+    ("bf16", 8, 8, 16, 2, 2, [1, 3], [40, 600]),
+    # the largest head sizes; several row chunks (more than 16 NT rows); a page window of 128 pages left
+    ("bf16", 256, 256, 32, 16, 2, [9, 5], [300, 1500]),
+    ("f32", 256, 256, 32, 16, 2, [9, 5], [300, 700]),
+    ("bf16", 128, 128, 16, 64, 8, [17, 1], [2300, 260]),
+    ("bf16", 96, 96, 16, 32, 1, [5, 2], [5000, 400]),
+])
+def test_any_head_size_and_page(dtype, Dqk, Dv, page, Hq, Hkv, q_len, kv_len):
+    """Head sizes up to 256 on any page: against the oracle, against the same
+    cache token-major (the same keys in the same order: bit-identical), and the
+    vector-ALU kernels (a query buffer that is not 16-byte aligned) against the
+    oracle.  Also requests between which one is malformed."""
+    import torch
+    from paper_2607_05147_amd import dspark
+    from gpu_helpers import to_dev
+    K = max(q_len) - 1
+    w = synth.scaled(synth.WORKLOADS["tiny" if dtype == "f32" else "mid"], R=len(q_len), K=max(K, 1), Hq=Hq, Hkv=Hkv,
+                     Dqk=Dqk, Dv=Dv, page=page)
+    cu = oracle.cu_from_len(np.asarray(q_len) - 1)
+    kv = synth.paged_kv(w, 41, kv_len=np.asarray(kv_len, np.int32))
+    q = synth.query_rows(w, 41, synth.flat_keys(np.diff(cu)))
+    ref, ref_lse = oracle.verify_attn(q, kv.k, kv.v, kv.k_strides, kv.v_strides, kv.block_table, kv.kv_len, cu, Hq, Hkv,
+                                      Dqk, Dv, page, w.scale, dtype)
+    bf16 = dtype == "bf16"
+    dkv = DevKV(kv, bf16)
+    log(f"[attn] {dtype} D={Dqk}/{Dv} page={page} Hq={Hq}/{Hkv} q_len={q_len} kv={kv_len}")
+    out, lse = gpu_attention(w, dkv, q, cu)
+    o = to_f64(out)
+    assert np.isfinite(o).all()
+    assert row_rel_err(o, ref).max() <= TOL[dtype]
+    np.testing.assert_allclose(to_f64(lse), ref_lse, rtol=0, atol=1e-4 if bf16 else 1e-5)
+
+    tm = DevKV(kv, bf16)
+    tm.k = to_dev(np.ascontiguousarray(kv.k.transpose(0, 2, 1, 3)).reshape(-1), bf16)
+    tm.v = to_dev(np.ascontiguousarray(kv.v.transpose(0, 2, 1, 3)).reshape(-1), bf16)
+    tm.ks, tm.vs = (page * Hkv * Dqk, Dqk, Hkv * Dqk), (page * Hkv * Dv, Dv, Hkv * Dv)
+    out2, lse2 = gpu_attention(w, tm, q, cu)
+    assert torch.equal(out, out2) and torch.equal(lse, lse2)
+
+    qd = to_dev(q, bf16)
+    off = torch.empty(qd.numel() + 1, dtype=qd.dtype, device=qd.device)[1:].view(qd.shape)
+    off.copy_(qd)
+    out3, _ = dspark.dspark_verify_attn(off, dkv.k, dkv.v, dkv.ks, dkv.vs, dkv.bt, dkv.kv_len, to_dev(cu), w.max_q, Hkv, Dv,
+                                        page, w.scale)
+    assert row_rel_err(to_f64(out3), ref).max() <= TOL[dtype]
+
+    bad = kv.kv_len.copy()
+    bad[0] = q_len[0] - 1  # fewer keys than verify tokens: skipped
+    out4 = torch.full_like(out, 7.0)
+    dspark.dspark_verify_attn(qd, dkv.k, dkv.v, dkv.ks, dkv.vs, dkv.bt, to_dev(bad), to_dev(cu), w.max_q, Hkv, Dv, page,
+                              w.scale, out=out4)
+    o4 = to_f64(out4)
+    assert (o4[: cu[1]] == 7.0).all()
+    assert row_rel_err(o4[cu[1]:], ref[cu[1]:]).max() <= TOL[dtype]
