@@ -24,18 +24,19 @@
 // the transposing V reads are free of bank conflicts.  Page ids of the split
 // are loaded once (one per lane) and picked per step with readlane.
 //
-// The workgroups are persistent and take items from a list that a one-block
-// plan kernel builds on the device, longest first.  A request whose context
-// has more than one split stores per-split partials (m, l, unnormalised o);
-// a merge kernel combines them afterwards in split order (bitwise
-// reproducible).  Exchanging them across a kernel boundary needs no
+// How the work is dealt depends on the batch's size.  Small and middling batches
+// are cut into equal ranges, one per resident workgroup (attn_ranges.h).  Large
+// ones go through a queue: the workgroups are persistent and take items from a
+// list that a one-block plan kernel builds on the device, longest first; a
+// request whose context has more than one split stores per-split partials (m, l,
+// unnormalised o), and a merge kernel combines them afterwards in split order
+// (bitwise reproducible).  Exchanging them across a kernel boundary needs no
 // device-scope fences, which on this part would write back and invalidate the
 // whole L2 of an XCD.
 #include <algorithm>
 #include <type_traits>
 
-#include "device_common.h"
-#include "kernels.h"
+#include "attn_ranges.h"
 
 namespace dspark {
 
@@ -53,6 +54,15 @@ constexpr int kSplit = 4096;
 constexpr int kMinSplit = 512;
 constexpr int64_t kTargetItems = 1536;
 static_assert(kSplit / 64 <= DSPARK_WAVE, "a split's page ids fit one per lane");
+// Batches of at most this many steps per resident workgroup (from the host's
+// bound on the contexts) are cut into equal ranges, without a plan kernel; larger
+// ones go through the queue, which evens out the workgroups' speeds.  Whole call,
+// ranges
+// against queue (us, 64/8 heads): 4 requests of 2K-16K keys 51 / 62, one 25 / 33, 8 of
+// 300-700 19 / 25, 32 of 1K-4K (32/8 heads) 80 / 88, 32 of 2K-16K 251 / 251, 64 of
+// them 246 / 237, 128 of about 4.6K 476 / 443.
+constexpr int kRangeUnits = 320;
+constexpr int kMfMinUnits = 4;  // steps of a range, at least
 constexpr int kStepTok = 32;   // keys per step
 constexpr int kRing = 4;       // LDS buffers; copies run kRing - 1 steps ahead
 constexpr int kD = 128;
@@ -83,6 +93,8 @@ struct MfGeom {
     int64_t n_items;   // upper bound on attention work items
     int64_t n_merge;   // upper bound on merge items (8 rows each)
     size_t counter_bytes, list_bytes, mlist_bytes, slot_floats, part_bytes;
+    int ranges, direct;          // equal ranges instead of the queue; a worker per chunk
+    int64_t resident, workers;   // ranges per head; workgroups
 };
 
 constexpr int kMergeRows = 8;  // rows per merge item (32 threads of 4 values per row)
@@ -107,11 +119,24 @@ static MfGeom mf_geom(const AttnArgs& a) {
     g.mlist_bytes = ((size_t)g.n_merge * 2 * sizeof(int4) + 255) & ~(size_t)255;
     g.slot_floats = (size_t)g.chunk_rows * (kD + 2);
     g.part_bytes = g.max_splits > 1 ? (size_t)slots * g.max_splits * g.slot_floats * sizeof(float) : 0;
+    // two resident workgroups per CU (64 KB of LDS and <= 256 VGPRs each)
+    const int64_t steps = (max_kv + kStepTok - 1) / kStepTok;
+    const int64_t units = (int64_t)a.R * g.rc_max * steps;  // per head, at most
+    g.resident = std::max(1, 2 * kRangeCUs / a.Hkv);
+    g.workers = a.Hkv * std::min<int64_t>(g.resident, (units + kMfMinUnits - 1) / kMfMinUnits);
+    g.ranges = units <= kRangeUnits * g.resident && g.rc_max * steps < (int64_t)1 << 31 &&
+               (int64_t)a.R * a.Hkv < (int64_t)1 << 31;
+    // (up to twice the keys when the chunks alone fill the part: 64 requests x 8
+    // heads of 256-500 keys 30 against 34 us)
+    g.direct = g.ranges && (max_kv <= kDirectKeys || (max_kv <= 2 * kDirectKeys && slots >= 2 * kRangeCUs));
+    if (g.direct) g.workers = slots;
     return g;
 }
 
 size_t attn_mfma_workspace(const AttnArgs& a) {
     const MfGeom g = mf_geom(a);
+    if (g.direct) return 0;
+    if (g.ranges) return range_head_bytes(a.R) + (size_t)g.workers * 2 * g.slot_floats * sizeof(float);
     return g.counter_bytes + g.list_bytes + g.mlist_bytes + g.part_bytes;
 }
 
@@ -270,20 +295,19 @@ __device__ __align__(16) uint16_t g_zero_row[kD];
 
 constexpr float kRescale = 8.0f;  // log2 headroom before the running max is moved
 
-template <int TPW>
-__device__ __forceinline__ void attn_item(const MfParams& p, const int r, const int g, const int s,
-                                          const int rc, const int q0, const int ql, const int kv,
-                                          const int nsplit, const uint32_t lds0, int& nxt) {
+// Steps [s0, s1) of row chunk rc of (request r, KV head g), a whole context when
+// `whole`, else a partial to `part`.  The work queue claims its next item in
+// `nxt` three steps before the end (QUEUE).
+template <int TPW, bool QUEUE>
+__device__ __forceinline__ void attn_item(const MfParams& p, const int r, const int g, const int rc, const int q0,
+                                          const int ql, const int kv, const int s0, const int s1, const bool whole,
+                                          float* part, const uint32_t lds0, int& nxt) {
     const AttnArgs& a = p.a;
     constexpr int kChunkRows = 16 * kMfWaves * TPW;
-    constexpr int kSlotFloats = kChunkRows * (kD + 2);
-    const int rg = r * a.Hkv + g;
-    // the plan only lists valid items: 1 <= ql <= max_q, ql <= kv <= max_pages * page,
-    // s < nsplit, rc * kChunkRows < ql * group
+    // 1 <= ql <= max_q, ql <= kv <= max_pages * page, rc * kChunkRows < ql * group
     const int rows = ql * p.group;
     const int row0 = rc * kChunkRows;
-    int start, end;
-    split_range(kv, p.split, s, start, end);
+    const int end = min(kv, s1 * kStepTok);
     const int nrows = min(kChunkRows, rows - row0);
     const int nt = (nrows + 15) >> 4;
 
@@ -298,11 +322,6 @@ __device__ __forceinline__ void attn_item(const MfParams& p, const int r, const 
     const uint16_t* __restrict__ qg = (const uint16_t*)a.q;
     const uint16_t* __restrict__ kc = (const uint16_t*)a.k;
     const uint16_t* __restrict__ vc = (const uint16_t*)a.v;
-
-    // ---- page ids of the split, one per lane
-    const int pg0 = start >> p.page_shift;
-    const int npg = ((end - 1) >> p.page_shift) - pg0 + 1;  // <= 64 (pages of >= 64 keys)
-    const int my_page = lane < npg ? a.block_table[(int64_t)r * a.max_pages + pg0 + lane] : 0;
 
     // ---- query fragments (B operand of S^T = K Q^T) and causal limits
     bf16x8 qf[TPW][4];
@@ -370,161 +389,174 @@ __device__ __forceinline__ void attn_item(const MfParams& p, const int r, const 
         cp_koff[i] = t * p.ks2b + 16 * cp_kchunk[i];
         cp_voff[i] = t * p.vs2b + 16 * cp_vchunk[i];
     }
-    const int nsteps = (end - start + kStepTok - 1) / kStepTok;  // >= 1
-    const int last = nsteps - 1;
     // this wave's copy destinations start 2 KB into each tile (wave-uniform)
     const uint32_t lds_wave = __builtin_amdgcn_readfirstlane(lds0 + wave * 2048);
     const uint64_t kc_head = (uint64_t)(uintptr_t)kc + (uint64_t)((uint32_t)g * p.ks1b);
     const uint64_t vc_head = (uint64_t)(uintptr_t)vc + (uint64_t)((uint32_t)g * p.vs1b);
 
-    auto issue = [&](int n) {
-        const int tok0 = start + n * kStepTok;
-        const int page = __builtin_amdgcn_readlane(my_page, (tok0 >> p.page_shift) - pg0);
-        const int slot0 = tok0 & ((1 << p.page_shift) - 1);
-        const uint32_t kd = lds_wave + ((unsigned)n & (kRing - 1)) * (2 * kTileBytes);
-        const uint32_t vd = kd + kTileBytes;
-        if (tok0 + kStepTok <= end) {
-            const uint64_t kb = kc_head + (uint64_t)(uint32_t)page * p.ks0b + (uint32_t)slot0 * p.ks2b;
-            const uint64_t vb = vc_head + (uint64_t)(uint32_t)page * p.vs0b + (uint32_t)slot0 * p.vs2b;
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                lds_copy16_s(kb, cp_koff[i], kd + i * 1024);
-                lds_copy16_s(vb, cp_voff[i], vd + i * 1024);
-            }
-        } else {
-            // last, partial step: keys at or past the end come from the zero row
-            const uint16_t* kb = kc + (int64_t)page * a.ks[0] + (int64_t)g * a.ks[1];
-            const uint16_t* vb = vc + (int64_t)page * a.vs[0] + (int64_t)g * a.vs[1];
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const int64_t tr = slot0 + cp_row[i];
-                const bool in = tok0 + cp_row[i] < end;
-                const uint16_t* ksrc = in ? kb + tr * a.ks[2] + 8 * cp_kchunk[i] : g_zero_row + 8 * cp_kchunk[i];
-                const uint16_t* vsrc = in ? vb + tr * a.vs[2] + 8 * cp_vchunk[i] : g_zero_row + 8 * cp_vchunk[i];
-                lds_copy16(ksrc, kd + i * 1024);
-                lds_copy16(vsrc, vd + i * 1024);
-            }
-        }
-    };
+    // ---- segments of up to 64 pages, whose ids are one per lane (a queue item is
+    // one segment)
+    for (int sb = s0; sb < s1;) {
+        const int start = sb * kStepTok;
+        const int pg0 = start >> p.page_shift;
+        const int64_t window = ((int64_t)(pg0 + DSPARK_WAVE) << p.page_shift) / kStepTok;
+        const int se = QUEUE ? s1 : (int)min((int64_t)s1, window);
+        const int nsteps = se - sb;
+        const int last_pg = (kv - 1) >> p.page_shift;
+        const int my_page = pg0 + lane <= last_pg ? a.block_table[(int64_t)r * a.max_pages + pg0 + lane] : 0;
 
-    auto compute = [&](int n, auto bufc) {
-        constexpr unsigned buf = decltype(bufc)::value;
-        const int tok0 = start + n * kStepTok;
-        constexpr uint32_t boff = buf * (2 * kTileBytes);
-        // all K fragments of the step first (8 LDS reads in flight), then the scores
-        bf16x8 kfr[2][4];
+        auto issue = [&](int n) {
+            const int tok0 = start + n * kStepTok;
+            // (steps past the segment's end, never read, may lie past its page window)
+            const int page = __builtin_amdgcn_readlane(my_page, min((tok0 >> p.page_shift) - pg0, DSPARK_WAVE - 1));
+            const int slot0 = tok0 & ((1 << p.page_shift) - 1);
+            const uint32_t kd = lds_wave + ((unsigned)n & (kRing - 1)) * (2 * kTileBytes);
+            const uint32_t vd = kd + kTileBytes;
+            if (tok0 + kStepTok <= end) {
+                const uint64_t kb = kc_head + (uint64_t)(uint32_t)page * p.ks0b + (uint32_t)slot0 * p.ks2b;
+                const uint64_t vb = vc_head + (uint64_t)(uint32_t)page * p.vs0b + (uint32_t)slot0 * p.vs2b;
 #pragma unroll
-        for (int mb = 0; mb < 2; ++mb)
+                for (int i = 0; i < 2; ++i) {
+                    lds_copy16_s(kb, cp_koff[i], kd + i * 1024);
+                    lds_copy16_s(vb, cp_voff[i], vd + i * 1024);
+                }
+            } else {
+                // last, partial step: keys at or past the end come from the zero row
+                const uint16_t* kb = kc + (int64_t)page * a.ks[0] + (int64_t)g * a.ks[1];
+                const uint16_t* vb = vc + (int64_t)page * a.vs[0] + (int64_t)g * a.vs[1];
 #pragma unroll
-            for (int ks = 0; ks < 4; ++ks) kfr[mb][ks] = *lds_ptr<const lds_bf16x8>(koff[mb][ks] + boff);
-        f32x4 sc[TPW][2];
-#pragma unroll
-        for (int j = 0; j < TPW; ++j)
-#pragma unroll
-            for (int mb = 0; mb < 2; ++mb) {
-                sc[j][mb] = f32x4{0.f, 0.f, 0.f, 0.f};
-                if (j < nt_w)
-#pragma unroll
-                    for (int ks = 0; ks < 4; ++ks)
-                        sc[j][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kfr[mb][ks], qf[j][ks], sc[j][mb], 0, 0, 0);
+                for (int i = 0; i < 2; ++i) {
+                    const int64_t tr = slot0 + cp_row[i];
+                    const bool in = tok0 + cp_row[i] < end;
+                    const uint16_t* ksrc = in ? kb + tr * a.ks[2] + 8 * cp_kchunk[i] : g_zero_row + 8 * cp_kchunk[i];
+                    const uint16_t* vsrc = in ? vb + tr * a.vs[2] + 8 * cp_vchunk[i] : g_zero_row + 8 * cp_vchunk[i];
+                    lds_copy16(ksrc, kd + i * 1024);
+                    lds_copy16(vsrc, vd + i * 1024);
+                }
             }
-        // V^T fragments (16 transposing reads in flight) while the softmax runs.
-        bf16x8 vfr[8];
+        };
+
+        auto compute = [&](int n, auto bufc) {
+            constexpr unsigned buf = decltype(bufc)::value;
+            const int tok0 = start + n * kStepTok;
+            constexpr uint32_t boff = buf * (2 * kTileBytes);
+            // all K fragments of the step first (8 LDS reads in flight), then the scores
+            bf16x8 kfr[2][4];
 #pragma unroll
-        for (int db = 0; db < 8; ++db) {
-            const s16x4 h0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                lds_ptr<lds_s16x4>(voff[db][0] + boff));
-            const s16x4 h1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                lds_ptr<lds_s16x4>(voff[db][1] + boff));
-            vfr[db] = __builtin_bit_cast(
-                bf16x8, (short __attribute__((ext_vector_type(8)))){h0[0], h0[1], h0[2], h0[3],
-                                                                     h1[0], h1[1], h1[2], h1[3]});
-        }
-        // keys of this lane: tok0 + 8 lq + 4 mb + e; masks only where needed
-        const bool full = tok0 + kStepTok <= end && tok0 + kStepTok - 1 <= lim_min;
-        bf16x8 pf[TPW];
+            for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
-        for (int j = 0; j < TPW; ++j) {
-            if (j < nt_w) {
-                // raw scores; the scale is applied inside the exponent below
-                float sv[8];
+                for (int ks = 0; ks < 4; ++ks) kfr[mb][ks] = *lds_ptr<const lds_bf16x8>(koff[mb][ks] + boff);
+            f32x4 sc[TPW][2];
 #pragma unroll
-                for (int mb = 0; mb < 2; ++mb)
+            for (int j = 0; j < TPW; ++j)
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) sv[4 * mb + e] = sc[j][mb][e];
-                if (!full) {
+                for (int mb = 0; mb < 2; ++mb) {
+                    sc[j][mb] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    if (j < nt_w)
+#pragma unroll
+                        for (int ks = 0; ks < 4; ++ks)
+                            sc[j][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kfr[mb][ks], qf[j][ks], sc[j][mb], 0, 0, 0);
+                }
+            // V^T fragments (16 transposing reads in flight) while the softmax runs.
+            bf16x8 vfr[8];
+#pragma unroll
+            for (int db = 0; db < 8; ++db) {
+                const s16x4 h0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                    lds_ptr<lds_s16x4>(voff[db][0] + boff));
+                const s16x4 h1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                    lds_ptr<lds_s16x4>(voff[db][1] + boff));
+                vfr[db] = __builtin_bit_cast(
+                    bf16x8, (short __attribute__((ext_vector_type(8)))){h0[0], h0[1], h0[2], h0[3],
+                                                                         h1[0], h1[1], h1[2], h1[3]});
+            }
+            // keys of this lane: tok0 + 8 lq + 4 mb + e; masks only where needed
+            const bool full = tok0 + kStepTok <= end && tok0 + kStepTok - 1 <= lim_min;
+            bf16x8 pf[TPW];
+#pragma unroll
+            for (int j = 0; j < TPW; ++j) {
+                if (j < nt_w) {
+                    // raw scores; the scale is applied inside the exponent below
+                    float sv[8];
 #pragma unroll
                     for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
-                        for (int e = 0; e < 4; ++e) {
-                            const int key = tok0 + 8 * lq + 4 * mb + e;
-                            if (!(key < end && key <= lim[j])) sv[4 * mb + e] = -__builtin_huge_valf();
-                        }
-                }
-                float bm = vmax(vmax(vmax(sv[0], sv[1]), sv[2]),
-                                vmax(vmax(sv[3], sv[4]), vmax(vmax(sv[5], sv[6]), sv[7])));
-                bm = row_max4(bm) * p.scale2;
-                // move the running max only when the new one exceeds it by kRescale
-                // (P stays below 2^kRescale; the result is normalised at the end)
-                const bool need = bm > mrow[j] + kRescale;
-                if (__builtin_amdgcn_ballot_w64(need)) {
-                    const float mn = need ? bm : mrow[j];
-                    const float alpha = need ? __builtin_amdgcn_exp2f(mrow[j] - mn) : 1.0f;
-                    lsum[j] *= alpha;
+                        for (int e = 0; e < 4; ++e) sv[4 * mb + e] = sc[j][mb][e];
+                    if (!full) {
 #pragma unroll
-                    for (int db = 0; db < 8; ++db) acc[j][db] *= alpha;
-                    mrow[j] = mn;
-                }
-                const float mu = mrow[j] == -__builtin_huge_valf() ? 0.0f : mrow[j];
-                float pr[8];
+                        for (int mb = 0; mb < 2; ++mb)
 #pragma unroll
-                for (int k = 0; k < 8; ++k) pr[k] = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[k], p.scale2, -mu));
-                lsum[j] += ((pr[0] + pr[1]) + (pr[2] + pr[3])) + ((pr[4] + pr[5]) + (pr[6] + pr[7]));
-                // k-slot 8 lq + i <-> key 8 lq + i: M-block 0 gives i = 0..3, M-block 1 i = 4..7
-                u32x4 pk;
-                pk[0] = cvt_pk_bf16(pr[0], pr[1]);
-                pk[1] = cvt_pk_bf16(pr[2], pr[3]);
-                pk[2] = cvt_pk_bf16(pr[4], pr[5]);
-                pk[3] = cvt_pk_bf16(pr[6], pr[7]);
-                pf[j] = __builtin_bit_cast(bf16x8, pk);
+                            for (int e = 0; e < 4; ++e) {
+                                const int key = tok0 + 8 * lq + 4 * mb + e;
+                                if (!(key < end && key <= lim[j])) sv[4 * mb + e] = -__builtin_huge_valf();
+                            }
+                    }
+                    float bm = vmax(vmax(vmax(sv[0], sv[1]), sv[2]),
+                                    vmax(vmax(sv[3], sv[4]), vmax(vmax(sv[5], sv[6]), sv[7])));
+                    bm = row_max4(bm) * p.scale2;
+                    // move the running max only when the new one exceeds it by kRescale
+                    // (P stays below 2^kRescale; the result is normalised at the end)
+                    const bool need = bm > mrow[j] + kRescale;
+                    if (__builtin_amdgcn_ballot_w64(need)) {
+                        const float mn = need ? bm : mrow[j];
+                        const float alpha = need ? __builtin_amdgcn_exp2f(mrow[j] - mn) : 1.0f;
+                        lsum[j] *= alpha;
+#pragma unroll
+                        for (int db = 0; db < 8; ++db) acc[j][db] *= alpha;
+                        mrow[j] = mn;
+                    }
+                    const float mu = mrow[j] == -__builtin_huge_valf() ? 0.0f : mrow[j];
+                    float pr[8];
+#pragma unroll
+                    for (int k = 0; k < 8; ++k) pr[k] = __builtin_amdgcn_exp2f(__builtin_fmaf(sv[k], p.scale2, -mu));
+                    lsum[j] += ((pr[0] + pr[1]) + (pr[2] + pr[3])) + ((pr[4] + pr[5]) + (pr[6] + pr[7]));
+                    // k-slot 8 lq + i <-> key 8 lq + i: M-block 0 gives i = 0..3, M-block 1 i = 4..7
+                    u32x4 pk;
+                    pk[0] = cvt_pk_bf16(pr[0], pr[1]);
+                    pk[1] = cvt_pk_bf16(pr[2], pr[3]);
+                    pk[2] = cvt_pk_bf16(pr[4], pr[5]);
+                    pk[3] = cvt_pk_bf16(pr[6], pr[7]);
+                    pf[j] = __builtin_bit_cast(bf16x8, pk);
+                }
             }
-        }
 #pragma unroll
-        for (int j = 0; j < TPW; ++j)
-            if (j < nt_w)
+            for (int j = 0; j < TPW; ++j)
+                if (j < nt_w)
 #pragma unroll
-                for (int db = 0; db < 8; ++db)
-                    acc[j][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vfr[db], pf[j], acc[j][db], 0, 0, 0);
-    };
+                    for (int db = 0; db < 8; ++db)
+                        acc[j][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vfr[db], pf[j], acc[j][db], 0, 0, 0);
+        };
 
-    // ---- main loop.  Every thread issues kCopiesPerStep copies per step, in step
-    // order, also past the last step (copies of the zero row into buffers that
-    // are not read again), so "step n has landed" is always
-    // vmcnt <= (kRing - 2) * kCopiesPerStep.  Keys past the split end are copied
-    // as zeros (masked scores, zero values).  The loop is unrolled by the ring
-    // size so that every LDS address is a per-lane base plus an immediate.
-    wait_vmcnt<0>();
+        // ---- main loop.  Every thread issues kCopiesPerStep copies per step, in step
+        // order, also past the last step (copies of the zero row into buffers that
+        // are not read again), so "step n has landed" is always
+        // vmcnt <= (kRing - 2) * kCopiesPerStep.  Keys past the split end are copied
+        // as zeros (masked scores, zero values).  The loop is unrolled by the ring
+        // size so that every LDS address is a per-lane base plus an immediate.
+        wait_vmcnt<0>();
+        if (!QUEUE) lds_barrier();  // everyone is done with the previous segment's buffers
 #pragma unroll
-    for (int n = 0; n < kRing - 1; ++n) issue(n);
-    // the next item is claimed three steps before this one ends: late enough
-    // that no claimed item waits behind a long one, early enough for the
-    // atomic to return before the end (it adds one operation to wave 0's
-    // count, which at worst makes one wait cover a copy of the next step too)
-    const int claim = max(nsteps - 3, 0);
-    auto one = [&](int n, auto bufc) {
-        wait_vmcnt<(kRing - 2) * kCopiesPerStep>();
-        lds_barrier();  // step n visible to all; everyone is done with step n - 1
-        if (n == claim && tid == 0) nxt = atomicAdd(p.work, 1);
-        issue(n + kRing - 1);
-        if (nt_w > 0) compute(n, bufc);
-    };
-    for (int n = 0; n < nsteps; n += kRing) {
-        one(n, std::integral_constant<unsigned, 0>{});
-        if (n + 1 < nsteps) one(n + 1, std::integral_constant<unsigned, 1>{});
-        if (n + 2 < nsteps) one(n + 2, std::integral_constant<unsigned, 2>{});
-        if (n + 3 < nsteps) one(n + 3, std::integral_constant<unsigned, 3>{});
+        for (int n = 0; n < kRing - 1; ++n) issue(n);
+        // the next item is claimed three steps before this one ends: late enough
+        // that no claimed item waits behind a long one, early enough for the
+        // atomic to return before the end (it adds one operation to wave 0's
+        // count, which at worst makes one wait cover a copy of the next step too)
+        const int claim = s1 - 3 > sb ? s1 - 3 - sb : 0;
+        auto one = [&](int n, auto bufc) {
+            wait_vmcnt<(kRing - 2) * kCopiesPerStep>();
+            lds_barrier();  // step n visible to all; everyone is done with step n - 1
+            if (QUEUE && se == s1 && n == claim && tid == 0) nxt = atomicAdd(p.work, 1);
+            issue(n + kRing - 1);
+            if (nt_w > 0) compute(n, bufc);
+        };
+        for (int n = 0; n < nsteps; n += kRing) {
+            one(n, std::integral_constant<unsigned, 0>{});
+            if (n + 1 < nsteps) one(n + 1, std::integral_constant<unsigned, 1>{});
+            if (n + 2 < nsteps) one(n + 2, std::integral_constant<unsigned, 2>{});
+            if (n + 3 < nsteps) one(n + 3, std::integral_constant<unsigned, 3>{});
+        }
+        wait_vmcnt<0>();
+        sb = se;
     }
-    wait_vmcnt<0>();
 
     // ---- finish rows: total l over the four lanes of a row
 #pragma unroll
@@ -533,7 +565,7 @@ __device__ __forceinline__ void attn_item(const MfParams& p, const int r, const 
         lsum[j] += __shfl_xor(lsum[j], 32, 64);
     }
     uint16_t* outp = (uint16_t*)a.out;
-    if (nsplit == 1) {
+    if (whole) {
 #pragma unroll
         for (int j = 0; j < TPW; ++j) {
             const int row = row0 + 16 * (wave + kMfWaves * j) + lr;
@@ -555,9 +587,8 @@ __device__ __forceinline__ void attn_item(const MfParams& p, const int r, const 
         return;
     }
 
-    // ---- several splits: store this split's partial (m, l, unnormalised o);
-    // the merge kernel combines them after this kernel has ended
-    float* part = p.part + (((int64_t)rg * p.rc_max + rc) * p.max_splits + s) * kSlotFloats;
+    // ---- a part of the context: store its (m, l, unnormalised o); a merge kernel
+    // combines them after this kernel has ended
 #pragma unroll
     for (int j = 0; j < TPW; ++j) {
         const int rr = 16 * (wave + kMfWaves * j) + lr;
@@ -591,7 +622,13 @@ void attn_mfma_kernel(MfParams p) {
         const int4 e0 = p.list[2 * it];      // uniform: scalar loads
         const int4 e1 = p.list[2 * it + 1];
         int nxt = 0;  // claimed by thread 0 near the end of the item
-        attn_item<TPW>(p, e0.x, e0.y, e0.z, e0.w, e1.x, e1.y, e1.z, e1.w, lds0, nxt);
+        // {r, g, split, row chunk}, {q0, q_len, kv, splits}
+        int start, end;
+        split_range(e1.z, p.split, e0.z, start, end);
+        float* part = p.part + (((int64_t)(e0.x * p.a.Hkv + e0.y) * p.rc_max + e0.w) * p.max_splits + e0.z) *
+                                   (16 * kMfWaves * TPW * (kD + 2));
+        attn_item<TPW, true>(p, e0.x, e0.y, e0.w, e1.x, e1.y, e1.z, start / kStepTok,
+                             (end + kStepTok - 1) / kStepTok, e1.w == 1, part, lds0, nxt);
         __syncthreads();  // everyone is done with this item's LDS and s_item
         if (threadIdx.x == 0) s_item = nxt;
         __syncthreads();
@@ -599,11 +636,24 @@ void attn_mfma_kernel(MfParams p) {
     }
 }
 
+// One equal range of the batch per workgroup (attn_ranges.h).
+template <int TPW>
+__global__ __launch_bounds__(kMfThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void attn_mfma_ranges(MfParams p, Ranges rg) {
+    __shared__ __align__(16) unsigned char lds[kRing][2][kTileBytes];
+    uint32_t lds0 = (uint32_t)(uintptr_t)&lds[0][0][0];
+    asm volatile("" : "+s"(lds0));
+    range_walk<kStepTok>(rg, [&](int r, int g, int rc, int q0, int ql, int kv, int s0, int s1, int ns, int64_t slot) {
+        int none;
+        attn_item<TPW, false>(p, r, g, rc, q0, ql, kv, s0, s1, s0 == 0 && s1 == ns,
+                              rg.part + slot * (16 * kMfWaves * TPW * (kD + 2)), lds0, none);
+    });
+}
+
 // Combines the split partials of one 8-row group: 32 threads per row, four
 // values each.  The partials of up to kMergeBatch splits are loaded in one
 // round (o does not depend on the row max), then combined in split order
 // (bitwise reproducible).
-constexpr int kMergeBatch = 8;
 template <int TPW>
 __global__ __launch_bounds__(256) void attn_mfma_merge(MfParams p) {
     constexpr int kChunkRows = 16 * kMfWaves * TPW;
@@ -695,6 +745,27 @@ hipError_t launch_attn_mfma(const AttnArgs& a, void* ws, hipStream_t s) {
     p.list = (int4*)((char*)ws + g.counter_bytes);
     p.mlist = (int4*)((char*)ws + g.counter_bytes + g.list_bytes);
     p.part = (float*)((char*)ws + g.counter_bytes + g.list_bytes + g.mlist_bytes);
+    if (g.ranges) {
+        Ranges rg;
+        rg.a = a;
+        rg.group = g.group;
+        rg.chunk_rows = g.chunk_rows;
+        rg.by_head = 1;
+        rg.direct = g.direct;
+        rg.rc_max = g.rc_max;
+        rg.resident = (int)g.resident;
+        rg.min_units = kMfMinUnits;
+        rg.head = (int64_t*)ws;
+        rg.part = (float*)((char*)ws + range_head_bytes(a.R));
+        if (g.tpw == 2)
+            hipLaunchKernelGGL(attn_mfma_ranges<2>, dim3((unsigned)g.workers), dim3(kMfThreads), 0, s, p, rg);
+        else
+            hipLaunchKernelGGL(attn_mfma_ranges<1>, dim3((unsigned)g.workers), dim3(kMfThreads), 0, s, p, rg);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess || g.direct) return e;
+        return g.tpw == 2 ? launch_merge<false, 16 * kMfWaves * 2, kD, kStepTok>(rg, s)
+                          : launch_merge<false, 16 * kMfWaves, kD, kStepTok>(rg, s);
+    }
     hipLaunchKernelGGL(mf_plan, dim3(1), dim3(kPlanThreads), 0, s, p);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

@@ -6,17 +6,10 @@
 // request's keys and values.
 //
 // Work unit = one step (32 keys bf16, 16 keys fp32) of one (request, KV head,
-// row chunk of 16 * NT rows).  A workgroup is a single wave with its own LDS
-// ring, so nothing in the loop waits for another wave, and the units of the
-// whole batch, in (request, head, chunk, step) order, are cut into equal
-// contiguous ranges, one per wave: every wave streams the same number of keys
-// whatever the contexts' lengths are, and the kernel needs neither a plan
-// launch nor a work queue.  Each wave finds its range itself from a wave scan
-// over the requests (two dependent loads).  A range that ends inside a context
-// leaves a partial (m, l, unnormalised o); at most two per wave, so the
-// partials' size depends on the grid and not on the contexts.  attn_stream_merge
-// combines them in key order (bitwise reproducible).  Contexts that are short
-// for the whole batch (kDirectKeys) take one wave each and no merge.
+// row chunk of 16 * NT rows); the batch's units are cut into equal ranges, one
+// per worker (attn_ranges.h).  A worker is a single wave with its own K and V
+// buffers, so nothing in its loop waits for another wave.  Contexts that are
+// short for the whole batch (kDirectKeys) take one wave each and no merge.
 //
 //   * K and V rows are copied from their page straight into LDS
 //     (global_load_lds_dwordx4), one step ahead.  A 16-key half step lies
@@ -40,8 +33,7 @@
 #include <algorithm>
 #include <type_traits>
 
-#include "device_common.h"
-#include "kernels.h"
+#include "attn_ranges.h"
 
 namespace dspark {
 namespace stream {
@@ -57,9 +49,7 @@ typedef __attribute__((address_space(3))) u32x4 lds_u32x4;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 constexpr float kRescale = 8.0f;     // log2 headroom before the running max is moved
-constexpr int kCUs = 256;            // gfx950; sizes the grid and the partials
 constexpr int kMinUnits = 4;         // steps per wave, at least
-constexpr int kDirectKeys = 256;     // contexts up to this: one wave per (request, head, chunk)
 constexpr int kPageRegs = 2;         // page ids per lane: 128 pages in flight of a range
 constexpr int kMaxD = 256;
 
@@ -91,15 +81,12 @@ struct Cfg {
     static constexpr int cu(int nt) { return LdsWaves < 4 * eu(nt) ? LdsWaves : 4 * eu(nt); }
 };
 
-struct Params {
-    AttnArgs a;
-    int group, chunk_rows, rc_max, waves, direct;
+struct Params : Ranges {
     int64_t ks1b, vs1b;              // KV strides in bytes
     uint32_t ks0b, vs0b, ks2b, vs2b;
     int kbytes, vbytes;              // bytes of a key / value row
     int pad;                         // some row is shorter than the LDS row
     float scale2;
-    float* part;                     // [wave][2] {m[rows], l[rows], o[rows][Dp]}
 };
 
 // Physical chunk of chunk c in LDS row t: XORs that keep c inside its aligned
@@ -127,36 +114,6 @@ __device__ __forceinline__ int v_slot(int t, int c) {
 // 16 bytes of zeros (zero-initialised at load, never written): keys at or past
 // the context's end and the pad of short rows are copied from here.
 __device__ __align__(16) uint32_t g_zero[4];
-
-// Shape of request r: false when it is malformed (ql outside [1, max_q], kv
-// outside [ql, max_pages * page], rows outside [0, min(cu_q[R], R * max_q))).
-__device__ __forceinline__ bool shape_of(const AttnArgs& a, int r, int total_rows, int& q0, int& ql, int& kv) {
-    q0 = a.cu_q[r];
-    ql = a.cu_q[r + 1] - q0;
-    kv = a.kv_len[r];
-    if (ql < 1 || ql > a.max_q || kv < ql || kv > a.max_pages * a.page) return false;
-    return q0 >= 0 && (int64_t)q0 + ql <= total_rows;
-}
-
-template <int STEP>
-__device__ __forceinline__ int64_t units_of(const Params& p, int r, int total_rows) {
-    int q0, ql, kv;
-    if (!shape_of(p.a, r, total_rows, q0, ql, kv)) return 0;
-    const int ns = (kv + STEP - 1) / STEP;
-    const int nrc = (ql * p.group + p.chunk_rows - 1) / p.chunk_rows;
-    return (int64_t)p.a.Hkv * nrc * ns;  // below 2^31 (checked on the host)
-}
-
-__device__ __forceinline__ int64_t wave_sum_i64(int64_t v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, DSPARK_WAVE);
-    return v;
-}
-
-__device__ __forceinline__ int64_t units_per_wave(const Params& p, int64_t total) {
-    const int64_t per = (total + p.waves - 1) / p.waves;
-    return per < kMinUnits ? kMinUnits : per;
-}
 
 // The wait is the builtin, which the compiler counts: with every ordinary load
 // waited for before the step loop, it adds no wait of its own inside it.
@@ -534,176 +491,16 @@ void attn_stream_kernel(Params p) {
     __shared__ __align__(16) unsigned char lds[2 * C::TileB];
     uint32_t lds0 = (uint32_t)(uintptr_t)&lds[0];
     asm volatile("" : "+s"(lds0));
-    const AttnArgs& a = p.a;
-    const int lane = threadIdx.x;
-    const int total_rows = min(max(a.cu_q[a.R], 0), a.R * a.max_q);
-    int q0, ql, kv;
-    if (p.direct) {  // one (request, head, chunk) per workgroup
-        int b = blockIdx.x;
-        const int rc = b % p.rc_max;
-        b /= p.rc_max;
-        const int g = b % a.Hkv, r = b / a.Hkv;
-        if (!shape_of(a, r, total_rows, q0, ql, kv) || rc * (16 * NT) >= ql * p.group) return;
-        const int ns = (kv + C::Step - 1) / C::Step;
-        attend<F32, CH, NT>(p, lds0, r, g, rc, q0, ql, kv, 0, ns, ns, 0);
-        return;
-    }
-    // this wave's range [u, u1) of the batch's units
-    const int64_t n0 = lane < a.R ? units_of<C::Step>(p, lane, total_rows) : 0;
-    int64_t total = n0;
-    for (int b = DSPARK_WAVE; b < a.R; b += DSPARK_WAVE)
-        total += b + lane < a.R ? units_of<C::Step>(p, b + lane, total_rows) : 0;
-    total = wave_sum_i64(total);
-    const int64_t per = units_per_wave(p, total);
-    const int64_t u0 = (int64_t)blockIdx.x * per;
-    if (u0 >= total) return;
-    const int64_t u1 = min(total, u0 + per);
-    // the request that holds unit u0, and its first unit
-    int r = 0;
-    int64_t ur = 0, before = 0;
-    for (int b = 0; b < a.R; b += DSPARK_WAVE) {
-        int64_t n = n0;
-        if (b > 0) n = b + lane < a.R ? units_of<C::Step>(p, b + lane, total_rows) : 0;
-        int64_t incl = n;
-#pragma unroll
-        for (int o = 1; o < DSPARK_WAVE; o <<= 1) {
-            const int64_t t = __shfl_up(incl, o, DSPARK_WAVE);
-            if (lane >= o) incl += t;
-        }
-        const unsigned long long hit = __ballot(before + incl > u0);
-        if (hit) {
-            const int l = (int)__builtin_ctzll(hit);
-            r = b + l;
-            ur = before + __shfl(incl - n, l, DSPARK_WAVE);
-            break;
-        }
-        before += __shfl(incl, DSPARK_WAVE - 1, DSPARK_WAVE);
-    }
-    r = __builtin_amdgcn_readfirstlane(r);
-    int64_t u = u0;
-    while (u < u1) {
-        const bool ok = shape_of(a, r, total_rows, q0, ql, kv);
-        const int ns = (kv + C::Step - 1) / C::Step;
-        const int nrc = (ql * p.group + 16 * NT - 1) / (16 * NT);
-        const int units = ok ? a.Hkv * nrc * ns : 0;
-        int local = (int)(u - ur);
-        while (local < units && u < u1) {
-            const int item = local / ns;
-            const int s0 = local - item * ns;
-            const int s1 = (int)min((int64_t)ns, s0 + (u1 - u));
-            const int g = item / nrc;
-            attend<F32, CH, NT>(p, lds0, __builtin_amdgcn_readfirstlane(r), __builtin_amdgcn_readfirstlane(g),
-                                __builtin_amdgcn_readfirstlane(item - g * nrc), __builtin_amdgcn_readfirstlane(q0),
-                                __builtin_amdgcn_readfirstlane(ql), __builtin_amdgcn_readfirstlane(kv),
-                                __builtin_amdgcn_readfirstlane(s0), __builtin_amdgcn_readfirstlane(s1),
-                                __builtin_amdgcn_readfirstlane(ns), 2 * (int64_t)blockIdx.x + (u != u0));
-            local += s1 - s0;
-            u += s1 - s0;
-        }
-        ur += units;
-        ++r;
-    }
-}
-
-// Combines the partials of every (request, head, chunk) whose units several
-// waves shared, in key order.  Workgroups (request and head, part of the rows);
-// a thread takes four values of a row; up to kMergeBatch partials are in
-// flight.  A chain of dependent loads (lengths, then partials), so the rows are
-// spread over up to kMergeParts workgroups.
-constexpr int kMergeThreads = 256;
-constexpr int kMergeBatch = 8;
-constexpr int kMergeParts = 8;
-template <bool F32, int CH, int NT>
-__global__ __launch_bounds__(kMergeThreads) void attn_stream_merge(Params p) {
-    typedef Cfg<F32, CH> C;
-    constexpr int kRows = 16 * NT;
-    constexpr int64_t kSlot = (int64_t)kRows * (C::Dp + 2);
-    __shared__ int64_t s_sum[2][kMergeThreads / DSPARK_WAVE];
-    const AttnArgs& a = p.a;
-    const int tid = threadIdx.x;
-    const int r = blockIdx.x / a.Hkv, g = blockIdx.x % a.Hkv;
-    const int total_rows = min(max(a.cu_q[a.R], 0), a.R * a.max_q);
-    int64_t total = 0, ur = 0;
-    for (int b = tid; b < a.R; b += kMergeThreads) {
-        const int64_t n = units_of<C::Step>(p, b, total_rows);
-        total += n;
-        if (b < r) ur += n;
-    }
-    total = wave_sum_i64(total);
-    ur = wave_sum_i64(ur);
-    if ((tid & 63) == 0) {
-        s_sum[0][tid >> 6] = total;
-        s_sum[1][tid >> 6] = ur;
-    }
-    __syncthreads();
-    total = ur = 0;
-#pragma unroll
-    for (int w = 0; w < kMergeThreads / DSPARK_WAVE; ++w) {
-        total += s_sum[0][w];
-        ur += s_sum[1][w];
-    }
-    int q0, ql, kv;
-    if (!shape_of(a, r, total_rows, q0, ql, kv)) return;
-    const int64_t per = units_per_wave(p, total);
-    const int ns = (kv + C::Step - 1) / C::Step;
-    const int rows = ql * p.group;
-    const int nrc = (rows + kRows - 1) / kRows;
-    const int groups = a.Dv / 4;
-    for (int i = blockIdx.y * kMergeThreads + tid; i < rows * groups; i += gridDim.y * kMergeThreads) {
-        const int row = i / groups, c4 = (i - row * groups) * 4;
-        const int rc = row / kRows, rr = row - rc * kRows;
-        const int64_t u0 = ur + (int64_t)(g * nrc + rc) * ns;  // the chunk's units [u0, u0 + ns)
-        const int64_t w0 = u0 / per, w1 = (u0 + ns - 1) / per;
-        if (w0 == w1) continue;  // one wave had them all and wrote the rows
-        // wave w0's partial is its first when its range starts with this chunk
-        const int64_t first = 2 * w0 + (w0 * per != u0);
-        float M = -__builtin_huge_valf(), L = 0.0f;
-        f32x4 o = f32x4{0.f, 0.f, 0.f, 0.f};
-        for (int64_t w = w0; w <= w1; w += kMergeBatch) {
-            float ms[kMergeBatch], ls[kMergeBatch];
-            f32x4 os[kMergeBatch];
-#pragma unroll
-            for (int k = 0; k < kMergeBatch; ++k) {
-                const int64_t wk = min(w + k, w1);
-                const float* sl = p.part + (wk == w0 ? first : 2 * wk) * kSlot;
-                ms[k] = sl[rr];
-                ls[k] = sl[kRows + rr];
-                os[k] = *(const f32x4*)(sl + 2 * kRows + (int64_t)rr * C::Dp + c4);
-            }
-            float Mb = M;
-#pragma unroll
-            for (int k = 0; k < kMergeBatch; ++k)
-                if (w + k <= w1) Mb = vmax(Mb, ms[k]);
-            if (M > -__builtin_huge_valf() && Mb != M) {
-                const float f = exp2f(M - Mb);
-                L *= f;
-                o *= f;
-            }
-            M = Mb;
-#pragma unroll
-            for (int k = 0; k < kMergeBatch; ++k) {
-                if (w + k > w1) break;
-                const float f = ms[k] == -__builtin_huge_valf() ? 0.0f : exp2f(ms[k] - M);
-                L += ls[k] * f;
-                o += f * os[k];
-            }
-        }
-        const int t = row / p.group;
-        const int64_t orow = (int64_t)(q0 + t) * a.Hq + g * p.group + (row - t * p.group);
-        const float inv = 1.0f / L;
-        if (F32) *(f32x4*)((float*)a.out + orow * a.Dv + c4) = o * inv;
-        else
-            *(uint2*)((uint16_t*)a.out + orow * a.Dv + c4) =
-                uint2{pack2_bf16(o[0] * inv, o[1] * inv), pack2_bf16(o[2] * inv, o[3] * inv)};
-        if (a.lse && c4 == 0) a.lse[orow] = (M + log2f(L)) * kLn2;
-    }
+    range_walk<C::Step>(p, [&](int r, int g, int rc, int q0, int ql, int kv, int s0, int s1, int ns, int64_t slot) {
+        attend<F32, CH, NT>(p, lds0, r, g, rc, q0, ql, kv, s0, s1, ns, slot);
+    });
 }
 
 // ------------------------------------------------------------------ host
 
 struct Geom {
     int ch, nt, rc_max, direct;
-    int64_t waves;        // grid of the attention kernel
+    int64_t resident, waves;  // ranges; grid of the attention kernel
     size_t part_bytes;
 };
 
@@ -753,7 +550,8 @@ static Geom geom(const AttnArgs& a) {
     with_cfg(a.bf16, g.ch, g.nt, [&](auto f32, auto ch, auto nt) {
         typedef Cfg<decltype(f32)::value, decltype(ch)::value> C;
         const int64_t units = items * ((max_kv + C::Step - 1) / C::Step);
-        g.waves = g.direct ? items : std::min<int64_t>((int64_t)kCUs * C::cu(decltype(nt)::value), (units + kMinUnits - 1) / kMinUnits);
+        g.resident = kRangeCUs * C::cu(decltype(nt)::value);
+        g.waves = g.direct ? items : std::min<int64_t>(g.resident, (units + kMinUnits - 1) / kMinUnits);
         if (!g.direct) g.part_bytes = (size_t)g.waves * 2 * (16 * decltype(nt)::value) * (C::Dp + 2) * sizeof(float);
         return 0;
     });
@@ -782,7 +580,10 @@ bool attn_stream_supported(const AttnArgs& a) {
            (uintptr_t)a.out % (a.bf16 ? 8 : 16) == 0;
 }
 
-size_t attn_stream_workspace(const AttnArgs& a) { return stream::geom(a).part_bytes; }
+size_t attn_stream_workspace(const AttnArgs& a) {
+    const stream::Geom g = stream::geom(a);
+    return g.direct ? 0 : range_head_bytes(a.R) + g.part_bytes;
+}
 
 hipError_t launch_attn_stream(const AttnArgs& a, void* ws, hipStream_t s) {
     const stream::Geom g = stream::geom(a);
@@ -792,7 +593,9 @@ hipError_t launch_attn_stream(const AttnArgs& a, void* ws, hipStream_t s) {
     p.group = a.Hq / a.Hkv;
     p.chunk_rows = 16 * g.nt;
     p.rc_max = g.rc_max;
-    p.waves = (int)g.waves;
+    p.by_head = 0;
+    p.resident = (int)g.resident;
+    p.min_units = stream::kMinUnits;
     p.direct = g.direct;
     p.ks0b = (uint32_t)(a.ks[0] * esz);
     p.ks1b = a.ks[1] * esz;
@@ -804,18 +607,15 @@ hipError_t launch_attn_stream(const AttnArgs& a, void* ws, hipStream_t s) {
     p.vbytes = (int)(a.Dv * esz);
     p.pad = p.kbytes != 16 * g.ch || p.vbytes != 16 * g.ch;
     p.scale2 = a.scale * stream::kLog2e;
-    p.part = (float*)ws;
+    p.head = (int64_t*)ws;
+    p.part = (float*)((char*)ws + range_head_bytes(a.R));
     return stream::with_cfg(a.bf16, g.ch, g.nt, [&](auto f32, auto ch, auto nt) {
         constexpr bool F = decltype(f32)::value;
         constexpr int CH = decltype(ch)::value, NT = decltype(nt)::value;
         hipLaunchKernelGGL((stream::attn_stream_kernel<F, CH, NT>), dim3((unsigned)g.waves), dim3(DSPARK_WAVE), 0, s, p);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess || g.direct) return e;
-        const int64_t quads = (int64_t)a.max_q * p.group * (a.Dv / 4);  // of a (request, head), at most
-        const int64_t parts = std::min<int64_t>(stream::kMergeParts, (quads + stream::kMergeThreads - 1) / stream::kMergeThreads);
-        hipLaunchKernelGGL((stream::attn_stream_merge<F, CH, NT>), dim3((unsigned)(a.R * a.Hkv), (unsigned)parts),
-                           dim3(stream::kMergeThreads), 0, s, p);
-        return hipGetLastError();
+        return launch_merge<F, 16 * NT, stream::Cfg<F, CH>::Dp, stream::Cfg<F, CH>::Step>(p, s);
     });
 }
 

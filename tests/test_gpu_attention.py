@@ -405,3 +405,38 @@ def test_any_head_size_and_page(dtype, Dqk, Dv, page, Hq, Hkv, q_len, kv_len):
     o4 = to_f64(out4)
     assert (o4[: cu[1]] == 7.0).all()
     assert row_rel_err(o4[cu[1]:], ref[cu[1]:]).max() <= TOL[dtype]
+
+
+@pytest.mark.parametrize("R,Hkv,q_len,kv_len", [
+    (3, 8, [1, 5, 17], [64, 200, 256]),             # one workgroup per (request, head): no merge
+    (64, 8, [2], [512, 257]),                       # the same up to 512 keys when they fill the part
+    (3, 8, [1, 5, 17], [257, 4097, 2000]),          # several workgroups per context
+    (2, 1, [17, 3], [8192, 8193]),                  # more than a window of 64 pages
+    (5, 3, [1, 2, 9, 4, 3], [40, 900, 33, 65, 1]),  # a head count that does not divide the part
+])
+def test_ranges_and_queue_agree(R, Hkv, q_len, kv_len):
+    """The cut of a batch into ranges against the work queue: the same inputs
+    with the block table as it is, and widened with unused slots until the
+    host's bound on the contexts makes the batch a large one."""
+    import torch
+    w = synth.scaled(synth.WORKLOADS["mid"], R=R, Hq=4 * Hkv, Hkv=Hkv)
+    q_len = np.resize(q_len, R)
+    kv = synth.paged_kv(w, 51, kv_len=np.maximum(np.resize(kv_len, R), q_len).astype(np.int32))
+    cu = oracle.cu_from_len(q_len - 1)
+    q = synth.query_rows(w, 51, synth.flat_keys(q_len))
+    log(f"[attn] ranges and queue: R={R} Hkv={Hkv} q_len={list(q_len[:5])} kv={list(kv.kv_len[:5])}")
+    out, lse = gpu_attention(w, DevKV(kv, True), q, cu)
+    wide = DevKV(kv, True)
+    pad = torch.full((R, 320 * 512 // Hkv // R // 2 + 64), int(kv.n_pages), dtype=torch.int32, device=wide.bt.device)
+    wide.bt = torch.cat([wide.bt, pad], 1).contiguous()
+    out2, lse2 = gpu_attention(w, wide, q, cu)
+    rows = sorted({(int(t), int(h)) for t, h in zip(np.random.default_rng(1).integers(0, cu[-1], 300),
+                                                    np.random.default_rng(2).integers(0, w.Hq, 300))})
+    ref, ref_lse = oracle.verify_attn(q, kv.k, kv.v, kv.k_strides, kv.v_strides, kv.block_table, kv.kv_len, cu, w.Hq, w.Hkv,
+                                      w.Dqk, w.Dv, w.page, w.scale, w.dtype, rows=rows)
+    for o, l in ((out, lse), (out2, lse2)):
+        o, l = to_f64(o), to_f64(l)
+        assert row_rel_err(np.stack([o[t, h] for t, h in rows]), ref).max() <= TOL["bf16"]
+        np.testing.assert_allclose(np.array([l[t, h] for t, h in rows]), ref_lse, rtol=0, atol=1e-4)
+    # both round P to bf16 and the output once: each is within 2^-7 of a row
+    assert row_rel_err(to_f64(out), to_f64(out2)).max() <= 2.0 ** -7
