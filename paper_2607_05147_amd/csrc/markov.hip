@@ -13,21 +13,22 @@
 // logits, V % 4 == 0, a grid the device holds at once; md_check after the
 // block), which keeps z in registers across two grid-wide
 // exchanges so that the projection and the base logits are read once and p
-// is written once, or the three launches:
+// is written once, or the two launches:
 //   md_tile   one workgroup per 128 vocabulary entries: W2^T e for every
 //             request on v_mfma_f32_16x16x32_bf16 (the tile's W2t rows stay in
 //             registers as A operands, the embeddings stream through LDS in
 //             chunks of 32 requests as B operands), plus the base logits; z is
 //             written to draft_p in fp32, with the tile's softmax statistics
 //             (max, sum of exp) per request;
-//   md_stats  one wave per request: the row's max and total and the tile in
-//             which the running mass passes u * total (fp64 prefix over the
-//             tiles in vocabulary order);
 //   md_norm   a streaming pass over draft_p that turns z into
-//             p_k = exp(z - max) / total in place; the workgroup whose segment
+//             p_k = exp(z - max) / total in place; each workgroup first computes
+//             its row's max and total and the tile in which the running mass
+//             passes u * total (fp64 prefix over the tiles in vocabulary order),
+//             behind its loads of z; the workgroup whose segment
 //             holds a request's draw makes it (fp64 prefix of that tile's
 //             masses), writes x_k, gathers e_{k+1} into the other embedding
 //             buffer and writes c_{k+1}.
+// A small batch runs all positions in one launch, md_block.
 // The positions of a block are sequential by definition (x_k feeds position
 // k + 1).
 #include <algorithm>
@@ -59,6 +60,7 @@ __host__ __device__ constexpr int ceil_div(int a, int b) { return (a + b - 1) / 
 constexpr int kCoGroups = 8;
 constexpr int kSyncStride = 32;
 constexpr int kSyncWords = kSyncStride * (1 + 2 * kCoGroups);
+constexpr int kTokBytes = 2 * 32 * 8;  // md_block's tokens of two positions
 
 // Slot of 16-byte chunk c in row t of the embedding chunk (nch chunks per row,
 // a power of two).  The XOR (bits of t in the order 0, 2, 1, 3) puts the 16
@@ -348,7 +350,7 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NT == 
     }
 }
 
-// ---------------------------------------------------------------- md_stats
+// --------------------------------------------------------------- row_stats
 
 // Per request (one wave): the row maximum and total from the tile statistics
 // (tile masses in fp64), and the tile in which the running mass passes
@@ -398,8 +400,9 @@ __device__ __forceinline__ RowInfo ld_info(const RowInfo* p) {
     return v;
 }
 
-// SC: the statistics are read and the row's RowInfo written device-coherently.
-template <int P, bool SC>
+// SC: the statistics are read device-coherently; SCS: the row's RowInfo (info[r])
+// is written so.
+template <int P, bool SC, bool SCS = SC>
 __device__ __forceinline__ void row_stats(const MarkovArgs& a, const float2* stats, RowInfo* info, int ntiles,
                                           int k, int r, int lane) {
     const float2* st = stats + (int64_t)r * ntiles;
@@ -463,28 +466,14 @@ __device__ __forceinline__ void row_stats(const MarkovArgs& a, const float2* sta
                 ri.tile = lastpos;
                 ri.thr = __builtin_huge_val();
             }
-            st_info<SC>(info + r, ri);
+            st_info<SCS>(info + r, ri);
         }
     } else if (lane == 0) {
         // rounding pushed u * total past the end: the row's last tile with mass
         ri.tile = max(last, 0);
         ri.thr = __builtin_huge_val();
-        st_info<SC>(info + r, ri);
+        st_info<SCS>(info + r, ri);
     }
-}
-
-template <int P>
-__global__ __launch_bounds__(DSPARK_WAVE) void md_stats(MarkovArgs a, const float2* stats, RowInfo* info,
-                                                        int ntiles, int k) {
-    row_stats<P, false>(a, stats, info, ntiles, k, blockIdx.x, threadIdx.x);
-}
-
-inline void stats_pass(const MarkovArgs& a, const float2* stats, RowInfo* info, int ntiles, int k,
-                       hipStream_t s) {
-    if (ntiles <= DSPARK_WAVE * 16)
-        hipLaunchKernelGGL(md_stats<16>, dim3(a.R), dim3(DSPARK_WAVE), 0, s, a, stats, info, ntiles, k);
-    else
-        hipLaunchKernelGGL(md_stats<kStatsMaxPer>, dim3(a.R), dim3(DSPARK_WAVE), 0, s, a, stats, info, ntiles, k);
 }
 
 // ----------------------------------------------------------------- md_norm
@@ -503,16 +492,31 @@ constexpr int kNormV = 8192;
 constexpr int kNormIt = kNormV / (4 * kThreads);  // float4 groups per thread
 static_assert(kNormV % kTileV == 0, "a tile lies inside one segment");
 
-template <bool VEC>
-__global__ __launch_bounds__(kThreads) void md_norm(MarkovArgs a, const RowInfo* info, uint16_t* E_next,
+template <bool VEC, int P>
+__global__ __launch_bounds__(kThreads) void md_norm(MarkovArgs a, const float2* stats, int ntiles, uint16_t* E_next,
                                                     const float* sh, int k) {
+    __shared__ RowInfo s_ri;
     const int r = blockIdx.x;
     const int tid = threadIdx.x, lane = tid & 63;
     const int s0 = blockIdx.y * kNormV;
     const int s1 = min(a.V, s0 + kNormV);
     const int64_t row = (int64_t)r * a.K + (k - 1);
     float* p = a.draft_p + row * a.V;
-    const RowInfo ri = info[r];
+    // every z load of the thread first, then the row's statistics (wave 0), which
+    // the loads cover
+    float4 zv[VEC ? kNormIt : 1];
+    float zs[VEC ? 1 : 4 * kNormIt];
+    if (VEC) {
+#pragma unroll
+        for (int i = 0; i < kNormIt; ++i)
+            zv[i] = *(const float4*)(p + min(s0 + 4 * (tid + i * kThreads), s1 - 4));
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4 * kNormIt; ++i) zs[i] = p[min(s0 + tid + i * kThreads, s1 - 1)];
+    }
+    if (tid < DSPARK_WAVE) row_stats<P, false>(a, stats, &s_ri - r, ntiles, k, r, lane);
+    __syncthreads();
+    const RowInfo ri = s_ri;
     const float inv = 1.0f / ri.S;
     const int tb = ri.tile * kTileV;
     const bool draws = tb >= s0 && tb < s1;  // the same in the whole workgroup
@@ -529,10 +533,6 @@ __global__ __launch_bounds__(kThreads) void md_norm(MarkovArgs a, const RowInfo*
     if (VEC) {
         // V % 4 == 0: groups start at multiples of 4, so a group is wholly
         // inside or outside the draw tile and the row
-        float4 zv[kNormIt];
-#pragma unroll
-        for (int i = 0; i < kNormIt; ++i)
-            zv[i] = *(const float4*)(p + min(s0 + 4 * (tid + i * kThreads), s1 - 4));
 #pragma unroll
         for (int i = 0; i < kNormIt; ++i) {
             const int v = s0 + 4 * (tid + i * kThreads);
@@ -543,9 +543,6 @@ __global__ __launch_bounds__(kThreads) void md_norm(MarkovArgs a, const RowInfo*
                                            __builtin_amdgcn_exp2f(zv[i].w - ri.M) * inv};
         }
     } else {
-        float zs[4 * kNormIt];
-#pragma unroll
-        for (int i = 0; i < 4 * kNormIt; ++i) zs[i] = p[min(s0 + tid + i * kThreads, s1 - 1)];
 #pragma unroll
         for (int i = 0; i < 4 * kNormIt; ++i) {
             const int v = s0 + tid + i * kThreads;
@@ -588,20 +585,22 @@ __global__ __launch_bounds__(kThreads) void md_norm(MarkovArgs a, const RowInfo*
 }
 
 // One position after the embeddings E are in place: md_tile over every
-// vocabulary tile (z and the tile statistics), md_stats, then md_norm, which
+// vocabulary tile (z and the tile statistics), then md_norm, which
 // draws x_k and gathers the next embedding into En.
 template <int KS, int NT>
-void position(const MarkovArgs& a, const uint16_t* E, float2* stats, RowInfo* info, uint16_t* En,
+void position(const MarkovArgs& a, const uint16_t* E, float2* stats, uint16_t* En,
               const float* shp, int ntiles, int k, bool vec, hipStream_t s) {
     const dim3 g(ntiles), b(kThreads);
     if (vec && a.base_bf16) hipLaunchKernelGGL((md_tile<KS, NT, true, true>), g, b, 0, s, a, E, stats, ntiles, k);
     else if (vec) hipLaunchKernelGGL((md_tile<KS, NT, true, false>), g, b, 0, s, a, E, stats, ntiles, k);
     else if (a.base_bf16) hipLaunchKernelGGL((md_tile<KS, NT, false, true>), g, b, 0, s, a, E, stats, ntiles, k);
     else hipLaunchKernelGGL((md_tile<KS, NT, false, false>), g, b, 0, s, a, E, stats, ntiles, k);
-    stats_pass(a, stats, info, ntiles, k, s);
     const dim3 gn(a.R, ceil_div(a.V, kNormV));
-    if (vec) hipLaunchKernelGGL(md_norm<true>, gn, b, 0, s, a, (const RowInfo*)info, En, shp, k);
-    else hipLaunchKernelGGL(md_norm<false>, gn, b, 0, s, a, (const RowInfo*)info, En, shp, k);
+#define DS_NORM(VECV, P) hipLaunchKernelGGL((md_norm<VECV, P>), gn, b, 0, s, a, (const float2*)stats, ntiles, En, shp, k)
+    if (ntiles <= DSPARK_WAVE * 4) { if (vec) DS_NORM(true, 4); else DS_NORM(false, 4); }
+    else if (ntiles <= DSPARK_WAVE * 16) { if (vec) DS_NORM(true, 16); else DS_NORM(false, 16); }
+    else { if (vec) DS_NORM(true, kStatsMaxPer); else DS_NORM(false, kStatsMaxPer); }
+#undef DS_NORM
 }
 
 // ----------------------------------------------------------------- md_coop
@@ -624,8 +623,8 @@ void position(const MarkovArgs& a, const uint16_t* E, float2* stats, RowInfo* in
 //      accumulators (128 AGPRs per lane), and the per-tile statistics (max,
 //      sum of 2^(z - max)) go to memory;
 //   -  grid barrier;
-//   B  one wave per request: row maximum, total and draw tile (the md_stats
-//      computation);
+//   B  one wave per request: row maximum, total and draw tile
+//      (row_stats);
 //   -  grid barrier;
 //   C  the draws of the requests whose draw tile a workgroup owns, eight at
 //      a time, one per wave: the tile's masses go through LDS, then the fp64
@@ -673,7 +672,9 @@ struct CoopArgs {
 // to the loads and the row statistics.
 __device__ __forceinline__ void pin_acc(f32x4& v) { asm volatile("" : "+a"(v)); }
 
-__device__ __forceinline__ void grid_barrier(unsigned* sync, unsigned b) {
+// Arrival at barrier b of this workgroup, whose earlier stores are complete, and
+// the wait for the others; the work between the two is not ordered by the barrier.
+__device__ __forceinline__ void grid_arrive(unsigned* sync, unsigned b) {
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
     __builtin_amdgcn_s_waitcnt(0);  // this thread's stores are complete
     __syncthreads();
@@ -687,7 +688,12 @@ __device__ __forceinline__ void grid_barrier(unsigned* sync, unsigned b) {
                 __hip_atomic_store(sync + kSyncStride * (1 + kCoGroups + y), b, __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
         }
-        unsigned* flag = sync + kSyncStride * (1 + kCoGroups + x);
+    }
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+}
+__device__ __forceinline__ void grid_wait(unsigned* sync, unsigned b) {
+    if (threadIdx.x == 0) {
+        unsigned* flag = sync + kSyncStride * (1 + kCoGroups + blockIdx.x % kCoGroups);
         const uint64_t t0 = wall_clock64();
         while (__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < b &&
                __hip_atomic_load(sync + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u) {
@@ -698,6 +704,10 @@ __device__ __forceinline__ void grid_barrier(unsigned* sync, unsigned b) {
     }
     __syncthreads();
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
+}
+__device__ __forceinline__ void grid_barrier(unsigned* sync, unsigned b) {
+    grid_arrive(sync, b);
+    grid_wait(sync, b);
 }
 
 template <int KS, int NT>
@@ -1025,7 +1035,11 @@ bool coop_applies(const MarkovArgs& a, int ntiles, bool vec) {
 // pitch 80 bytes) and shared by the four waves.  d % 8 == 0, so a lane's 8
 // inputs are either all inside the row or all past its end.
 constexpr int kHpRows = 64, kHpCols = 128, kHpNt = kHpCols / 16, kHpPitch = 40;
-__global__ __launch_bounds__(kThreads) void rnn_hproj(MarkovArgs a, float* Hp) {
+// The inputs are cut into gridDim.z parts, whose partial products (Hp + part * rows *
+// 3 rank) the readers add in order: a step is a load, a barrier and eight products,
+// so one workgroup for all 4096 inputs is a chain of 128 of them whatever the
+// number of rows (81 us for 512 rows and for 2048).  Parts: 18 us for 512 rows.
+__global__ __launch_bounds__(kThreads) void rnn_hproj(MarkovArgs a, float* Hp, int per) {
     __shared__ __align__(16) uint16_t sb[2][kHpCols * kHpPitch];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int lr = lane & 15, lq = lane >> 4;
@@ -1047,7 +1061,8 @@ __global__ __launch_bounds__(kThreads) void rnn_hproj(MarkovArgs a, float* Hp) {
         brow[i] = a.Wrnn + (int64_t)min(n0 + (c >> 2), ncols - 1) * nz + 2 * a.rank;
         bdst[i] = (c >> 2) * kHpPitch + 8 * bpart[i];
     }
-    const int nsteps = ceil_div(a.d, 32);
+    const int first = blockIdx.z * per, nsteps = min(ceil_div(a.d, 32), first + per);
+    Hp += (int64_t)blockIdx.z * nrows * ncols;
     auto load_a = [&](int st) {
         const int kk = 32 * st + 8 * lq;
         const bool in = st < nsteps && kk < a.d;
@@ -1067,12 +1082,12 @@ __global__ __launch_bounds__(kThreads) void rnn_hproj(MarkovArgs a, float* Hp) {
 #pragma unroll
     for (int nt = 0; nt < kHpNt; ++nt) acc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
     uint4 vb[2];
-    load_b(0, vb);
-    bf16x8 a_cur = load_a(0), a_next = load_a(1);
+    load_b(first, vb);
+    bf16x8 a_cur = load_a(first), a_next = load_a(first + 1);
 #pragma unroll
-    for (int i = 0; i < 2; ++i) *(uint4*)(&sb[0][bdst[i]]) = vb[i];
+    for (int i = 0; i < 2; ++i) *(uint4*)(&sb[first & 1][bdst[i]]) = vb[i];
     __syncthreads();
-    for (int st = 0; st < nsteps; ++st) {
+    for (int st = first; st < nsteps; ++st) {
         load_b(st + 1, vb);  // the next step's tile stays in flight during the products
         const uint16_t* cur = sb[st & 1];
 #pragma unroll
@@ -1097,6 +1112,14 @@ __global__ __launch_bounds__(kThreads) void rnn_hproj(MarkovArgs a, float* Hp) {
             if (row < nrows && col < ncols) Hp[(int64_t)row * ncols + col] = acc[nt][e];
         }
     }
+}
+
+// Parts of the backbone projection, at most: three workgroups per CU or so, and a
+// part per wave of the recurrence, which adds them to its products.
+constexpr int kHpParts = 8;
+inline int hp_parts(int R, int K, int rank) {
+    const int64_t wgs = (((int64_t)R * K + kHpRows - 1) / kHpRows) * ceil_div(3 * rank, kHpCols);
+    return (int)std::min<int64_t>(kHpParts, std::max<int64_t>(1, 768 / wgs));
 }
 
 // hi + mid (+ lo): each term the bf16 rounding of what the previous ones
@@ -1126,16 +1149,17 @@ __device__ __forceinline__ void split3(float v, uint16_t* dst, int stride) {
 // tanh(a_c) with g = sigmoid(a_g), written in fp32 and as three terms, and the
 // head's output o_k = tanh(a_o) as two terms (hi, mid) for the vocabulary
 // product.  A workgroup owns
-// 16 dims x 16 requests; its four waves take every fourth 32-input step (both
-// operands straight from memory, kStDepth steps ahead) and wave 0 adds the
-// four partial products in wave order.  The state is double-buffered (others
+// 16 dims x 16 requests; its eight waves take every eighth 32-input step (both
+// operands straight from memory, kStDepth steps ahead: all of them at rank 256) and
+// wave 0 adds the eight partial products in wave order.  The state is double-buffered (others
 // may still read s_{k-1}); at k = 1 it is zero and its steps are skipped.
-constexpr int kStJ = 16, kStR = 16, kStDepth = 4;
-__global__ __launch_bounds__(kThreads) void rnn_state(MarkovArgs a, const float* Hp,
+constexpr int kStJ = 16, kStR = 16, kStDepth = 4, kStWaves = 8;
+static_assert(kHpParts <= kStWaves && kHpParts <= kCoWaves, "a part of the backbone projection per wave");
+__global__ __launch_bounds__(kStWaves * DSPARK_WAVE) void rnn_state(MarkovArgs a, const float* Hp, int hpz,
                                                       const float* s_prev, const uint16_t* S3_prev,
                                                       float* s_next, uint16_t* S3_next,
                                                       const uint16_t* Ee, uint16_t* E2, int k) {
-    __shared__ f32x4 part[kWaves - 1][3][DSPARK_WAVE];
+    __shared__ f32x4 part[kStWaves - 1][3][DSPARK_WAVE];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int lr = lane & 15, lq = lane >> 4;
     const int rank = a.rank, nz = 2 * rank + a.d;
@@ -1146,7 +1170,7 @@ __global__ __launch_bounds__(kThreads) void rnn_state(MarkovArgs a, const float*
     const int st0 = (k > 1 ? 0 : ks_s) + wave;  // this wave's steps: st0, st0 + 4, ...
     bf16x8 af[kStDepth], bfr[kStDepth][3];
     auto load = [&](int i, int slot) {  // this wave's i-th step
-        const int kk = 32 * min(st0 + kWaves * i, nst - 1) + 8 * lq;  // past the end: unused
+        const int kk = 32 * min(st0 + kStWaves * i, nst - 1) + 8 * lq;  // past the end: unused
         const bool state = kk < 3 * rank;                            // uniform over the wave
         af[slot] = state ? *(const bf16x8*)(S3_prev + (int64_t)ra * 3 * rank + kk)
                          : *(const bf16x8*)(Ee + (int64_t)ra * rank + (kk - 3 * rank));
@@ -1155,21 +1179,19 @@ __global__ __launch_bounds__(kThreads) void rnn_state(MarkovArgs a, const float*
         for (int p = 0; p < 3; ++p)
             bfr[slot][p] = *(const bf16x8*)(a.Wrnn + (int64_t)(p * rank + j0 + lr) * nz + col);
     };
-    const int nmine = st0 < nst ? (nst - st0 + kWaves - 1) / kWaves : 0;
-    // wave 0's epilogue inputs (the projection of the hidden states and the
-    // previous state of its requests m0 + 4 lq + e, dim j0 + lr) do not depend
-    // on the products: they are loaded first (rows clamped, then masked)
+    const int nmine = st0 < nst ? (nst - st0 + kStWaves - 1) / kStWaves : 0;
+    // the projection of the hidden states (wave w takes part w of it) and, in wave
+    // 0, the previous state, of requests m0 + 4 lq + e, dim j0 + lr, do not depend on
+    // the products: they are loaded first (rows clamped, then masked)
     const int j = j0 + lr;
     float hpv[4][3], spv[4];
-    if (wave == 0) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int rc = min(m0 + 4 * lq + e, a.R - 1);
-            const float* hp = Hp ? Hp + ((int64_t)rc * a.K + (k - 1)) * (3 * rank) : nullptr;
+    for (int e = 0; e < 4; ++e) {
+        const int rc = min(m0 + 4 * lq + e, a.R - 1);
+        const float* hp = Hp + ((int64_t)wave * a.R * a.K + (int64_t)rc * a.K + (k - 1)) * (3 * rank) + j;
 #pragma unroll
-            for (int p = 0; p < 3; ++p) hpv[e][p] = hp ? hp[p * rank + j] : 0.0f;
-            spv[e] = k > 1 ? s_prev[(int64_t)rc * rank + j] : 0.0f;
-        }
+        for (int p = 0; p < 3; ++p) hpv[e][p] = wave < hpz ? hp[p * rank] : 0.0f;
+        spv[e] = wave == 0 && k > 1 ? s_prev[(int64_t)rc * rank + j] : 0.0f;
     }
     f32x4 acc[3];
 #pragma unroll
@@ -1187,6 +1209,10 @@ __global__ __launch_bounds__(kThreads) void rnn_state(MarkovArgs a, const float*
             load(i0 + kStDepth + u, u);
         }
     }
+#pragma unroll
+    for (int p = 0; p < 3; ++p)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[p][e] += hpv[e][p];
     if (wave > 0) {
 #pragma unroll
         for (int p = 0; p < 3; ++p) part[wave - 1][p][lane] = acc[p];
@@ -1194,7 +1220,7 @@ __global__ __launch_bounds__(kThreads) void rnn_state(MarkovArgs a, const float*
     __syncthreads();
     if (wave > 0) return;
 #pragma unroll
-    for (int w = 0; w < kWaves - 1; ++w)
+    for (int w = 0; w < kStWaves - 1; ++w)
 #pragma unroll
         for (int p = 0; p < 3; ++p) acc[p] += part[w][p][lane];
     // lane holds requests m0 + 4 lq + e, state dim j0 + lr
@@ -1202,12 +1228,7 @@ __global__ __launch_bounds__(kThreads) void rnn_state(MarkovArgs a, const float*
     for (int e = 0; e < 4; ++e) {
         const int r = m0 + 4 * lq + e;
         if (r >= a.R) continue;
-        float ag = acc[0][e], ac = acc[1][e], ao = acc[2][e];
-        if (Hp) {
-            ag += hpv[e][0];
-            ac += hpv[e][1];
-            ao += hpv[e][2];
-        }
+        const float ag = acc[0][e], ac = acc[1][e], ao = acc[2][e];
         const float g = 1.0f / (1.0f + expf(-ag));
         const float sp = spv[e];
         const float sn = g * sp + (1.0f - g) * tanhf(ac);
@@ -1217,21 +1238,451 @@ __global__ __launch_bounds__(kThreads) void rnn_state(MarkovArgs a, const float*
     }
 }
 
+// ---------------------------------------------------------------- md_block
+
+// The whole block of a small batch (up to 32 requests) in one launch: the
+// positions are looped inside, with the workgroups resident at once and the
+// exchanges and barrier of md_coop.  A position at these sizes is a chain of
+// latencies (launches, loads, exchanges), not of bytes, so what counts is how many
+// links it has.  Per position:
+//   S  (RNN head) the recurrence, 16 state dims x 16 requests per workgroup, its
+//      32-input steps over the eight waves; barrier;
+//   A  e_k = W1[x_{k-1}] (or the head's output) into LDS, the products of the
+//      workgroup's up to four tiles, z in registers, tile statistics; barrier;
+//   B  every workgroup computes every row's statistics itself from the tile
+//      statistics (at most kBkStats of them), which saves an exchange;
+//   C  the draws of the tiles owned here; x_k is all that crosses to the next
+//      position, whose barrier the workgroup arrives at before it writes p and
+//      loads the next position's first tile.
+// W2t is read again at every position, from the caches (a tile per workgroup).
+// Against the launches per position (us per block): (bf16, K = 16): 1 request x
+// 12416 entries 502 -> 196, 20 x 4000 497 -> 238, 24 x 50000 622 -> 409, 8 x 129280
+// 637 -> 543; RNN head, 8 x 129280 890 -> 734.
+constexpr int kBkRows = 32, kBkRT = kBkRows / 16;
+constexpr int kBkStats = 10240;  // tile statistics of a position, at most
+
+struct BlockArgs {
+    MarkovArgs a;
+    float2* stats;   // [R, ntiles]
+    const float* sh; // w_h . h per (r, k), or null
+    uint64_t* tok;   // [2][kBkRows] x of the last two positions (device-coherent)
+    unsigned* sync;
+    int ntiles;
+    // RNN head
+    const float* Hp;  // backbone part of the projection, in hpz parts
+    int hpz;
+    float* S[2];      // [R, rank] state, double-buffered by position
+    uint16_t* T[2];   // [R, 3 rank] state as three terms
+    uint16_t* E2;     // [R, 2 rank] output as two terms
+};
+
+__device__ __forceinline__ void st_dev16(uint16_t* p, uint16_t v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void st_dev32(float* p, float v) {
+    __hip_atomic_store((uint32_t*)p, __float_as_uint(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ float ld_dev32(const float* p) {
+    return __uint_as_float(__hip_atomic_load((uint32_t*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+__device__ __forceinline__ uint4 ld_dev128(const uint16_t* p) {
+    const uint64_t x = ld_dev64(p), y = ld_dev64(p + 4);
+    return uint4{(uint32_t)x, (uint32_t)(x >> 32), (uint32_t)y, (uint32_t)(y >> 32)};
+}
+
+template <int KS, int NT, bool BF16>
+__global__ __launch_bounds__(kCoThreads) void md_block(BlockArgs c, const bool vec) {
+    const MarkovArgs& a = c.a;
+    constexpr int kNch = 4 * KS, kRank = 32 * KS;
+    __shared__ __align__(16) uint16_t se[NT * kBkRows * kRank];
+    __shared__ float2 sst[kCoTiles][kCoWaves][kBkRows];
+    __shared__ RowInfo sinfo[kBkRows];
+    __shared__ float smass[kCoWaves][kTileV];
+    __shared__ int stok[kBkRows], sdraw[kBkRows], ndraw;
+    __shared__ f32x4 spart[NT == 2 ? kCoWaves - 1 : 1][3][DSPARK_WAVE];
+    const int R = a.R, nrt = (R + 15) >> 4, Gt = gridDim.x, b0 = blockIdx.x;
+    const int nt = b0 < c.ntiles ? min(kCoTiles, (c.ntiles - b0 + Gt - 1) / Gt) : 0;
+    auto tile_of = [&](int i) { return b0 + i * Gt; };
+    constexpr float kLog2e = 1.4426950408889634f;
+    const float scale2 = a.inv_temp * kLog2e;
+    unsigned bar = 0;
+
+    for (int k = 1; k <= a.K; ++k) {
+        // opaque to the compiler, which would otherwise keep every address of the
+        // loop body in registers across the positions, and spill them
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        const int lr = lane & 15, lq = lane >> 4;
+        bf16x8 af[KS];
+        float ub[kBkRT][4];
+        auto load_tile = [&](int i, int k) {  // W2t rows and base logits of position k
+            const int vt = tile_of(i) * kTileV + 16 * wave;
+            const uint16_t* src = a.W2t + (int64_t)min(vt + lr, a.V - 1) * kRank + 8 * lq;
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) af[ks] = *(const bf16x8*)(src + 32 * ks);
+#pragma unroll
+            for (int rt = 0; rt < kBkRT; ++rt) {
+                const int64_t row = ((int64_t)min(16 * rt + lr, R - 1) * a.K + (k - 1)) * a.ld;
+                const int vb = vt + 4 * lq;
+                if (vec) {
+                    const int64_t at = row + min(vb, a.V - 4);
+                    if (BF16) {
+                        const uint2 w = *(const uint2*)((const uint16_t*)a.base + at);
+                        ub[rt][0] = __uint_as_float(w.x << 16), ub[rt][1] = __uint_as_float(w.x & 0xffff0000u);
+                        ub[rt][2] = __uint_as_float(w.y << 16), ub[rt][3] = __uint_as_float(w.y & 0xffff0000u);
+                    } else {
+                        const float4 w = *(const float4*)((const float*)a.base + at);
+                        ub[rt][0] = w.x, ub[rt][1] = w.y, ub[rt][2] = w.z, ub[rt][3] = w.w;
+                    }
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int64_t at = row + min(vb + e, a.V - 1);
+                        ub[rt][e] = BF16 ? bf16_to_f32(((const uint16_t*)a.base)[at]) : ((const float*)a.base)[at];
+                    }
+                }
+            }
+        };
+        if (nt > 0) load_tile(0, k);
+        if (k > 1) grid_wait(c.sync, bar);
+        // x_{k-1} of every request (-1: its anchor was no token)
+        if (tid < R) {
+            const int x = k == 1 ? a.anchor[tid] : (int)(uint32_t)ld_dev64(c.tok + (k & 1) * kBkRows + tid);
+            stok[tid] = x >= 0 && x < a.V ? x : -1;
+        }
+        if (tid == 0) ndraw = 0;
+        __syncthreads();
+        if constexpr (NT == 2) {
+            // ---- S: as rnn_state, the steps over eight waves
+            constexpr int rank = kRank;
+            const int nz = 2 * rank + a.d;
+            const float* s_prev = k & 1 ? c.S[0] : c.S[1];
+            const uint16_t* T_prev = k & 1 ? c.T[0] : c.T[1];
+            float* s_next = k & 1 ? c.S[1] : c.S[0];
+            uint16_t* T_next = k & 1 ? c.T[1] : c.T[0];
+            const int nj = rank / 16, ks_s = 3 * rank / 32, nst = ks_s + rank / 32;
+            constexpr int kPer = (4 * KS + kCoWaves - 1) / kCoWaves;  // steps per wave
+            for (int blk = b0; blk < nj * nrt; blk += Gt) {
+                const int j0 = blk % nj * 16, m0 = blk / nj * 16;
+                const int ra = min(m0 + lr, R - 1), j = j0 + lr;
+                const int st0 = (k > 1 ? 0 : ks_s) + wave;
+                float hpv[4][3], spv[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int rc = min(m0 + 4 * lq + e, R - 1);
+                    const float* hp = c.Hp + ((int64_t)wave * R * a.K + (int64_t)rc * a.K + (k - 1)) * (3 * rank) + j;
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) hpv[e][q] = wave < c.hpz ? hp[q * rank] : 0.0f;
+                    spv[e] = wave == 0 && k > 1 ? ld_dev32(s_prev + (int64_t)rc * rank + j) : 0.0f;
+                }
+                uint4 av[kPer];
+                bf16x8 bv[kPer][3];
+#pragma unroll
+                for (int u = 0; u < kPer; ++u) {
+                    const int kk = 32 * min(st0 + kCoWaves * u, nst - 1) + 8 * lq;  // past the end: unused
+                    const bool state = kk < 3 * rank;                              // uniform over the wave
+                    av[u] = state ? ld_dev128(T_prev + (int64_t)ra * 3 * rank + kk)
+                                  : *(const uint4*)(a.W1 + (int64_t)max(stok[ra], 0) * rank + (kk - 3 * rank));
+                    const int col = state ? kk % rank : kk - 2 * rank;
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) bv[u][q] = *(const bf16x8*)(a.Wrnn + (int64_t)(q * rank + j0 + lr) * nz + col);
+                }
+                f32x4 acc[3];
+#pragma unroll
+                for (int q = 0; q < 3; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int u = 0; u < kPer; ++u)
+                    if (st0 + kCoWaves * u < nst) {
+#pragma unroll
+                        for (int q = 0; q < 3; ++q)
+                            acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av[u]), bv[u][q],
+                                                                           acc[q], 0, 0, 0);
+                    }
+#pragma unroll
+                for (int q = 0; q < 3; ++q)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[q][e] += hpv[e][q];
+                if (wave > 0) {
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) spart[wave - 1][q][lane] = acc[q];
+                }
+                __syncthreads();
+                if (wave == 0) {
+#pragma unroll
+                    for (int w = 0; w < kCoWaves - 1; ++w)
+#pragma unroll
+                        for (int q = 0; q < 3; ++q) acc[q] += spart[w][q][lane];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        const int r = m0 + 4 * lq + e;
+                        if (r >= R) continue;
+                        const float g = 1.0f / (1.0f + expf(-acc[0][e]));
+                        const float sn = g * spv[e] + (1.0f - g) * tanhf(acc[1][e]);
+                        const float o = tanhf(acc[2][e]);
+                        st_dev32(s_next + (int64_t)r * rank + j, sn);
+                        uint16_t t3[3], t2[2];
+                        split3(sn, t3, 1);
+                        split2(o, t2, 1);
+#pragma unroll
+                        for (int q = 0; q < 3; ++q) st_dev16(T_next + (int64_t)r * 3 * rank + q * rank + j, t3[q]);
+#pragma unroll
+                        for (int q = 0; q < 2; ++q) st_dev16(c.E2 + (int64_t)r * 2 * rank + q * rank + j, t2[q]);
+                    }
+                }
+                __syncthreads();  // the partial sums are read
+            }
+            grid_barrier(c.sync, ++bar);
+        }
+
+        // ---- A: the B operand into LDS (rows past R are zero), products, statistics
+        if (nt > 0) {
+            constexpr int kECopy = (NT * kBkRows * kNch + kCoThreads - 1) / kCoThreads;
+#pragma unroll
+            for (int j = 0; j < kECopy; ++j) {
+                const int idx = tid + j * kCoThreads, t = idx / (NT * kNch), q = idx % (NT * kNch);
+                if (idx >= NT * kBkRows * kNch) break;
+                uint4 v = uint4{0u, 0u, 0u, 0u};
+                if (t < R)
+                    v = NT == 2 ? ld_dev128(c.E2 + (int64_t)t * 2 * kRank + 8 * q)
+                                : *(const uint4*)(a.W1 + (int64_t)max(stok[t], 0) * kRank + 8 * q);
+                *(uint4*)(se + ((q / kNch * kBkRows + t) * kNch + eslot(t, q % kNch, kNch)) * 8) = v;
+            }
+        }
+        lds_barrier();
+        f32x4 z[kCoTiles][kBkRT];
+#pragma unroll
+        for (int i = 0; i < kCoTiles; ++i) {
+            if (i >= nt) continue;
+            if (i > 0) load_tile(i, k);
+#pragma unroll
+            for (int rt = 0; rt < kBkRT; ++rt) {
+                z[i][rt] = f32x4{0.f, 0.f, 0.f, 0.f};
+                if (rt >= nrt) continue;
+                const int t = 16 * rt + lr;
+#pragma unroll
+                for (int n = 0; n < NT; ++n)
+#pragma unroll
+                    for (int ks = 0; ks < KS; ++ks)
+                        z[i][rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                            af[ks], *(const bf16x8*)(se + ((n * kBkRows + t) * kNch + eslot(t, 4 * ks + lq, kNch)) * 8),
+                            z[i][rt], 0, 0, 0);
+                const int vb = tile_of(i) * kTileV + 16 * wave + 4 * lq;
+                float m = -__builtin_huge_valf();
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    z[i][rt][e] = vb + e < a.V && t < R ? scale2 * (ub[rt][e] + z[i][rt][e]) : -__builtin_huge_valf();
+                    m = fmaxf(m, z[i][rt][e]);
+                }
+                m = quad_max(m);
+                float s = 0.0f;
+                if (m > -__builtin_huge_valf()) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) s += __builtin_amdgcn_exp2f(z[i][rt][e] - m);
+                }
+                s = quad_sum(s);
+                if (lq == 0) sst[i][wave][t] = float2{m, s};
+            }
+        }
+        lds_barrier();
+        {
+            const int i = tid / kBkRows, r = tid % kBkRows;  // the first 128 threads: every (tile, request)
+            if (i < nt && r < R) {
+                float M = -__builtin_huge_valf();
+#pragma unroll
+                for (int w = 0; w < kCoWaves; ++w) M = fmaxf(M, sst[i][w][r].x);
+                float S = 0.0f;
+                if (M > -__builtin_huge_valf()) {
+#pragma unroll
+                    for (int w = 0; w < kCoWaves; ++w)
+                        if (sst[i][w][r].x > -__builtin_huge_valf()) S += sst[i][w][r].y * exp2f(sst[i][w][r].x - M);
+                }
+                st_f2<true>(c.stats + (int64_t)r * c.ntiles + tile_of(i), float2{M, S});
+            }
+        }
+        grid_barrier(c.sync, ++bar);
+
+        // ---- B: row maximum, total and draw tile of every request, one wave each
+        if (nt > 0)
+            for (int r = wave; r < R; r += kCoWaves) {
+                if (c.ntiles <= DSPARK_WAVE) row_stats<1, true, false>(a, c.stats, sinfo, c.ntiles, k, r, lane);
+                else if (c.ntiles <= 4 * DSPARK_WAVE) row_stats<4, true, false>(a, c.stats, sinfo, c.ntiles, k, r, lane);
+                else if (c.ntiles <= 8 * DSPARK_WAVE) row_stats<8, true, false>(a, c.stats, sinfo, c.ntiles, k, r, lane);
+                else row_stats<16, true, false>(a, c.stats, sinfo, c.ntiles, k, r, lane);
+            }
+        __syncthreads();
+        // ---- C: the draws of the tiles owned here
+        if (nt > 0 && tid < R) {
+            const int d = sinfo[tid].tile - b0;
+            if (d >= 0 && d % Gt == 0 && d / Gt < nt) sdraw[atomicAdd(&ndraw, 1)] = tid;
+        }
+        __syncthreads();
+        const int nd = ndraw;
+        for (int j0 = 0; j0 < nd; j0 += kCoWaves) {
+            for (int j = j0; j < min(nd, j0 + kCoWaves); ++j) {
+                const int rl = sdraw[j];
+                const int ti = (sinfo[rl].tile - b0) / Gt;
+                const float M = sinfo[rl].M;
+#pragma unroll
+                for (int i = 0; i < kCoTiles; ++i)
+#pragma unroll
+                    for (int rt = 0; rt < kBkRT; ++rt)
+                        if (i == ti && 16 * rt + lr == rl) {
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                smass[j - j0][16 * wave + 4 * lq + e] = __builtin_amdgcn_exp2f(z[i][rt][e] - M);
+                        }
+            }
+            lds_barrier();
+            if (j0 + wave < nd) {  // wave w makes draw j0 + w
+                const int rl = sdraw[j0 + wave];
+                const RowInfo ri = sinfo[rl];
+                const double m0 = smass[wave][2 * lane], m1 = smass[wave][2 * lane + 1];
+                double incl = m0 + m1;
+#pragma unroll
+                for (int o = 1; o < DSPARK_WAVE; o <<= 1) {
+                    const double t = __shfl_up(incl, o, DSPARK_WAVE);
+                    if (lane >= o) incl += t;
+                }
+                const double before = incl - (m0 + m1);  // mass before entry 2 * lane
+                // first entry whose running mass passes thr (zero masses are never drawn)
+                const unsigned long long h0 = __ballot(before + m0 > ri.thr && m0 > 0.0);
+                const unsigned long long h1 = __ballot(incl > ri.thr && m1 > 0.0);
+                // rounding: the tile's last entry with mass
+                const unsigned long long l0 = __ballot(m0 > 0.0), l1 = __ballot(m1 > 0.0);
+                int at;
+                if (h0 | h1) {
+                    const int f0 = h0 ? 2 * (int)__builtin_ctzll(h0) : kTileV;
+                    const int f1 = h1 ? 2 * (int)__builtin_ctzll(h1) + 1 : kTileV;
+                    at = min(f0, f1);
+                } else {
+                    const int e0 = l0 ? 2 * (63 - (int)__builtin_clzll(l0)) : 0;
+                    const int e1 = l1 ? 2 * (63 - (int)__builtin_clzll(l1)) + 1 : 0;
+                    at = max(e0, e1);
+                }
+                const int x = stok[rl] >= 0 ? ri.tile * kTileV + at : -1;
+                if (lane == 0) {
+                    a.draft_tok[(int64_t)rl * a.K + (k - 1)] = x;
+                    st_dev64(c.tok + ((k + 1) & 1) * kBkRows + rl, (uint64_t)(uint32_t)x);
+                }
+                if (k < a.K) {
+                    const float sc = embed_dot(a, a.W1 + (int64_t)max(x, 0) * a.rank, lane) +
+                                     (c.sh ? c.sh[(int64_t)rl * a.K + k] : 0.0f);
+                    if (lane == 0)
+                        a.conf[(int64_t)rl * a.K + k] = x >= 0 ? confidence(a, sc, k + 1) : __builtin_nanf("");
+                }
+            }
+            if (j0 + kCoWaves < nd) lds_barrier();
+        }
+        if (k < a.K) grid_arrive(c.sync, ++bar);
+#pragma unroll
+        for (int rt = 0; rt < kBkRT; ++rt) {
+            const int r = 16 * rt + lr;
+            if (nt == 0 || r >= R) continue;
+            const float M = sinfo[r].M, inv = 1.0f / sinfo[r].S;
+            float* out = a.draft_p + ((int64_t)r * a.K + (k - 1)) * a.V;
+#pragma unroll
+            for (int i = 0; i < kCoTiles; ++i) {
+                if (i >= nt) continue;
+                const int vb = tile_of(i) * kTileV + 16 * wave + 4 * lq;
+                float4 p;
+                p.x = __builtin_amdgcn_exp2f(z[i][rt][0] - M) * inv;
+                p.y = __builtin_amdgcn_exp2f(z[i][rt][1] - M) * inv;
+                p.z = __builtin_amdgcn_exp2f(z[i][rt][2] - M) * inv;
+                p.w = __builtin_amdgcn_exp2f(z[i][rt][3] - M) * inv;
+                if (vec) {
+                    if (vb < a.V) *(float4*)(out + vb) = p;
+                } else {
+                    if (vb < a.V) out[vb] = p.x;
+                    if (vb + 1 < a.V) out[vb + 1] = p.y;
+                    if (vb + 2 < a.V) out[vb + 2] = p.z;
+                    if (vb + 3 < a.V) out[vb + 3] = p.w;
+                }
+            }
+        }
+    }
+}
+
+// Grid of md_block, or 0 where it does not apply: up to 32 requests, kBkStats tile
+// statistics and four tiles a workgroup.  A workgroup takes a CU's registers, so the
+// grid is at most 64 workgroups: blocks drafted on several streams at once (a process
+// has four hardware queues) are then all resident together, and none waits for a
+// workgroup that another one's waiting workgroups keep out.  Where the block would
+// otherwise run as md_coop (bf16 base logits, V % 4 == 0), which takes the whole part
+// by itself, the grid is up to 256.  64 workgroups lose where they have to take
+// several tiles or rows in turn (fp32, 32 requests: 537 us with 32768 entries and 322
+// with 3000, against 305 and 245 in three launches per position), so there it is at
+// most 64 tiles and a request per wave.
+constexpr int kBkGrid = 64, kBkGridAlone = 256;
+template <int KS, int NT, bool BF16>
+int block_grid(const MarkovArgs& a, int ntiles, bool alone) {
+    const int most = alone ? kBkGridAlone : kBkGrid;
+    if (a.R > (alone ? kBkRows : kCoWaves) || ntiles > (alone ? kCoTiles * most : most) || (int64_t)a.R * ntiles > kBkStats) return 0;
+    constexpr int kMaxDevices = 64;
+    static int cache[kMaxDevices];  // workgroups held at once; 0: not yet asked, -1: none
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return 0;
+    if (cache[dev] == 0) {
+        int cus = 0, nb = 0;
+        const bool ok = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
+                        hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, md_block<KS, NT, BF16>, kCoThreads, 0) == hipSuccess;
+        cache[dev] = ok && nb * cus > 0 ? nb * cus : -1;
+    }
+    int G = ceil_div(ntiles, ceil_div(ntiles, most));
+    if (NT == 2) G = std::max(G, std::min(most, a.rank / 16 * ceil_div(a.R, 16)));  // the recurrence's blocks
+    return (alone ? G : 4 * G) <= cache[dev] ? G : 0;
+}
+
+template <int KS, int NT>
+bool launch_block(const BlockArgs& c, bool vec, hipStream_t s) {
+    const bool alone = coop_applies<KS, NT>(c.a, c.ntiles, vec);
+    const int G = c.a.base_bf16 ? block_grid<KS, NT, true>(c.a, c.ntiles, alone)
+                                : block_grid<KS, NT, false>(c.a, c.ntiles, alone);
+    if (G == 0) return false;
+    if (c.a.base_bf16) hipLaunchKernelGGL((md_block<KS, NT, true>), dim3(G), dim3(kCoThreads), 0, s, c, vec);
+    else hipLaunchKernelGGL((md_block<KS, NT, false>), dim3(G), dim3(kCoThreads), 0, s, c, vec);
+    return true;
+}
+
 template <int KS>
 hipError_t launch_rnn_ks(const MarkovArgs& a, uint16_t* Ee, uint16_t* E2, float* S0, float* S1,
                          uint16_t* T0, uint16_t* T1, float* Hp, float2* stats, RowInfo* info,
-                         float* sh, unsigned* sync, int ntiles, bool vec, hipStream_t s) {
+                         float* sh, unsigned* sync, uint64_t* tok, int ntiles, bool vec, hipStream_t s) {
     const int64_t rows = (int64_t)a.R * a.K;
+    int hpz = 0;  // parts of the backbone projection
     if (a.d > 0) {
         hipLaunchKernelGGL(md_hidden, dim3((unsigned)ceil_div((int)rows, kWaves)), dim3(kThreads), 0, s, a, sh);
-        hipLaunchKernelGGL(rnn_hproj, dim3((unsigned)ceil_div((int)rows, kHpRows), ceil_div(3 * a.rank, kHpCols)),
-                           dim3(kThreads), 0, s, a, Hp);
+        // at least eight steps a part
+        const int nsteps = ceil_div(a.d, 32);
+        const int per = std::max(ceil_div(nsteps, hp_parts(a.R, a.K, a.rank)), 8);
+        hpz = ceil_div(nsteps, per);
+        hipLaunchKernelGGL(rnn_hproj, dim3((unsigned)ceil_div((int)rows, kHpRows), ceil_div(3 * a.rank, kHpCols), hpz),
+                           dim3(kThreads), 0, s, a, Hp, per);
     }
     const float* shp = a.d > 0 ? sh : nullptr;
     const float* hpp = a.d > 0 ? Hp : nullptr;
     hipLaunchKernelGGL(md_first, dim3(ceil_div(a.R, kWaves)), dim3(kThreads), 0, s, a, shp, Ee, sync);
-    // the vocabulary product with the output's two terms: md_coop where it
-    // applies, else md_tile, md_stats and md_norm
+    BlockArgs c;
+    c.a = a;
+    c.stats = stats;
+    c.sh = shp;
+    c.tok = tok;
+    c.sync = sync;
+    c.ntiles = ntiles;
+    c.Hp = hpp;
+    c.hpz = hpz;
+    c.S[0] = S0;
+    c.S[1] = S1;
+    c.T[0] = T0;
+    c.T[1] = T1;
+    c.E2 = E2;
+    // a small batch's positions in one launch; else the vocabulary product with the
+    // output's two terms: md_coop where it applies, else md_tile and md_norm
+    if (launch_block<KS, 2>(c, vec, s)) {
+        hipLaunchKernelGGL(md_check, dim3((unsigned)ceil_div((int)rows, kThreads)), dim3(kThreads), 0, s, a,
+                           (const unsigned*)sync);
+        return hipGetLastError();
+    }
     const bool coop = coop_applies<KS, 2>(a, ntiles, vec);
     unsigned launch = 0;
     for (int k = 1; k <= a.K; ++k) {
@@ -1240,11 +1691,11 @@ hipError_t launch_rnn_ks(const MarkovArgs& a, uint16_t* Ee, uint16_t* E2, float*
         float* sn = (k & 1) ? S0 : S1;
         const uint16_t* tp = (k & 1) ? T1 : T0;
         uint16_t* tn = (k & 1) ? T0 : T1;
-        hipLaunchKernelGGL(rnn_state, dim3(a.rank / kStJ, ceil_div(a.R, kStR)), dim3(kThreads), 0, s, a, hpp,
-                           sp, tp, sn, tn, (const uint16_t*)Ee, E2, k);
+        hipLaunchKernelGGL(rnn_state, dim3(a.rank / kStJ, ceil_div(a.R, kStR)), dim3(kStWaves * DSPARK_WAVE), 0,
+                           s, a, hpp, hpz, sp, tp, sn, tn, (const uint16_t*)Ee, E2, k);
         // the draw gathers W1[x_k] into Ee: the embedding input of position k + 1
         if (coop) coop_position<KS, 2>(a, E2, Ee, stats, info, shp, sync, ntiles, k, launch, s);
-        else position<KS, 2>(a, E2, stats, info, Ee, shp, ntiles, k, vec, s);
+        else position<KS, 2>(a, E2, stats, Ee, shp, ntiles, k, vec, s);
     }
     if (coop)
         hipLaunchKernelGGL(md_check, dim3((unsigned)ceil_div((int)rows, kThreads)), dim3(kThreads), 0, s, a,
@@ -1254,20 +1705,32 @@ hipError_t launch_rnn_ks(const MarkovArgs& a, uint16_t* Ee, uint16_t* E2, float*
 
 template <int KS>
 hipError_t launch_ks(const MarkovArgs& a, uint16_t* E0, uint16_t* E1, float2* stats, RowInfo* info,
-                     float* sh, unsigned* sync, int ntiles, bool vec, hipStream_t s) {
+                     float* sh, unsigned* sync, uint64_t* tok, int ntiles, bool vec, hipStream_t s) {
     const int64_t rows = (int64_t)a.R * a.K;
     if (a.d > 0) hipLaunchKernelGGL(md_hidden, dim3((unsigned)ceil_div((int)rows, kWaves)), dim3(kThreads), 0, s, a, sh);
     const float* shp = a.d > 0 ? sh : nullptr;
     hipLaunchKernelGGL(md_first, dim3(ceil_div(a.R, kWaves)), dim3(kThreads), 0, s, a, shp, E0, sync);
-    // one md_coop launch per position and group of 128 requests where it
-    // applies; three launches per position otherwise
+    BlockArgs c = {};
+    c.a = a;
+    c.stats = stats;
+    c.sh = shp;
+    c.tok = tok;
+    c.sync = sync;
+    c.ntiles = ntiles;
+    // a small batch's positions in one launch; else one md_coop launch per position
+    // and group of 128 requests where it applies, two launches per position otherwise
+    if (launch_block<KS, 1>(c, vec, s)) {
+        hipLaunchKernelGGL(md_check, dim3((unsigned)ceil_div((int)rows, kThreads)), dim3(kThreads), 0, s, a,
+                           (const unsigned*)sync);
+        return hipGetLastError();
+    }
     const bool coop = coop_applies<KS, 1>(a, ntiles, vec);
     unsigned launch = 0;
     for (int k = 1; k <= a.K; ++k) {
         uint16_t* Ek = (k & 1) ? E0 : E1;
         uint16_t* En = (k & 1) ? E1 : E0;
         if (coop) coop_position<KS, 1>(a, Ek, En, stats, info, shp, sync, ntiles, k, launch, s);
-        else position<KS, 1>(a, Ek, stats, info, En, shp, ntiles, k, vec, s);
+        else position<KS, 1>(a, Ek, stats, En, shp, ntiles, k, vec, s);
     }
     if (coop)
         hipLaunchKernelGGL(md_check, dim3((unsigned)ceil_div((int)rows, kThreads)), dim3(kThreads), 0, s, a,
@@ -1290,7 +1753,7 @@ WsLayout ws_layout(int R, int K, int V, int rank) {
     l.stats = align256((size_t)R * ntiles * sizeof(float2));
     l.info = align256((size_t)R * sizeof(mkd::RowInfo));
     l.sh = align256((size_t)R * K * sizeof(float));
-    l.sync = align256(mkd::kSyncWords * sizeof(unsigned));  // md_coop's barrier words
+    l.sync = align256(mkd::kSyncWords * sizeof(unsigned)) + align256(mkd::kTokBytes);  // barrier words, tokens
     l.total = 2 * l.e + l.stats + l.info + l.sh + l.sync;
     return l;
 }
@@ -1312,11 +1775,11 @@ RnnLayout rnn_layout(int R, int K, int V, int rank) {
     l.e2 = align256((size_t)R * 2 * rank * 2);
     l.st = align256((size_t)R * rank * 4);
     l.st3 = align256((size_t)R * 3 * rank * 2);
-    l.hp = align256((size_t)R * K * 3 * rank * 4);
+    l.hp = align256((size_t)R * K * 3 * rank * 4 * mkd::hp_parts(R, K, rank));
     l.stats = align256((size_t)R * ntiles * sizeof(float2));
     l.info = align256((size_t)R * sizeof(mkd::RowInfo));
     l.sh = align256((size_t)R * K * sizeof(float));
-    l.sync = align256(mkd::kSyncWords * sizeof(unsigned));
+    l.sync = align256(mkd::kSyncWords * sizeof(unsigned)) + align256(mkd::kTokBytes);
     l.total = l.ee + l.e2 + 2 * l.st + 2 * l.st3 + l.hp + l.stats + l.info + l.sh + l.sync;
     return l;
 }
@@ -1339,14 +1802,15 @@ hipError_t launch_rnn(const MarkovArgs& a, void* ws, hipStream_t s) {
     mkd::RowInfo* info = (mkd::RowInfo*)p;       p += l.info;
     float* sh = (float*)p;                       p += l.sh;
     unsigned* sync = (unsigned*)p;
+    uint64_t* tok = (uint64_t*)(p + align256(mkd::kSyncWords * sizeof(unsigned)));
     const size_t eb = a.base_bf16 ? 2 : 4;
     const bool vec = a.V % 4 == 0 && a.ld % 4 == 0 && ((uintptr_t)a.base % (4 * eb)) == 0 &&
                      ((uintptr_t)a.draft_p % 16) == 0;
     switch (a.rank) {
-        case 32: return mkd::launch_rnn_ks<1>(a, Ee, E2, S0, S1, T0, T1, Hp, stats, info, sh, sync, ntiles, vec, s);
-        case 64: return mkd::launch_rnn_ks<2>(a, Ee, E2, S0, S1, T0, T1, Hp, stats, info, sh, sync, ntiles, vec, s);
-        case 128: return mkd::launch_rnn_ks<4>(a, Ee, E2, S0, S1, T0, T1, Hp, stats, info, sh, sync, ntiles, vec, s);
-        default: return mkd::launch_rnn_ks<8>(a, Ee, E2, S0, S1, T0, T1, Hp, stats, info, sh, sync, ntiles, vec, s);
+        case 32: return mkd::launch_rnn_ks<1>(a, Ee, E2, S0, S1, T0, T1, Hp, stats, info, sh, sync, tok, ntiles, vec, s);
+        case 64: return mkd::launch_rnn_ks<2>(a, Ee, E2, S0, S1, T0, T1, Hp, stats, info, sh, sync, tok, ntiles, vec, s);
+        case 128: return mkd::launch_rnn_ks<4>(a, Ee, E2, S0, S1, T0, T1, Hp, stats, info, sh, sync, tok, ntiles, vec, s);
+        default: return mkd::launch_rnn_ks<8>(a, Ee, E2, S0, S1, T0, T1, Hp, stats, info, sh, sync, tok, ntiles, vec, s);
     }
 }
 
@@ -1364,14 +1828,15 @@ hipError_t launch_markov(const MarkovArgs& a, void* ws, hipStream_t s) {
     mkd::RowInfo* info = (mkd::RowInfo*)(p + 2 * l.e + l.stats);
     float* sh = (float*)(p + 2 * l.e + l.stats + l.info);
     unsigned* sync = (unsigned*)(p + 2 * l.e + l.stats + l.info + l.sh);
+    uint64_t* tok = (uint64_t*)(p + 2 * l.e + l.stats + l.info + l.sh + align256(mkd::kSyncWords * sizeof(unsigned)));
     const size_t eb = a.base_bf16 ? 2 : 4;
     const bool vec = a.V % 4 == 0 && a.ld % 4 == 0 && ((uintptr_t)a.base % (4 * eb)) == 0 &&
                      ((uintptr_t)a.draft_p % 16) == 0;
     switch (a.rank) {
-        case 32: return mkd::launch_ks<1>(a, E0, E1, stats, info, sh, sync, ntiles, vec, s);
-        case 64: return mkd::launch_ks<2>(a, E0, E1, stats, info, sh, sync, ntiles, vec, s);
-        case 128: return mkd::launch_ks<4>(a, E0, E1, stats, info, sh, sync, ntiles, vec, s);
-        default: return mkd::launch_ks<8>(a, E0, E1, stats, info, sh, sync, ntiles, vec, s);
+        case 32: return mkd::launch_ks<1>(a, E0, E1, stats, info, sh, sync, tok, ntiles, vec, s);
+        case 64: return mkd::launch_ks<2>(a, E0, E1, stats, info, sh, sync, tok, ntiles, vec, s);
+        case 128: return mkd::launch_ks<4>(a, E0, E1, stats, info, sh, sync, tok, ntiles, vec, s);
+        default: return mkd::launch_ks<8>(a, E0, E1, stats, info, sh, sync, tok, ntiles, vec, s);
     }
 }
 

@@ -156,3 +156,40 @@ def test_draft_degenerate_shapes(R, K, V):
     _compare(w, case, tok, p, conf, f"R={R} K={K} V={V}")
     if V == 1:
         assert (tok == 0).all().item() and torch.equal(p, torch.ones_like(p))
+
+
+# the lines between the one-launch block and the launches per position: 8 / 9 requests and
+# 64 / 65 tiles (8192 / 8193 entries) where the vector path of bf16 logits does not apply,
+# 32 / 33 requests where it does; a tile, a ragged second one, and several per workgroup
+@pytest.mark.parametrize("R,K,V,dt", [
+    (8, 3, 8192, "f32"), (9, 3, 8192, "f32"), (8, 3, 8193, "bf16"), (2, 3, 8189, "bf16"), (1, 16, 128, "bf16"),
+    (32, 3, 1000, "bf16"), (33, 3, 1000, "bf16"), (17, 3, 2052, "bf16"), (3, 4, 65540, "bf16"), (1, 2, 5, "f32"),
+])
+def test_draft_block_edges(R, K, V, dt):
+    w = synth.scaled(synth.WORKLOADS["serving"], R=R, K=K, V=V, logit_dtype=dt)
+    case = guard.draft_case(w, 3, rank=64, d=8)
+    tok, p, conf = _run_gpu(w, case, 64, 8)
+    _compare(w, case, tok, p, conf, f"edges {dt}")
+
+
+def test_draft_block_on_four_streams():
+    # four blocks at once, on streams of their own: each grid fits beside the
+    # others, so all finish and agree with a block drafted alone
+    w = synth.scaled(synth.WORKLOADS["serving"], R=8, K=16, V=8192, logit_dtype="f32")
+    case = guard.draft_case(w, 5, rank=64, d=8)
+    inp = case.inp
+    args = [to_dev(x) for x in (inp.anchor, inp.base, inp.W1, inp.W2t, inp.w_conf, inp.u)]
+    hidden, temp = to_dev(inp.hidden), to_dev(inp.sts_temp)
+    alone = _run_gpu(w, case, 64, 8)
+    _compare(w, case, *alone, "alone")
+    streams = [torch.cuda.Stream() for _ in range(4)]
+    outs = []
+    for _ in range(3):
+        for s in streams:
+            s.wait_stream(torch.cuda.current_stream())
+            with torch.cuda.stream(s):
+                outs.append(dspark.dspark_markov_draft(*args, w.K, hidden=hidden, sts_temp=temp))
+    torch.cuda.synchronize()
+    for o in outs:
+        for x, y in zip(o, alone):
+            assert torch.equal(x, y)

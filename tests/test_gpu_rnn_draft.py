@@ -160,3 +160,16 @@ def test_rnn_draft_degenerate_shapes(R, K, V):
     _compare(w, case, tok, p, conf, f"R={R} K={K} V={V}")
     if V == 1:
         assert (tok == 0).all().item() and torch.equal(p, torch.ones_like(p))
+
+
+# one launch for the block (up to 8 requests x 64 tiles, or 32 requests of bf16 logits) against
+# launches per position; the backbone projection in one part (d = 0 has none), a few and eight
+@pytest.mark.parametrize("R,K,V,rank,d,dt", [
+    (8, 3, 8192, 64, 256, "f32"), (9, 3, 8192, 64, 264, "f32"), (32, 3, 1000, 64, 2048, "bf16"),
+    (33, 3, 1000, 32, 520, "bf16"), (17, 4, 2052, 256, 1024, "bf16"), (1, 5, 129, 32, 0, "f32"), (3, 3, 9000, 256, 8, "bf16"),
+])
+def test_rnn_draft_block_edges(R, K, V, rank, d, dt):
+    w = synth.scaled(synth.WORKLOADS["serving"], R=R, K=K, V=V, logit_dtype=dt)
+    case = guard.draft_case(w, 4, rank=rank, d=d, head="rnn")
+    tok, p, conf = _run_gpu(w, case, d)
+    _compare(w, case, tok, p, conf, f"edges {dt}")
