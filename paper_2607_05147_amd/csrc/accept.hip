@@ -17,9 +17,12 @@
 //            the chunk masses, then inside the selected chunk only.
 //   rate     (optional) sum_v min(p_t, p_d) per tested row, one wave per chunk,
 //            then summed per row.
+// Short vocabularies (kFuseChunks, kRateFuseChunks) take resid and draw, and rate and
+// its sum, in one launch each.
 // Probabilities are evaluated in fp32 (exp2 of log2e-scaled logits); masses
 // are accumulated in fp64 across lanes and chunks.
 #include <algorithm>
+#include <atomic>
 
 #include "device_common.h"
 #include "kernels.h"
@@ -33,6 +36,13 @@ constexpr int kWaves = kBlk / kLanes;
 constexpr int kLanePer = kChunk / kLanes;      // 64 entries per lane and chunk
 constexpr int kThreadPer = kChunk / kBlk;      // 16 entries per thread (draw)
 constexpr int kMaxChunks = 256;                // V <= 2^20
+// Chunks up to which a request's workgroup computes its residual masses itself:
+// a launch less against four waves' share of the row.  Us per call, fused against
+// not: 1 request x 4000 entries 18.1 / 20.6, 256 x 8000 22.0 / 25.2, 8 x 16000
+// 20.4 / 22.0; with 8 chunks 64 x 32000 26.6 / 25.8, with 16 chunks 8 x 65000 29.7 /
+// 23.8; with entry loads (4 x 30001, fp32) 36.5 / 32.6.
+constexpr int kFuseChunks = 4;
+constexpr int kRateFuseChunks = 8;  // the same for the rate's sum per row
 static_assert(kMaxChunks <= kBlk, "the draw loads one chunk mass per thread");
 constexpr float kLog2e = 1.4426950408889634f;
 
@@ -459,25 +469,12 @@ __global__ __launch_bounds__(kBlk) void acc_resolve(
 
 // ---------------------------------------------------------------- residual masses
 
-// One wave per (request, chunk): the mass of max(0, p_t - p_d) of the
-// rejected row, for requests that rejected (the others return at once).
+// Mass of max(0, p_t - p_d) over chunk c of a rejected row (every lane gets it).
 template <bool BF16, bool VEC>
-__global__ __launch_bounds__(kBlk) void acc_resid(
-    const float* __restrict__ draft_p, const void* __restrict__ logits, int64_t ld, int R, int K,
-    int V, float scale2, const DrawInfo* __restrict__ draw, double* __restrict__ mass) {
-    const int nch = n_chunks(V);
-    const int lane = threadIdx.x & (kLanes - 1);
-    const int it = blockIdx.x * kWaves + wave_id();
-    if (it >= R * nch) return;
-    const int r = it / nch;
-    const int c = it - r * nch;
-    const DrawInfo d = draw[r];
-    if (d.kind != 2) return;
+__device__ __forceinline__ double chunk_resid(const float* pd, const void* rp, int V, float scale2, float M,
+                                              float invS, int c, int lane) {
     const int v0 = c * kChunk;
     const int v1 = min(V, v0 + kChunk);
-    const void* rp = (const char*)logits + (size_t)d.row * (size_t)ld * (BF16 ? 2 : 4);
-    const float* pd = draft_p + ((int64_t)r * K + d.t) * V;
-    const float invS = 1.0f / d.S;
     float acc = 0.0f;
     if (VEC) {
         WaveChunk<BF16> xc;
@@ -490,7 +487,7 @@ __global__ __launch_bounds__(kBlk) void acc_resid(
         if (v1 < v0 + kChunk) wc_mask<BF16>(x, v0, v1, lane, -__builtin_huge_valf());
 #pragma unroll
         for (int k = 0; k < kLanePer; ++k) {
-            const float pt = fexp2(__builtin_fmaf(x[k], scale2, -d.M)) * invS;
+            const float pt = fexp2(__builtin_fmaf(x[k], scale2, -M)) * invS;
             acc += fmaxf(pt - qd[k / 4][k % 4], 0.0f);
         }
     } else {
@@ -500,17 +497,37 @@ __global__ __launch_bounds__(kBlk) void acc_resid(
 #pragma unroll
         for (int k = 0; k < kLanePer; ++k) {
             // entries past v1 have x = -inf: exp2 gives 0 and the term vanishes
-            const float pt = fexp2(__builtin_fmaf(x[k], scale2, -d.M)) * invS;
+            const float pt = fexp2(__builtin_fmaf(x[k], scale2, -M)) * invS;
             acc += fmaxf(pt - q[k], 0.0f);
         }
     }
-    const double w = wave_sum_f64((double)acc);
+    return wave_sum_f64((double)acc);
+}
+
+// One wave per (request, chunk) of the rejected rows (the others return at once).
+template <bool BF16, bool VEC>
+__global__ __launch_bounds__(kBlk) void acc_resid(
+    const float* __restrict__ draft_p, const void* __restrict__ logits, int64_t ld, int R, int K,
+    int V, float scale2, const DrawInfo* __restrict__ draw, double* __restrict__ mass) {
+    const int nch = n_chunks(V);
+    const int lane = threadIdx.x & (kLanes - 1);
+    const int it = blockIdx.x * kWaves + wave_id();
+    if (it >= R * nch) return;
+    const int r = it / nch;
+    const int c = it - r * nch;
+    const DrawInfo d = draw[r];
+    if (d.kind != 2) return;
+    const void* rp = (const char*)logits + (size_t)d.row * (size_t)ld * (BF16 ? 2 : 4);
+    const double w = chunk_resid<BF16, VEC>(draft_p + ((int64_t)r * K + d.t) * V, rp, V, scale2, d.M,
+                                            1.0f / d.S, c, lane);
     if (lane == 0) mass[it] = w;
 }
 
 // ---------------------------------------------------------------- draw
 
-template <bool BF16>
+// FUSED: the residual masses are computed here, the four waves taking the chunks in
+// turn, instead of by acc_resid (short vocabularies: see kFuseChunks).
+template <bool BF16, bool FUSED>
 __global__ __launch_bounds__(kBlk) void acc_draw(
     const float* __restrict__ draft_p, const void* __restrict__ logits, int64_t ld,
     const float* __restrict__ u, int R, int K, int V, float scale2,
@@ -530,10 +547,21 @@ __global__ __launch_bounds__(kBlk) void acc_draw(
     const int nch = n_chunks(V);
     // the residual chunk masses (nch <= kBlk) and u are loaded together with
     // the draw record
-    const double mw = tid < nch ? mass[(int64_t)r * nch + tid] : 0.0;
+    double mw = !FUSED && tid < nch ? mass[(int64_t)r * nch + tid] : 0.0;
     const double uu = (double)u[(int64_t)r * (K + 1) + K];
     const DrawInfo d = draw[r];
     if (d.kind == 0) return;
+    if (FUSED && d.kind == 2) {
+        const void* row = (const char*)logits + (size_t)d.row * (size_t)ld * (BF16 ? 2 : 4);
+        for (int c = wave_id(); c < nch; c += kWaves) {
+            const double w = chunk_resid<BF16, true>(draft_p + ((int64_t)r * K + d.t) * V, row, V, scale2, d.M,
+                                                    1.0f / d.S, c, lane);
+            if (lane == 0) s_w[c] = w;
+        }
+        __syncthreads();
+        mw = tid < nch ? s_w[tid] : 0.0;
+        __syncthreads();
+    }
     const ChunkStat* st = stats + (int64_t)d.row * nch;
     // chunk masses, in the units of the entry masses used below
     int kind = d.kind;
@@ -712,6 +740,42 @@ __global__ __launch_bounds__(kBlk) void acc_draw(
 
 // ---------------------------------------------------------------- analytic rate
 
+// sum_v min(p_t, p_d) over chunk c of a tested row (every lane gets it).
+template <bool BF16, bool VEC>
+__device__ __forceinline__ double chunk_rate(const float* pd, const void* rp, int V, float scale2, float M,
+                                             float invS, int c, int lane) {
+    const int v0 = c * kChunk;
+    const int v1 = min(V, v0 + kChunk);
+    float acc = 0.0f;
+    if (VEC) {
+        WaveChunk<BF16> xc;
+        f32x4 qd[kLanePer / 4];
+        wc_load<BF16>(rp, v0, V, lane, xc);
+        wc_load_draft<BF16>(pd, v0, V, lane, qd);
+        float x[kLanePer];
+        wc_unpack<BF16>(xc, x);
+        // entries past v1: x = -inf gives min(0, p_d) = 0
+        if (v1 < v0 + kChunk) wc_mask<BF16>(x, v0, v1, lane, -__builtin_huge_valf());
+#pragma unroll
+        for (int k = 0; k < kLanePer; ++k)
+            acc += fminf(fexp2(__builtin_fmaf(x[k], scale2, -M)) * invS, qd[k / 4][k % 4]);
+    } else {
+        float x[kLanePer], q[kLanePer];
+        wc_load_slow<BF16>(rp, v0, v1, lane, -__builtin_huge_valf(), x);
+        wc_load_draft_slow<BF16>(pd, v0, v1, lane, q);
+#pragma unroll
+        for (int k = 0; k < kLanePer; ++k)
+            acc += fminf(fexp2(__builtin_fmaf(x[k], scale2, -M)) * invS, q[k]);
+    }
+    return wave_sum_f64((double)acc);
+}
+
+// Whether a verified row tests a draft (bonus rows and rows of malformed requests
+// carry none).
+__device__ __forceinline__ bool rate_row(const RowInfo& ri, const int32_t* cu_q, int R, int K) {
+    return ri.req >= 0 && ri.req < R && ri.t >= 0 && ri.t < K && ri.t < cu_q[ri.req + 1] - cu_q[ri.req] - 1;
+}
+
 // One wave per (row, chunk): sum_v min(p_t, p_d) over the chunk for rows that
 // test a draft; other rows return at once.
 template <bool BF16, bool VEC>
@@ -726,38 +790,10 @@ __global__ __launch_bounds__(kBlk) void acc_rate_pass(
     const int row = it / nch;
     const int c = it - row * nch;
     const RowInfo ri = rows[row];
-    const int r = ri.req;
-    // rows of malformed requests and bonus rows carry no draft
-    if (r < 0 || r >= R || ri.t < 0 || ri.t >= K) return;
-    const int ql = cu_q[r + 1] - cu_q[r];
-    if (ri.t >= ql - 1) return;
-    const int v0 = c * kChunk;
-    const int v1 = min(V, v0 + kChunk);
+    if (!rate_row(ri, cu_q, R, K)) return;
     const void* rp = (const char*)logits + (size_t)row * (size_t)ld * (BF16 ? 2 : 4);
-    const float* pd = draft_p + ((int64_t)r * K + ri.t) * V;
-    const float invS = 1.0f / ri.S;
-    float acc = 0.0f;
-    if (VEC) {
-        WaveChunk<BF16> xc;
-        f32x4 qd[kLanePer / 4];
-        wc_load<BF16>(rp, v0, V, lane, xc);
-        wc_load_draft<BF16>(pd, v0, V, lane, qd);
-        float x[kLanePer];
-        wc_unpack<BF16>(xc, x);
-        // entries past v1: x = -inf gives min(0, p_d) = 0
-        if (v1 < v0 + kChunk) wc_mask<BF16>(x, v0, v1, lane, -__builtin_huge_valf());
-#pragma unroll
-        for (int k = 0; k < kLanePer; ++k)
-            acc += fminf(fexp2(__builtin_fmaf(x[k], scale2, -ri.M)) * invS, qd[k / 4][k % 4]);
-    } else {
-        float x[kLanePer], q[kLanePer];
-        wc_load_slow<BF16>(rp, v0, v1, lane, -__builtin_huge_valf(), x);
-        wc_load_draft_slow<BF16>(pd, v0, v1, lane, q);
-#pragma unroll
-        for (int k = 0; k < kLanePer; ++k)
-            acc += fminf(fexp2(__builtin_fmaf(x[k], scale2, -ri.M)) * invS, q[k]);
-    }
-    const double w = wave_sum_f64((double)acc);
+    const double w = chunk_rate<BF16, VEC>(draft_p + ((int64_t)ri.req * K + ri.t) * V, rp, V, scale2, ri.M,
+                                           1.0f / ri.S, c, lane);
     if (lane == 0) part[it] = w;
 }
 
@@ -778,15 +814,57 @@ __global__ __launch_bounds__(kBlk) void acc_rate_final(
     }
 }
 
+// Short vocabularies (kRateFuseChunks): one workgroup per verified row, its four waves
+// taking the chunks in turn, the chunk sums added in chunk order; -1 for rows that
+// test no draft.  A launch less: 8 requests x 2000 entries 28.3 -> 23.6 us per call; with 32 chunks 117 -> 134 (too few waves in flight).
+template <bool BF16, bool VEC>
+__global__ __launch_bounds__(kBlk) void acc_rate_rows(
+    const float* __restrict__ draft_p, const void* __restrict__ logits, int64_t ld,
+    const int32_t* __restrict__ cu_q, int R, int K, int V, float scale2,
+    const RowInfo* __restrict__ rows, float* __restrict__ rate) {
+    __shared__ double s_part[kRateFuseChunks];
+    const int nch = n_chunks(V);
+    const int lane = threadIdx.x & (kLanes - 1);
+    const int row = blockIdx.x;
+    if (row >= clamp_rows(cu_q[R], R * (K + 1))) return;
+    const RowInfo ri = rows[row];
+    if (!rate_row(ri, cu_q, R, K)) {
+        if (threadIdx.x == 0) rate[row] = -1.0f;
+        return;
+    }
+    const void* rp = (const char*)logits + (size_t)row * (size_t)ld * (BF16 ? 2 : 4);
+    for (int c = wave_id(); c < nch; c += kWaves) {
+        const double w = chunk_rate<BF16, VEC>(draft_p + ((int64_t)ri.req * K + ri.t) * V, rp, V, scale2, ri.M,
+                                               1.0f / ri.S, c, lane);
+        if (lane == 0) s_part[c] = w;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double t = 0.0;
+        for (int c = 0; c < nch; ++c) t += s_part[c];
+        rate[row] = (float)t;
+    }
+}
+
 // ---------------------------------------------------------------- launch
 
-// resident workgroups of a kernel on the whole device (persistent grids)
-static int resident_blocks(const void* fn, int cus) {
-    int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kBlk, 0) != hipSuccess ||
-        per_cu < 1)
-        per_cu = 1;
-    return per_cu * cus;
+// Resident workgroups of a kernel on the whole device (persistent grids), asked
+// once per device: the query costs as much as a launch.
+template <typename F>
+static int resident_blocks(F fn, std::atomic<int>* cache) {
+    constexpr int kMaxDevices = 64;
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return 0;
+    const bool keep = dev >= 0 && dev < kMaxDevices;
+    int n = keep ? cache[dev].load(std::memory_order_relaxed) : 0;
+    if (n == 0) {
+        int per_cu = 0, cus = 0;
+        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kBlk, 0) != hipSuccess || per_cu < 1) per_cu = 1;
+        n = per_cu * cus;
+        if (keep) cache[dev].store(n, std::memory_order_relaxed);
+    }
+    return n;
 }
 
 template <bool BF16>
@@ -802,21 +880,18 @@ static hipError_t launch_typed(const AcceptArgs& a, void* ws, hipStream_t s) {
                      a.V % G == 0;
     const int max_rows = a.R * (a.K + 1);
     const int64_t wave_items = (int64_t)max_rows * nch;
-    int dev = 0, cus = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
-    if (e != hipSuccess) return e;
     const dim3 blk(kBlk);
     // the row pass runs as many persistent workgroups as are resident at once
-    const void* rowpass = greedy ? (vec ? (const void*)acc_rowpass<BF16, true, true>
-                                        : (const void*)acc_rowpass<BF16, true, false>)
-                                 : (vec ? (const void*)acc_rowpass<BF16, false, true>
-                                        : (const void*)acc_rowpass<BF16, false, false>);
-    const int pgrid = (int)std::max<int64_t>(
-        1, std::min<int64_t>((wave_items + kWaves - 1) / kWaves, resident_blocks(rowpass, cus)));
-#define DS_ROWPASS(G, VV)                                                                    \
-    hipLaunchKernelGGL((acc_rowpass<BF16, G, VV>), dim3(pgrid), blk, 0, s, a.logits, a.ld, \
-                       a.cu_q, a.R, a.V, max_rows, scale2, w.stats, w.rows)
+    hipError_t e = hipSuccess;
+#define DS_ROWPASS(G, VV)                                                                              \
+    do {                                                                                               \
+        static std::atomic<int> cache[64];                                                             \
+        const int most = resident_blocks(acc_rowpass<BF16, G, VV>, cache);                             \
+        if (most == 0) return hipErrorInvalidDevice;                                                   \
+        const int pgrid = (int)std::max<int64_t>(1, std::min<int64_t>((wave_items + kWaves - 1) / kWaves, most)); \
+        hipLaunchKernelGGL((acc_rowpass<BF16, G, VV>), dim3(pgrid), blk, 0, s, a.logits, a.ld, a.cu_q, a.R, a.V, \
+                           max_rows, scale2, w.stats, w.rows);                                         \
+    } while (0)
     if (greedy) { if (vec) DS_ROWPASS(true, true); else DS_ROWPASS(true, false); }
     else { if (vec) DS_ROWPASS(false, true); else DS_ROWPASS(false, false); }
 #undef DS_ROWPASS
@@ -834,16 +909,30 @@ static hipError_t launch_typed(const AcceptArgs& a, void* ws, hipStream_t s) {
     // draft rows start at multiples of V floats: 16-byte aligned when V % 4 == 0
     // (implied by whole logit words)
     const bool pdvec = vec && ((uintptr_t)a.draft_p % 16) == 0;
-    const int rgrid = (int)(((int64_t)a.R * nch + kWaves - 1) / kWaves);
-    if (pdvec)
-        hipLaunchKernelGGL((acc_resid<BF16, true>), dim3(rgrid), blk, 0, s, a.draft_p, a.logits,
-                           a.ld, a.R, a.K, a.V, scale2, w.draw, w.mass);
-    else
-        hipLaunchKernelGGL((acc_resid<BF16, false>), dim3(rgrid), blk, 0, s, a.draft_p, a.logits,
-                           a.ld, a.R, a.K, a.V, scale2, w.draw, w.mass);
-    hipLaunchKernelGGL((acc_draw<BF16>), dim3(a.R), blk, 0, s, a.draft_p, a.logits, a.ld, a.u,
-                       a.R, a.K, a.V, scale2, w.stats, w.draw, w.mass, a.next_tok);
-    if (a.accept_rate) {
+#define DS_DRAW(F)                                                                              \
+    hipLaunchKernelGGL((acc_draw<BF16, F>), dim3(a.R), blk, 0, s, a.draft_p, a.logits, a.ld, a.u, a.R, a.K, \
+                       a.V, scale2, w.stats, w.draw, w.mass, a.next_tok)
+    if (pdvec && nch <= kFuseChunks) {
+        DS_DRAW(true);
+    } else {
+        const int rgrid = (int)(((int64_t)a.R * nch + kWaves - 1) / kWaves);
+        if (pdvec)
+            hipLaunchKernelGGL((acc_resid<BF16, true>), dim3(rgrid), blk, 0, s, a.draft_p, a.logits,
+                               a.ld, a.R, a.K, a.V, scale2, w.draw, w.mass);
+        else
+            hipLaunchKernelGGL((acc_resid<BF16, false>), dim3(rgrid), blk, 0, s, a.draft_p, a.logits,
+                               a.ld, a.R, a.K, a.V, scale2, w.draw, w.mass);
+        DS_DRAW(false);
+    }
+#undef DS_DRAW
+    if (a.accept_rate && nch <= kRateFuseChunks) {
+        if (pdvec)
+            hipLaunchKernelGGL((acc_rate_rows<BF16, true>), dim3(max_rows), blk, 0, s, a.draft_p, a.logits, a.ld,
+                               a.cu_q, a.R, a.K, a.V, scale2, w.rows, a.accept_rate);
+        else
+            hipLaunchKernelGGL((acc_rate_rows<BF16, false>), dim3(max_rows), blk, 0, s, a.draft_p, a.logits, a.ld,
+                               a.cu_q, a.R, a.K, a.V, scale2, w.rows, a.accept_rate);
+    } else if (a.accept_rate) {
         const int qgrid = (int)std::max<int64_t>(1, (wave_items + kWaves - 1) / kWaves);
         if (pdvec)
             hipLaunchKernelGGL((acc_rate_pass<BF16, true>), dim3(qgrid), blk, 0, s, a.draft_p,

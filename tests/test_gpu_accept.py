@@ -258,3 +258,21 @@ def test_rows_past_the_batch_end():
     # the one row past request 0 is owned by no well-formed request
     assert rate[ql[0]] == -1
     log("[accept] rows past cu_q[R]: requests 1-3 rejected, request 0 exact")
+
+
+@pytest.mark.parametrize("dt", ["f32", "bf16"])
+@pytest.mark.parametrize("V", [4096, 16384, 16392, 16385, 32768, 32776])
+def test_chunk_counts_around_the_fused_launches(dt, V):
+    """Four and five chunks (residual masses in the draw's launch or their own),
+    eight and nine (the rate's sum in its pass or a launch of its own), whole and
+    ragged, aligned and not: decisions, tokens and rates against the oracle."""
+    w = synth.scaled(synth.WORKLOADS["mid"], R=6, K=4, V=V, logit_dtype=dt)
+    case = guard.build_case(w, 6, with_kv=False)
+    _compare(case, f"chunks {dt} V={V}")
+    _, _, _, rate_o = oracle.accept(case.drafts.draft_tok, case.drafts.draft_p, case.logits, w.logit_dtype, case.cu_q, w.K,
+                                    w.V, u=case.drafts.u, want_rate=True)
+    _, _, rate = gpu_accept(w, case.drafts, case.logits, case.cu_q, want_rate=True)
+    total = case.total_q
+    tested = rate_o[:total] >= 0
+    assert np.array_equal(rate[:total] < 0, ~tested)
+    np.testing.assert_allclose(rate[:total][tested], rate_o[:total][tested], atol=2e-5)
