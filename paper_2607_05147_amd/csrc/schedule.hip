@@ -1,8 +1,9 @@
 // Hardware-aware prefix scheduler (Algorithm 1 of the section on
-// confidence-scheduled verification) as two gfx950 kernels, so the
+// confidence-scheduled verification) as one or two gfx950 kernels, so the
 // verification step needs no host round trip.
 //
-// sched_rank (one workgroup per 16 candidates, the whole GPU):
+// sched_rank (one workgroup per 16 candidates, the whole GPU; small schedules run
+// both kernels' work in one workgroup, sched_one):
 //   1. survival a[r][j] = prod_{i<=j} c[r][i] in fp64, multiplied in
 //      increasing j (the same sequence of roundings on every implementation),
 //      recomputed by every workgroup into LDS;
@@ -10,9 +11,9 @@
 //      Instead of sorting, every candidate (a > 0) counts the candidates that
 //      come before it in that order -- its position n -- and sums their a in
 //      the same pass, which gives tau_n = R + sum_{m<=n} a_(m) directly.
-//      Sixteen lanes share a candidate, each taking every 16th key, so a
-//      wave's LDS reads are sixteen consecutive doubles (no bank conflicts)
-//      broadcast to the four candidates of the wave;
+//      Lanes of a group share a candidate, each taking every 32nd key, so a
+//      wave's LDS reads are consecutive doubles (no bank conflicts)
+//      broadcast to the candidates of the wave;
 //   3. tau and the flat index are written at position n; workgroup 0 writes
 //      the candidate count.
 // sched_select (one workgroup):
@@ -32,8 +33,10 @@
 
 namespace dspark {
 
-constexpr int kRankThreads = 256;
-constexpr int kRankSlices = 16;  // lanes per candidate
+// 512 threads and 32 lanes a candidate: two waves per SIMD and half the chain of
+// dependent fp64 sums of 256 and 16 (512 requests x 8: 11.4 us with those)
+constexpr int kRankThreads = 512;
+constexpr int kRankSlices = 32;  // lanes per candidate
 constexpr int kRankCand = kRankThreads / kRankSlices;
 constexpr int kSelThreads = 1024;
 constexpr int kSelWaves = kSelThreads / DSPARK_WAVE;
@@ -52,6 +55,38 @@ __device__ __forceinline__ double sched_conf(float c) {
     if (!(c > 0.0f)) return 0.0;
     if (c > 1.0f) return 1.0;
     return (double)c;
+}
+
+// Position cnt of candidate x (survival ax) in the admission order and the sum of the
+// a before it; S consecutive lanes share a candidate, lane s of them takes every S-th key.
+template <int S>
+__device__ __forceinline__ void rank_of(const double* a_l, int N, int x, double ax, int s, int& cnt, double& sum) {
+    // y comes before x iff a_y > a_x, or a_y == a_x and y < x: over y < x
+    // the test is a_y >= a_x, over y > x it is a_y > a_x
+    cnt = 0;
+    sum = 0.0;
+    if (ax > 0.0) {
+#pragma unroll 8
+        for (int i = s; i < x; i += S) {
+            const double ay = a_l[i];
+            const bool b = ay >= ax;
+            cnt += b;
+            sum = sum + (b ? ay : 0.0);
+        }
+        const int i1 = x + 1 + ((s - (x + 1)) & (S - 1));  // first i > x with i % S == s
+#pragma unroll 8
+        for (int i = i1; i < N; i += S) {
+            const double ay = a_l[i];
+            const bool b = ay > ax;
+            cnt += b;
+            sum = sum + (b ? ay : 0.0);
+        }
+    }
+#pragma unroll
+    for (int o = S / 2; o > 0; o >>= 1) {
+        cnt += __shfl_xor(cnt, o, DSPARK_WAVE);
+        sum = sum + __shfl_xor(sum, o, DSPARK_WAVE);
+    }
 }
 
 __global__ __launch_bounds__(kRankThreads) void sched_rank(const float* __restrict__ conf, int R,
@@ -97,32 +132,9 @@ __global__ __launch_bounds__(kRankThreads) void sched_rank(const float* __restri
     const int s = tid % kRankSlices;
     const int x = blockIdx.x * kRankCand + tid / kRankSlices;
     const double ax = x < N ? a_l[x] : 0.0;
-    // y comes before x iff a_y > a_x, or a_y == a_x and y < x: over y < x
-    // the test is a_y >= a_x, over y > x it is a_y > a_x
-    int cnt = 0;
-    double sum = 0.0;
-    if (ax > 0.0) {
-#pragma unroll 8
-        for (int i = s; i < x; i += kRankSlices) {
-            const double ay = a_l[i];
-            const bool b = ay >= ax;
-            cnt += b;
-            sum = sum + (b ? ay : 0.0);
-        }
-        const int i1 = x + 1 + ((s - (x + 1)) & (kRankSlices - 1));  // first i > x with i % 16 == s
-#pragma unroll 8
-        for (int i = i1; i < N; i += kRankSlices) {
-            const double ay = a_l[i];
-            const bool b = ay > ax;
-            cnt += b;
-            sum = sum + (b ? ay : 0.0);
-        }
-    }
-#pragma unroll
-    for (int o = kRankSlices / 2; o > 0; o >>= 1) {
-        cnt += __shfl_xor(cnt, o, DSPARK_WAVE);
-        sum = sum + __shfl_xor(sum, o, DSPARK_WAVE);
-    }
+    int cnt;
+    double sum;
+    rank_of<kRankSlices>(a_l, N, x, ax, s, cnt, sum);
 
     // 3. scatter by position
     double* tau = reinterpret_cast<double*>(ws + ws_tau_off());
@@ -134,12 +146,14 @@ __global__ __launch_bounds__(kRankThreads) void sched_rank(const float* __restri
     if (blockIdx.x == 0 && tid == 0) *reinterpret_cast<int32_t*>(ws) = s_ncand;
 }
 
+// The selection of one workgroup of kSelThreads from the candidates' tau and flat
+// index by position (tau_s, idx_s), lenl [R] its LDS for the lengths.
 template <int E>
-__global__ __launch_bounds__(kSelThreads) void sched_select(
-    const unsigned char* __restrict__ ws, int R, int K, const double* __restrict__ sps, int mode,
-    const int32_t* __restrict__ cap_in, int32_t* __restrict__ cap_out,
-    int32_t* __restrict__ len_out, int32_t* __restrict__ cu_q, int32_t* __restrict__ tok_req) {
-    extern __shared__ int32_t lenl[];  // [R]
+__device__ __forceinline__ void select_body(
+    const double* tau_s, const int32_t* idx_s, const int ncand, int32_t* lenl, int R, int K,
+    const double* __restrict__ sps, int mode, const int32_t* __restrict__ cap_in,
+    int32_t* __restrict__ cap_out, int32_t* __restrict__ len_out, int32_t* __restrict__ cu_q,
+    int32_t* __restrict__ tok_req) {
     __shared__ int s_first;
     __shared__ double s_best_v[kSelWaves];
     __shared__ int s_best_n[kSelWaves];
@@ -149,8 +163,6 @@ __global__ __launch_bounds__(kSelThreads) void sched_select(
     const int lane = tid & (DSPARK_WAVE - 1);
     const int wave = tid / DSPARK_WAVE;
     const int N = R * K;
-    const double* tau_s = reinterpret_cast<const double*>(ws + ws_tau_off());
-    const int32_t* idx_s = reinterpret_cast<const int32_t*>(ws + ws_idx_off(N));
 
     // every load up front (positions past the candidate count are read but
     // never used): this thread's positions i0 .. i0 + E - 1, tau at i0 - 1,
@@ -176,7 +188,6 @@ __global__ __launch_bounds__(kSelThreads) void sched_select(
     }
 #pragma unroll
     for (int e = 0; e < E; ++e) iv[e] = idx_s[min(i0 + e, nmax)];
-    const int ncand = *reinterpret_cast<const int32_t*>(ws);  // written by sched_rank, N = 0 too
 
     for (int r = tid; r < R; r += kSelThreads) lenl[r] = 0;
     if (tid == 0) s_first = ncand;
@@ -294,6 +305,63 @@ __global__ __launch_bounds__(kSelThreads) void sched_select(
 }
 
 template <int E>
+__global__ __launch_bounds__(kSelThreads) void sched_select(
+    const unsigned char* __restrict__ ws, int R, int K, const double* __restrict__ sps, int mode,
+    const int32_t* __restrict__ cap_in, int32_t* __restrict__ cap_out,
+    int32_t* __restrict__ len_out, int32_t* __restrict__ cu_q, int32_t* __restrict__ tok_req) {
+    extern __shared__ int32_t lenl[];  // [R]
+    const int ncand = *reinterpret_cast<const int32_t*>(ws);  // written by sched_rank, N = 0 too
+    select_body<E>(reinterpret_cast<const double*>(ws + ws_tau_off()),
+                   reinterpret_cast<const int32_t*>(ws + ws_idx_off(R * K)), ncand, lenl, R, K, sps, mode,
+                   cap_in, cap_out, len_out, cu_q, tok_req);
+}
+
+// Both in one workgroup, for at most kOneMax candidates (eight lanes each),
+// positions and tau through LDS instead of the workspace: a launch less against one
+// CU's share of the N x N comparisons.  One call 13.2 -> 11.2 us for 32 candidates,
+// capacity and top-K together 24.6 -> 20.4 for 128; with 256 candidates, two to a lane
+// group, the gain was gone, with 512 it took twice the time.
+constexpr int kOneMax = 128, kOneSlices = kSelThreads / kOneMax;
+__global__ __launch_bounds__(kSelThreads) void sched_one(
+    const float* __restrict__ conf, int R, int K, const double* __restrict__ sps, int mode,
+    const int32_t* __restrict__ cap_in, int32_t* __restrict__ cap_out,
+    int32_t* __restrict__ len_out, int32_t* __restrict__ cu_q, int32_t* __restrict__ tok_req) {
+    __shared__ double a_l[kOneMax], tau_l[kOneMax];
+    __shared__ float conf_l[kOneMax];
+    __shared__ int32_t idx_l[kOneMax], lenl[kOneMax];
+    __shared__ int s_ncand;
+    const int tid = threadIdx.x;
+    const int N = R * K;
+    if (tid == 0) s_ncand = 0;
+    if (tid < N) conf_l[tid] = conf[tid];
+    __syncthreads();
+    if (tid < R) {
+        double p = 1.0;
+        int mine = 0;
+        for (int j = 0; j < K; ++j) {
+            p = p * sched_conf(conf_l[tid * K + j]);
+            a_l[tid * K + j] = p;
+            mine += p > 0.0;
+        }
+        if (mine) atomicAdd(&s_ncand, mine);
+    }
+    __syncthreads();
+    {
+        const int x = tid / kOneSlices;
+        const double ax = x < N ? a_l[x] : 0.0;
+        int cnt;
+        double sum;
+        rank_of<kOneSlices>(a_l, N, x, ax, tid % kOneSlices, cnt, sum);
+        if (tid % kOneSlices == 0 && ax > 0.0) {
+            tau_l[cnt] = (double)R + (sum + ax);
+            idx_l[cnt] = x;
+        }
+    }
+    __syncthreads();
+    select_body<1>(tau_l, idx_l, s_ncand, lenl, R, K, sps, mode, cap_in, cap_out, len_out, cu_q, tok_req);
+}
+
+template <int E>
 static hipError_t launch_select(const unsigned char* ws, int R, int K, const double* sps,
                                 int mode, const int32_t* cap_in, int32_t* cap_out, int32_t* len,
                                 int32_t* cu_q, int32_t* tok_req, hipStream_t s) {
@@ -307,6 +375,11 @@ hipError_t launch_schedule(const float* conf, int R, int K, const double* sps, i
                            int32_t* tok_req, void* ws, hipStream_t s) {
     const int N = R * K;
     unsigned char* w = static_cast<unsigned char*>(ws);
+    if (N > 0 && N <= kOneMax) {
+        hipLaunchKernelGGL(sched_one, dim3(1), dim3(kSelThreads), 0, s, conf, R, K, sps, mode, cap_in, cap_out, len,
+                           cu_q, tok_req);
+        return hipGetLastError();
+    }
     const size_t lds = (size_t)(N > 0 ? N : 1) * 12;
     if (lds >= 64 * 1024) {
         hipError_t e = hipFuncSetAttribute((const void*)sched_rank,

@@ -180,3 +180,20 @@ def test_topk_sizes(R, K):
     conf = synth.confidences(w, 5)
     for frac in (0.0, 0.1, 0.5, 0.97, 1.2):
         _check_topk(conf, int(frac * R * K), f"R{R}K{K}")
+
+
+@pytest.mark.parametrize("R,K", [(1, 1), (128, 1), (129, 1), (16, 8), (43, 3), (2, 64), (63, 2), (64, 2)])
+def test_one_workgroup_limit(R, K):
+    """Up to 128 candidates one workgroup ranks and selects, above that two
+    kernels do: both modes, the capacity and the top-K admission around the
+    line, with ties, zeros and requests that end early."""
+    rng = np.random.default_rng(R * 100 + K)
+    conf = rng.beta(3.0, 1.0, (R, K)).astype(np.float32)
+    conf[rng.random((R, K)) < 0.1] = 0.0
+    if R > 1:
+        conf[1] = conf[0]
+    sps = 1.0 / (1.0 + np.maximum(0.0, np.arange(R * (K + 1) + 1) - R * 1.3) / 64.0)
+    for mode in (0, 1):
+        _check(conf, sps, mode, f"line mode{mode}")
+    for cap in (-1, 0, 1, R * K // 2, R * K, R * K + 5):
+        _check_topk(conf, cap, "line")
