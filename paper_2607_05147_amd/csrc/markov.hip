@@ -1114,8 +1114,8 @@ __global__ __launch_bounds__(kThreads) void rnn_hproj(MarkovArgs a, float* Hp, i
     }
 }
 
-// Parts of the backbone projection, at most: three workgroups per CU or so, and a
-// part per wave of the recurrence, which adds them to its products.
+// Parts of the backbone projection, at most: three workgroups per CU or so, and the
+// recurrence's waves add a part or two each to their products.
 constexpr int kHpParts = 8;
 inline int hp_parts(int R, int K, int rank) {
     const int64_t wgs = (((int64_t)R * K + kHpRows - 1) / kHpRows) * ceil_div(3 * rank, kHpCols);
@@ -1149,12 +1149,12 @@ __device__ __forceinline__ void split3(float v, uint16_t* dst, int stride) {
 // tanh(a_c) with g = sigmoid(a_g), written in fp32 and as three terms, and the
 // head's output o_k = tanh(a_o) as two terms (hi, mid) for the vocabulary
 // product.  A workgroup owns
-// 16 dims x 16 requests; its eight waves take every eighth 32-input step (both
-// operands straight from memory, kStDepth steps ahead: all of them at rank 256) and
-// wave 0 adds the eight partial products in wave order.  The state is double-buffered (others
+// 16 dims x 16 requests; its four waves take every fourth 32-input step (both
+// operands straight from memory, kStDepth steps ahead) and wave 0 adds the
+// four partial products in wave order (eight waves: 2 us a position more).  The state is double-buffered (others
 // may still read s_{k-1}); at k = 1 it is zero and its steps are skipped.
-constexpr int kStJ = 16, kStR = 16, kStDepth = 4, kStWaves = 8;
-static_assert(kHpParts <= kStWaves && kHpParts <= kCoWaves, "a part of the backbone projection per wave");
+constexpr int kStJ = 16, kStR = 16, kStDepth = 4, kStWaves = 4;
+static_assert(kHpParts <= 2 * kStWaves && kHpParts <= kCoWaves, "parts of the backbone projection per wave");
 __global__ __launch_bounds__(kStWaves * DSPARK_WAVE) void rnn_state(MarkovArgs a, const float* Hp, int hpz,
                                                       const float* s_prev, const uint16_t* S3_prev,
                                                       float* s_next, uint16_t* S3_next,
@@ -1180,17 +1180,21 @@ __global__ __launch_bounds__(kStWaves * DSPARK_WAVE) void rnn_state(MarkovArgs a
             bfr[slot][p] = *(const bf16x8*)(a.Wrnn + (int64_t)(p * rank + j0 + lr) * nz + col);
     };
     const int nmine = st0 < nst ? (nst - st0 + kStWaves - 1) / kStWaves : 0;
-    // the projection of the hidden states (wave w takes part w of it) and, in wave
-    // 0, the previous state, of requests m0 + 4 lq + e, dim j0 + lr, do not depend on
+    // the projection of the hidden states (wave w takes its parts w and w + 4) and, in
+    // wave 0, the previous state, of requests m0 + 4 lq + e, dim j0 + lr, do not depend on
     // the products: they are loaded first (rows clamped, then masked)
     const int j = j0 + lr;
-    float hpv[4][3], spv[4];
+    float hpv[4][3], hpw[4][3], spv[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         const int rc = min(m0 + 4 * lq + e, a.R - 1);
-        const float* hp = Hp + ((int64_t)wave * a.R * a.K + (int64_t)rc * a.K + (k - 1)) * (3 * rank) + j;
+        const int64_t all = (int64_t)a.R * a.K * 3 * rank;  // of a part
+        const float* hp = Hp + wave * all + ((int64_t)rc * a.K + (k - 1)) * (3 * rank) + j;
 #pragma unroll
-        for (int p = 0; p < 3; ++p) hpv[e][p] = wave < hpz ? hp[p * rank] : 0.0f;
+        for (int p = 0; p < 3; ++p) {
+            hpv[e][p] = wave < hpz ? hp[p * rank] : 0.0f;
+            hpw[e][p] = wave + kStWaves < hpz ? hp[kStWaves * all + p * rank] : 0.0f;
+        }
         spv[e] = wave == 0 && k > 1 ? s_prev[(int64_t)rc * rank + j] : 0.0f;
     }
     f32x4 acc[3];
@@ -1212,7 +1216,7 @@ __global__ __launch_bounds__(kStWaves * DSPARK_WAVE) void rnn_state(MarkovArgs a
 #pragma unroll
     for (int p = 0; p < 3; ++p)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) acc[p][e] += hpv[e][p];
+        for (int e = 0; e < 4; ++e) acc[p][e] += hpv[e][p] + hpw[e][p];
     if (wave > 0) {
 #pragma unroll
         for (int p = 0; p < 3; ++p) part[wave - 1][p][lane] = acc[p];
