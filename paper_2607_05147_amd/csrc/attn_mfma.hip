@@ -133,11 +133,13 @@ static MfGeom mf_geom(const AttnArgs& a) {
     return g;
 }
 
+// What the path writes, and never less than the queue's: a call is refused for its
+// workspace alike whichever way its batch is cut.
 size_t attn_mfma_workspace(const AttnArgs& a) {
     const MfGeom g = mf_geom(a);
-    if (g.direct) return 0;
-    if (g.ranges) return range_head_bytes(a.R) + (size_t)g.workers * 2 * g.slot_floats * sizeof(float);
-    return g.counter_bytes + g.list_bytes + g.mlist_bytes + g.part_bytes;
+    const size_t queue = g.counter_bytes + g.list_bytes + g.mlist_bytes + g.part_bytes;
+    if (g.direct || !g.ranges) return queue;
+    return std::max(queue, range_head_bytes(a.R) + (size_t)g.workers * 2 * g.slot_floats * sizeof(float));
 }
 
 struct MfParams {
