@@ -672,42 +672,51 @@ struct CoopArgs {
 // to the loads and the row statistics.
 __device__ __forceinline__ void pin_acc(f32x4& v) { asm volatile("" : "+a"(v)); }
 
-// Arrival at barrier b of this workgroup, whose earlier stores are complete, and
-// the wait for the others; the work between the two is not ordered by the barrier.
-__device__ __forceinline__ void grid_arrive(unsigned* sync, unsigned b) {
+// One thread's part of barrier b: its workgroup's arrival, and the wait for the others.
+__device__ __forceinline__ void sync_arrive(unsigned* sync, unsigned b) {
+    const unsigned G = gridDim.x, x = blockIdx.x % kCoGroups;
+    const unsigned nx = (G - x + kCoGroups - 1) / kCoGroups, ngrp = min(G, (unsigned)kCoGroups);
+    if (__hip_atomic_fetch_add(sync + kSyncStride * (1 + x), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) +
+                1u == nx * b &&
+        __hip_atomic_fetch_add(sync, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == ngrp * b) {
+        for (unsigned y = 0; y < ngrp; ++y)
+            __hip_atomic_store(sync + kSyncStride * (1 + kCoGroups + y), b, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+__device__ __forceinline__ void sync_poll(unsigned* sync, unsigned b) {
+    unsigned* flag = sync + kSyncStride * (1 + kCoGroups + blockIdx.x % kCoGroups);
+    const uint64_t t0 = wall_clock64();
+    while (__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < b &&
+           __hip_atomic_load(sync + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u) {
+        __builtin_amdgcn_s_sleep(8);
+        if (wall_clock64() - t0 > kSyncTimeout)
+            __hip_atomic_store(sync + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+__device__ __forceinline__ void grid_barrier(unsigned* sync, unsigned b) {
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
     __builtin_amdgcn_s_waitcnt(0);  // this thread's stores are complete
     __syncthreads();
     if (threadIdx.x == 0) {
-        const unsigned G = gridDim.x, x = blockIdx.x % kCoGroups;
-        const unsigned nx = (G - x + kCoGroups - 1) / kCoGroups, ngrp = min(G, (unsigned)kCoGroups);
-        if (__hip_atomic_fetch_add(sync + kSyncStride * (1 + x), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) +
-                    1u == nx * b &&
-            __hip_atomic_fetch_add(sync, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == ngrp * b) {
-            for (unsigned y = 0; y < ngrp; ++y)
-                __hip_atomic_store(sync + kSyncStride * (1 + kCoGroups + y), b, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-        }
-    }
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-}
-__device__ __forceinline__ void grid_wait(unsigned* sync, unsigned b) {
-    if (threadIdx.x == 0) {
-        unsigned* flag = sync + kSyncStride * (1 + kCoGroups + blockIdx.x % kCoGroups);
-        const uint64_t t0 = wall_clock64();
-        while (__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < b &&
-               __hip_atomic_load(sync + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u) {
-            __builtin_amdgcn_s_sleep(8);
-            if (wall_clock64() - t0 > kSyncTimeout)
-                __hip_atomic_store(sync + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
+        sync_arrive(sync, b);
+        sync_poll(sync, b);
     }
     __syncthreads();
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
 }
-__device__ __forceinline__ void grid_barrier(unsigned* sync, unsigned b) {
-    grid_arrive(sync, b);
-    grid_wait(sync, b);
+// The barrier in two halves; the work between them is not ordered by it.
+__device__ __forceinline__ void grid_arrive(unsigned* sync, unsigned b) {
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    if (threadIdx.x == 0) sync_arrive(sync, b);
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+}
+__device__ __forceinline__ void grid_wait(unsigned* sync, unsigned b) {
+    if (threadIdx.x == 0) sync_poll(sync, b);
+    __syncthreads();
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
 }
 
 template <int KS, int NT>
@@ -1617,6 +1626,9 @@ __global__ __launch_bounds__(kCoThreads) void md_block(BlockArgs c, const bool v
 // several tiles or rows in turn (fp32, 32 requests: 537 us with 32768 entries and 322
 // with 3000, against 305 and 245 in three launches per position), so there it is at
 // most 64 tiles and a request per wave.
+// The RNN head takes it only in md_coop's place: its recurrence on 64 workgroups costs
+// more than the launches (8 requests x 8000, d = 4096: 403 against 336 us; 1 x 7360,
+// d = 0: 275 against 242).
 constexpr int kBkGrid = 64, kBkGridAlone = 256;
 template <int KS, int NT, bool BF16>
 int block_grid(const MarkovArgs& a, int ntiles, bool alone) {
@@ -1640,11 +1652,18 @@ int block_grid(const MarkovArgs& a, int ntiles, bool alone) {
 template <int KS, int NT>
 bool launch_block(const BlockArgs& c, bool vec, hipStream_t s) {
     const bool alone = coop_applies<KS, NT>(c.a, c.ntiles, vec);
-    const int G = c.a.base_bf16 ? block_grid<KS, NT, true>(c.a, c.ntiles, alone)
-                                : block_grid<KS, NT, false>(c.a, c.ntiles, alone);
-    if (G == 0) return false;
-    if (c.a.base_bf16) hipLaunchKernelGGL((md_block<KS, NT, true>), dim3(G), dim3(kCoThreads), 0, s, c, vec);
-    else hipLaunchKernelGGL((md_block<KS, NT, false>), dim3(G), dim3(kCoThreads), 0, s, c, vec);
+    if (c.a.base_bf16) {
+        if (NT == 2 && !alone) return false;
+        const int G = block_grid<KS, NT, true>(c.a, c.ntiles, alone);
+        if (G == 0) return false;
+        hipLaunchKernelGGL((md_block<KS, NT, true>), dim3(G), dim3(kCoThreads), 0, s, c, vec);
+    } else if constexpr (NT == 1) {
+        const int G = block_grid<KS, NT, false>(c.a, c.ntiles, alone);
+        if (G == 0) return false;
+        hipLaunchKernelGGL((md_block<KS, NT, false>), dim3(G), dim3(kCoThreads), 0, s, c, vec);
+    } else {
+        return false;
+    }
     return true;
 }
 

@@ -162,7 +162,7 @@ def test_rnn_draft_degenerate_shapes(R, K, V):
         assert (tok == 0).all().item() and torch.equal(p, torch.ones_like(p))
 
 
-# one launch for the block (up to 8 requests x 64 tiles, or 32 requests of bf16 logits) against
+# one launch for the block (up to 32 requests of bf16 logits, V % 4 == 0) against
 # launches per position; the backbone projection in one part (d = 0 has none), a few and eight
 @pytest.mark.parametrize("R,K,V,rank,d,dt", [
     (8, 3, 8192, 64, 256, "f32"), (9, 3, 8192, 64, 264, "f32"), (32, 3, 1000, 64, 2048, "bf16"),
