@@ -737,7 +737,13 @@ __device__ __forceinline__ void value_item(const Params& p, const int r, const i
 // Persistent workgroups of eight waves: workgroup b serves queue b % 8 (its
 // XCD), then the others.  Each role runs its own item loop; the loops meet at
 // the same barriers.
+// Spilled registers lie in the queue's scratch memory, where waves are as far apart as
+// the largest kernel run on it has asked for.  With this kernel's 244 bytes a lane that is
+// 16 KB, and the spills of the drafter's kernels met in few cache sets: a Markov block of
+// 128 x 129280 after any latent call took 1058 us against 1000.  With `pad` it is 18 KB.
 __global__ __launch_bounds__(kThreads) void mla_kernel(Params p) {
+    volatile int pad[8];
+    pad[threadIdx.x & 7] = 0;
     __shared__ __align__(16) unsigned char lds[kRing * kTileB];
     __shared__ Shared sh;
     uint32_t lds0 = (uint32_t)(uintptr_t)&lds[0];
