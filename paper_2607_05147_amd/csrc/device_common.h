@@ -81,11 +81,13 @@ __device__ __forceinline__ T* lds_ptr(uint32_t addr) {
 // 16-byte copy global -> LDS for a whole wave: lane L's 16 bytes land at
 // lds_addr + 16 L (lds_addr is wave-uniform).  Emitted as inline asm so that
 // the compiler does not add its own conservative waits for it; the kernels
-// wait for these copies with explicit vmcnt counts.
+// wait for these copies with explicit vmcnt counts.  The copy reads m0 no sooner than
+// one wait state after it is written, and the compiler adds none inside the block.
 __device__ __forceinline__ void lds_copy16(const void* gsrc, uint32_t lds_addr) {
     const uint32_t m0 = __builtin_amdgcn_readfirstlane(lds_addr);
     asm volatile(
         "s_mov_b32 m0, %0\n\t"
+        "s_nop 0\n\t"
         "global_load_lds_dwordx4 %1, off"
         :
         : "s"(m0), "v"(gsrc)
@@ -100,6 +102,7 @@ __device__ __forceinline__ void lds_copy16_s(uint64_t sbase, uint32_t voff, uint
     const uint64_t sb = ((uint64_t)hi << 32) | lo;
     asm volatile(
         "s_mov_b32 m0, %0\n\t"
+        "s_nop 0\n\t"
         "global_load_lds_dwordx4 %1, %2"
         :
         : "s"(m0), "v"(voff), "s"(sb)
