@@ -576,7 +576,10 @@ __device__ __forceinline__ void value_item(const Params& p, const int r, const i
         t = pp_ / kRowChunks;
         c = pchunk(t, pp_ - t * kRowChunks);
     };
-    const uint64_t kc_head = (uint64_t)(uintptr_t)kc + (uint64_t)((uint32_t)g * p.s1b);
+    // kc_head and the item's first key in scalar registers: a step's page base is then
+    // scalar arithmetic, and no vector instruction writes the copies' address right
+    // before them
+    const uint64_t kc_head = uniform64((uint64_t)(uintptr_t)kc + (uint64_t)((uint32_t)g * p.s1b));
     const uint32_t lds_wave = __builtin_amdgcn_readfirstlane(lds0 + first * 1024);
     auto page_of = [&](int idx) {
         int pg = 0;
@@ -592,8 +595,9 @@ __device__ __forceinline__ void value_item(const Params& p, const int r, const i
         cp_at(i, lane, t, c);
         cpo[i] = t * p.s2b + 16 * c;
     }
+    const int start_s = __builtin_amdgcn_readfirstlane(start);
     auto issue = [&](int n) {
-        const int tok0 = start + n * kStep;
+        const int tok0 = start_s + n * kStep;
         const int pidx = min(max((tok0 >> p.page_shift) - pg0, 0), kPageRegs * DSPARK_WAVE - 1);
         const int page = page_of(pidx);
         const int slot0 = tok0 & ((1 << p.page_shift) - 1);

@@ -94,12 +94,19 @@ __device__ __forceinline__ void lds_copy16(const void* gsrc, uint32_t lds_addr) 
         : "memory", "m0");
 }
 
-// the same with a wave-uniform 64-bit base (SGPRs) and a per-lane 32-bit offset
+// a wave-uniform 64-bit value, in scalar registers
+__device__ __forceinline__ uint64_t uniform64(uint64_t v) {
+    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
+    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+    return ((uint64_t)hi << 32) | lo;
+}
+
+// the same with a wave-uniform 64-bit base (SGPRs) and a per-lane 32-bit offset.  The
+// base has to come from scalar arithmetic: a vector instruction's write of it would need
+// five wait states before the copy, which the compiler does not add inside the block.
 __device__ __forceinline__ void lds_copy16_s(uint64_t sbase, uint32_t voff, uint32_t lds_addr) {
     const uint32_t m0 = __builtin_amdgcn_readfirstlane(lds_addr);
-    const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)sbase);
-    const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(sbase >> 32));
-    const uint64_t sb = ((uint64_t)hi << 32) | lo;
+    const uint64_t sb = uniform64(sbase);
     asm volatile(
         "s_mov_b32 m0, %0\n\t"
         "s_nop 0\n\t"

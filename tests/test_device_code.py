@@ -2,7 +2,9 @@
 
 The copies from memory into LDS are written as inline assembly, inside which the
 compiler inserts no wait states, so what the hardware asks for has to hold in the
-code as built: one between a scalar write of m0 and the copy that reads it.
+code as built: one between a scalar write of m0 and the copy that reads it, and five
+between a vector instruction's write of a scalar register and the copy that takes its
+address from there.
 """
 import os
 import re
@@ -41,26 +43,56 @@ def _instructions(co):
             yield kernel, words[0], [x.strip() for x in words[1].split(",")] if len(words) > 1 else []
 
 
+def _sgprs(operand):
+    m = re.match(r"s\[(\d+):(\d+)\]|s(\d+)", operand)
+    if not m:
+        return set()
+    return {int(m[3])} if m[3] else set(range(int(m[1]), int(m[2]) + 1))
+
+
 def _hazards(code):
-    """Copies into LDS that come right after the write of m0 that they read."""
-    found, copies, last = [], 0, (None, None, [""])
+    """Copies into LDS that come too soon after the write of a scalar register that they
+    read: m0, and the address registers written by a vector instruction."""
+    m0, address, copies, before, now = [], [], 0, [], None
     for kernel, op, args in code:
+        if kernel != now:
+            before, now = [], kernel
         if op.startswith("global_load_lds"):
             copies += 1
-            if last[0] == kernel and last[2][:1] == ["m0"]:
-                found.append(f"{kernel}: {last[1]} {last[2]} right before {op} {args}")
-        last = kernel, op, args
-    return found, copies
+            reads = set().union(*(_sgprs(a) for a in args))
+            states = 0
+            for o, a in reversed(before):
+                if states < 1 and a[:1] == ["m0"]:
+                    m0.append(f"{kernel}: {o} {a} right before {op} {args}")
+                if o.startswith("v_") and a and _sgprs(a[0]) & reads:
+                    address.append(f"{kernel}: {o} {a} {states} states before {op} {args}")
+                states += int(a[0], 0) + 1 if o == "s_nop" else 1
+                if states >= 5:
+                    break
+        before = before[-8:] + [(op, args)]
+    return m0, address, copies
 
 
 def test_the_scan_sees_a_missing_wait():
-    copy = ("k", "global_load_lds_dwordx4", ["v1", "s[0:1]"])
-    m0, nop = ("k", "s_mov_b32", ["m0", "s4"]), ("k", "s_nop", ["0"])
-    assert len(_hazards([m0, copy])[0]) == 1 and _hazards([m0, nop, copy]) == ([], 1)
+    copy, nop = ("k", "global_load_lds_dwordx4", ["v1", "s[0:1]"]), lambda n: ("k", "s_nop", [str(n)])
+    m0, lane = ("k", "s_mov_b32", ["m0", "s4"]), ("k", "v_readfirstlane_b32", ["s1", "v2"])
+    assert len(_hazards([m0, copy])[0]) == 1 and _hazards([m0, nop(0), copy]) == ([], [], 1)
+    assert len(_hazards([lane, nop(3), copy])[1]) == 1 and _hazards([lane, nop(4), copy]) == ([], [], 1)
 
 
-@pytest.mark.parametrize("name", [os.path.basename(s) for s in build.sources()])
-def test_copies_into_lds_wait_for_m0(name, tmp_path):
-    found, copies = _hazards(_instructions(_code_object(os.path.join(build.CSRC, name), tmp_path)))
-    assert not found, f"{len(found)} of {copies}: " + "; ".join(found[:3])
-    assert copies > 0 or not name.startswith(("attn_m", "attn_stream"))
+@pytest.fixture(scope="module", params=[os.path.basename(s) for s in build.sources()])
+def copies(request, tmp_path_factory):
+    code = _code_object(os.path.join(build.CSRC, request.param), tmp_path_factory.mktemp("code"))
+    m0, address, n = _hazards(_instructions(code))
+    assert n > 0 or not request.param.startswith(("attn_m", "attn_stream"))
+    return m0, address, n
+
+
+def test_copies_into_lds_wait_for_m0(copies):
+    m0, _, n = copies
+    assert not m0, f"{len(m0)} of {n}: " + "; ".join(m0[:3])
+
+
+def test_copies_into_lds_wait_for_their_address(copies):
+    _, address, n = copies
+    assert not address, f"{len(address)} of {n}: " + "; ".join(address[:3])
