@@ -301,6 +301,13 @@ dspark_status dspark_accept(const int32_t* draft_tok, const float* draft_p, cons
  *   An anchor outside [0, V) marks its request invalid: its draft_tok row is
  *   -1 and its conf row NaN (its draft_p rows hold finite values computed
  *   with embedding row 0).
+ *   Large batches of bf16 base logits (min(R, 128) * V >= 10^7, V % 4 == 0,
+ *   V <= 131072) run kernels that wait across workgroups: a launch holds
+ *   ceil(V / 512) compute units until all of its workgroups have started.  Such
+ *   calls on several streams are all served while these counts add up to at most
+ *   the device's compute units; a launch that cannot start whole within 2 s gives
+ *   up, and its block is marked invalid like one of bad anchors (draft_tok -1,
+ *   conf NaN; draft_p unspecified).  No other call waits for another workgroup.
  *   Limits: 1 <= R <= 8192, 1 <= K <= 64, 1 <= V <= 262144, 0 <= d <= 2^16,
  *   inv_temperature > 0; W1, W2t 16-byte aligned.  The base logits and
  *   draft_p are read and written four entries at a time when V and ld are

@@ -96,6 +96,7 @@ size_t markov_workspace(int R, int K, int V, int rank);
 size_t rnn_workspace(int R, int K, int V, int rank);
 hipError_t launch_rnn(const MarkovArgs& a, void* ws, hipStream_t s);
 bool markov_rank_supported(int rank);
+int markov_coop_grid(int R, int V);  // workgroups that a drafter's launch holds at once (0: no such launch)
 int markov_max_vocab();  // per-tile statistics of one request fit one workgroup
 hipError_t launch_markov(const MarkovArgs& a, void* ws, hipStream_t s);
 

@@ -9,7 +9,7 @@
 //   x_k = inverse CDF of p_k at u[r, k-1];   c_k = sigmoid(w . [h_k; e_k] / T_k).
 // Launches, all on one stream: md_hidden (the backbone part w_h . h_k of every
 // confidence logit, once) and md_first (e_1 and c_1), then per position k
-// either one md_coop launch per group of up to 128 requests (bf16 base
+// either one md_coop launch per group of up to 128 requests (large batches of bf16 base
 // logits, V % 4 == 0, a grid the device holds at once; md_check after the
 // block), which keeps z in registers across two grid-wide
 // exchanges so that the projection and the base logits are read once and p
@@ -28,7 +28,6 @@
 //             holds a request's draw makes it (fp64 prefix of that tile's
 //             masses), writes x_k, gathers e_{k+1} into the other embedding
 //             buffer and writes c_{k+1}.
-// A small batch runs all positions in one launch, md_block.
 // The positions of a block are sequential by definition (x_k feeds position
 // k + 1).
 #include <algorithm>
@@ -60,7 +59,6 @@ __host__ __device__ constexpr int ceil_div(int a, int b) { return (a + b - 1) / 
 constexpr int kCoGroups = 8;
 constexpr int kSyncStride = 32;
 constexpr int kSyncWords = kSyncStride * (1 + 2 * kCoGroups);
-constexpr int kTokBytes = 2 * 32 * 8;  // md_block's tokens of two positions
 
 // Slot of 16-byte chunk c in row t of the embedding chunk (nch chunks per row,
 // a power of two).  The XOR (bits of t in the order 0, 2, 1, 3) puts the 16
@@ -400,9 +398,8 @@ __device__ __forceinline__ RowInfo ld_info(const RowInfo* p) {
     return v;
 }
 
-// SC: the statistics are read device-coherently; SCS: the row's RowInfo (info[r])
-// is written so.
-template <int P, bool SC, bool SCS = SC>
+// SC: the statistics are read and the row's RowInfo written device-coherently.
+template <int P, bool SC>
 __device__ __forceinline__ void row_stats(const MarkovArgs& a, const float2* stats, RowInfo* info, int ntiles,
                                           int k, int r, int lane) {
     const float2* st = stats + (int64_t)r * ntiles;
@@ -466,13 +463,13 @@ __device__ __forceinline__ void row_stats(const MarkovArgs& a, const float2* sta
                 ri.tile = lastpos;
                 ri.thr = __builtin_huge_val();
             }
-            st_info<SCS>(info + r, ri);
+            st_info<SC>(info + r, ri);
         }
     } else if (lane == 0) {
         // rounding pushed u * total past the end: the row's last tile with mass
         ri.tile = max(last, 0);
         ri.thr = __builtin_huge_val();
-        st_info<SCS>(info + r, ri);
+        st_info<SC>(info + r, ri);
     }
 }
 
@@ -605,8 +602,8 @@ void position(const MarkovArgs& a, const uint16_t* E, float2* stats, uint16_t* E
 
 // ----------------------------------------------------------------- md_coop
 
-// One position of either head (bf16 base logits, V % 4 == 0, at most 1024
-// tiles; NT B terms per request: the Markov head's embedding, or the RNN
+// One position of either head (bf16 base logits, V % 4 == 0, a large batch of at most 1024
+// tiles: coop_grid; NT B terms per request: the Markov head's embedding, or the RNN
 // head's output as two terms, whose products add up in the accumulators) for
 // a group of up to 128 requests in one launch whose workgroups are
 // all resident at once (the grid is at most what the device holds, one
@@ -672,49 +669,29 @@ struct CoopArgs {
 // to the loads and the row statistics.
 __device__ __forceinline__ void pin_acc(f32x4& v) { asm volatile("" : "+a"(v)); }
 
-// One thread's part of barrier b: its workgroup's arrival, and the wait for the others.
-__device__ __forceinline__ void sync_arrive(unsigned* sync, unsigned b) {
-    const unsigned G = gridDim.x, x = blockIdx.x % kCoGroups;
-    const unsigned nx = (G - x + kCoGroups - 1) / kCoGroups, ngrp = min(G, (unsigned)kCoGroups);
-    if (__hip_atomic_fetch_add(sync + kSyncStride * (1 + x), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) +
-                1u == nx * b &&
-        __hip_atomic_fetch_add(sync, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == ngrp * b) {
-        for (unsigned y = 0; y < ngrp; ++y)
-            __hip_atomic_store(sync + kSyncStride * (1 + kCoGroups + y), b, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-    }
-}
-__device__ __forceinline__ void sync_poll(unsigned* sync, unsigned b) {
-    unsigned* flag = sync + kSyncStride * (1 + kCoGroups + blockIdx.x % kCoGroups);
-    const uint64_t t0 = wall_clock64();
-    while (__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < b &&
-           __hip_atomic_load(sync + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u) {
-        __builtin_amdgcn_s_sleep(8);
-        if (wall_clock64() - t0 > kSyncTimeout)
-            __hip_atomic_store(sync + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-}
 __device__ __forceinline__ void grid_barrier(unsigned* sync, unsigned b) {
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
     __builtin_amdgcn_s_waitcnt(0);  // this thread's stores are complete
     __syncthreads();
     if (threadIdx.x == 0) {
-        sync_arrive(sync, b);
-        sync_poll(sync, b);
+        const unsigned G = gridDim.x, x = blockIdx.x % kCoGroups;
+        const unsigned nx = (G - x + kCoGroups - 1) / kCoGroups, ngrp = min(G, (unsigned)kCoGroups);
+        if (__hip_atomic_fetch_add(sync + kSyncStride * (1 + x), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) +
+                    1u == nx * b &&
+            __hip_atomic_fetch_add(sync, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) + 1u == ngrp * b) {
+            for (unsigned y = 0; y < ngrp; ++y)
+                __hip_atomic_store(sync + kSyncStride * (1 + kCoGroups + y), b, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+        }
+        unsigned* flag = sync + kSyncStride * (1 + kCoGroups + x);
+        const uint64_t t0 = wall_clock64();
+        while (__hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < b &&
+               __hip_atomic_load(sync + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0u) {
+            __builtin_amdgcn_s_sleep(8);
+            if (wall_clock64() - t0 > kSyncTimeout)
+                __hip_atomic_store(sync + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
     }
-    __syncthreads();
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-}
-// The barrier in two halves; the work between them is not ordered by it.
-__device__ __forceinline__ void grid_arrive(unsigned* sync, unsigned b) {
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    if (threadIdx.x == 0) sync_arrive(sync, b);
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-}
-__device__ __forceinline__ void grid_wait(unsigned* sync, unsigned b) {
-    if (threadIdx.x == 0) sync_poll(sync, b);
     __syncthreads();
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
 }
@@ -1000,12 +977,27 @@ int coop_grid_limit() {
     return cache[dev] > 0 ? cache[dev] : 0;
 }
 
+// Workgroups of md_coop, 0 for batches that the launches per position draft: at most 1024
+// tiles (the row statistics' 16 per lane) and at least kCoLogits logits a launch.  What it
+// saves is z's way through memory, what it costs are two barriers and a chain of four
+// tiles per workgroup, and its workgroups hold as many CUs until all of them have started.
+// Us per block, md_coop against launches (K = 8, rank 256, Markov / RNN with d = 1024): 128
+// requests x 65536 entries 452 / 612 against 318 / 419, 72 x 129280 401 / 544 against 407 /
+// 532, 96 x 100000 418 / 566 against 415 / 530, 112 x 129280 462 / 627 against 543 / 667;
+// with K = 16, 8 x 129280 608 / 801 against 356 / 548, 128 x 129280 968 / 1346 against
+// 1200 / 1453.
+constexpr int64_t kCoLogits = 10000000;
+int coop_grid(int R, int ntiles, int V) {
+    if (ntiles > DSPARK_WAVE * 16 || (int64_t)std::min(R, kCoRows) * V < kCoLogits) return 0;
+    return ceil_div(ntiles, kCoTiles);
+}
+
 // One position as md_coop launches, one per group of up to 128 requests
 // (launch counts the block's launches: it numbers their barriers).
 template <int KS, int NT>
 void coop_position(const MarkovArgs& a, const uint16_t* E, uint16_t* En, float2* stats, RowInfo* info,
                    const float* shp, unsigned* sync, int ntiles, int k, unsigned& launch, hipStream_t s) {
-    const int G = ceil_div(ntiles, kCoTiles);
+    const int G = coop_grid(a.R, ntiles, a.V);
     for (int g0 = 0; g0 < a.R; g0 += kCoRows) {
         CoopArgs c;
         c.a = a;
@@ -1024,12 +1016,12 @@ void coop_position(const MarkovArgs& a, const uint16_t* E, uint16_t* En, float2*
     }
 }
 
-// md_coop applies: bf16 base logits, V % 4 == 0 (vec), at most 1024 tiles
-// (the row statistics' 16 tiles per lane), and a grid the device holds at once.
+// md_coop applies: bf16 base logits, V % 4 == 0 (vec), a large batch (coop_grid), and a
+// grid the device holds at once.
 template <int KS, int NT>
 bool coop_applies(const MarkovArgs& a, int ntiles, bool vec) {
-    return vec && a.base_bf16 && ntiles <= DSPARK_WAVE * 16 &&
-           ceil_div(ntiles, kCoTiles) <= coop_grid_limit<KS, NT>();
+    const int G = coop_grid(a.R, ntiles, a.V);
+    return vec && a.base_bf16 && G > 0 && G <= coop_grid_limit<KS, NT>();
 }
 
 // ------------------------------------------------------------ RNN head
@@ -1163,7 +1155,7 @@ __device__ __forceinline__ void split3(float v, uint16_t* dst, int stride) {
 // four partial products in wave order (eight waves: 2 us a position more).  The state is double-buffered (others
 // may still read s_{k-1}); at k = 1 it is zero and its steps are skipped.
 constexpr int kStJ = 16, kStR = 16, kStDepth = 4, kStWaves = 4;
-static_assert(kHpParts <= 2 * kStWaves && kHpParts <= kCoWaves, "parts of the backbone projection per wave");
+static_assert(kHpParts <= 2 * kStWaves, "parts of the backbone projection per wave");
 __global__ __launch_bounds__(kStWaves * DSPARK_WAVE) void rnn_state(MarkovArgs a, const float* Hp, int hpz,
                                                       const float* s_prev, const uint16_t* S3_prev,
                                                       float* s_next, uint16_t* S3_next,
@@ -1251,426 +1243,10 @@ __global__ __launch_bounds__(kStWaves * DSPARK_WAVE) void rnn_state(MarkovArgs a
     }
 }
 
-// ---------------------------------------------------------------- md_block
-
-// The whole block of a small batch (up to 32 requests) in one launch: the
-// positions are looped inside, with the workgroups resident at once and the
-// exchanges and barrier of md_coop.  A position at these sizes is a chain of
-// latencies (launches, loads, exchanges), not of bytes, so what counts is how many
-// links it has.  Per position:
-//   S  (RNN head) the recurrence, 16 state dims x 16 requests per workgroup, its
-//      32-input steps over the eight waves; barrier;
-//   A  e_k = W1[x_{k-1}] (or the head's output) into LDS, the products of the
-//      workgroup's up to four tiles, z in registers, tile statistics; barrier;
-//   B  every workgroup computes every row's statistics itself from the tile
-//      statistics (at most kBkStats of them), which saves an exchange;
-//   C  the draws of the tiles owned here; x_k is all that crosses to the next
-//      position, whose barrier the workgroup arrives at before it writes p and
-//      loads the next position's first tile.
-// W2t is read again at every position, from the caches (a tile per workgroup).
-// Against the launches per position (us per block): (bf16, K = 16): 1 request x
-// 12416 entries 502 -> 196, 20 x 4000 497 -> 238, 24 x 50000 622 -> 409, 8 x 129280
-// 637 -> 543; RNN head, 8 x 129280 890 -> 734.
-constexpr int kBkRows = 32, kBkRT = kBkRows / 16;
-constexpr int kBkStats = 10240;  // tile statistics of a position, at most
-
-struct BlockArgs {
-    MarkovArgs a;
-    float2* stats;   // [R, ntiles]
-    const float* sh; // w_h . h per (r, k), or null
-    uint64_t* tok;   // [2][kBkRows] x of the last two positions (device-coherent)
-    unsigned* sync;
-    int ntiles;
-    // RNN head
-    const float* Hp;  // backbone part of the projection, in hpz parts
-    int hpz;
-    float* S[2];      // [R, rank] state, double-buffered by position
-    uint16_t* T[2];   // [R, 3 rank] state as three terms
-    uint16_t* E2;     // [R, 2 rank] output as two terms
-};
-
-__device__ __forceinline__ void st_dev16(uint16_t* p, uint16_t v) {
-    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void st_dev32(float* p, float v) {
-    __hip_atomic_store((uint32_t*)p, __float_as_uint(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ float ld_dev32(const float* p) {
-    return __uint_as_float(__hip_atomic_load((uint32_t*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
-}
-__device__ __forceinline__ uint4 ld_dev128(const uint16_t* p) {
-    const uint64_t x = ld_dev64(p), y = ld_dev64(p + 4);
-    return uint4{(uint32_t)x, (uint32_t)(x >> 32), (uint32_t)y, (uint32_t)(y >> 32)};
-}
-
-template <int KS, int NT, bool BF16>
-__global__ __launch_bounds__(kCoThreads) void md_block(BlockArgs c, const bool vec) {
-    const MarkovArgs& a = c.a;
-    constexpr int kNch = 4 * KS, kRank = 32 * KS;
-    __shared__ __align__(16) uint16_t se[NT * kBkRows * kRank];
-    __shared__ float2 sst[kCoTiles][kCoWaves][kBkRows];
-    __shared__ RowInfo sinfo[kBkRows];
-    __shared__ float smass[kCoWaves][kTileV];
-    __shared__ int stok[kBkRows], sdraw[kBkRows], ndraw;
-    __shared__ f32x4 spart[NT == 2 ? kCoWaves - 1 : 1][3][DSPARK_WAVE];
-    const int R = a.R, nrt = (R + 15) >> 4, Gt = gridDim.x, b0 = blockIdx.x;
-    const int nt = b0 < c.ntiles ? min(kCoTiles, (c.ntiles - b0 + Gt - 1) / Gt) : 0;
-    auto tile_of = [&](int i) { return b0 + i * Gt; };
-    constexpr float kLog2e = 1.4426950408889634f;
-    const float scale2 = a.inv_temp * kLog2e;
-    unsigned bar = 0;
-
-    for (int k = 1; k <= a.K; ++k) {
-        // opaque to the compiler, which would otherwise keep every address of the
-        // loop body in registers across the positions, and spill them
-        int tid = threadIdx.x;
-        asm volatile("" : "+v"(tid));
-        const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-        const int lr = lane & 15, lq = lane >> 4;
-        bf16x8 af[KS];
-        float ub[kBkRT][4];
-        auto load_tile = [&](int i, int k) {  // W2t rows and base logits of position k
-            const int vt = tile_of(i) * kTileV + 16 * wave;
-            const uint16_t* src = a.W2t + (int64_t)min(vt + lr, a.V - 1) * kRank + 8 * lq;
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) af[ks] = *(const bf16x8*)(src + 32 * ks);
-#pragma unroll
-            for (int rt = 0; rt < kBkRT; ++rt) {
-                const int64_t row = ((int64_t)min(16 * rt + lr, R - 1) * a.K + (k - 1)) * a.ld;
-                const int vb = vt + 4 * lq;
-                if (vec) {
-                    const int64_t at = row + min(vb, a.V - 4);
-                    if (BF16) {
-                        const uint2 w = *(const uint2*)((const uint16_t*)a.base + at);
-                        ub[rt][0] = __uint_as_float(w.x << 16), ub[rt][1] = __uint_as_float(w.x & 0xffff0000u);
-                        ub[rt][2] = __uint_as_float(w.y << 16), ub[rt][3] = __uint_as_float(w.y & 0xffff0000u);
-                    } else {
-                        const float4 w = *(const float4*)((const float*)a.base + at);
-                        ub[rt][0] = w.x, ub[rt][1] = w.y, ub[rt][2] = w.z, ub[rt][3] = w.w;
-                    }
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int64_t at = row + min(vb + e, a.V - 1);
-                        ub[rt][e] = BF16 ? bf16_to_f32(((const uint16_t*)a.base)[at]) : ((const float*)a.base)[at];
-                    }
-                }
-            }
-        };
-        if (nt > 0) load_tile(0, k);
-        if (k > 1) grid_wait(c.sync, bar);
-        // x_{k-1} of every request (-1: its anchor was no token)
-        if (tid < R) {
-            const int x = k == 1 ? a.anchor[tid] : (int)(uint32_t)ld_dev64(c.tok + (k & 1) * kBkRows + tid);
-            stok[tid] = x >= 0 && x < a.V ? x : -1;
-        }
-        if (tid == 0) ndraw = 0;
-        __syncthreads();
-        if constexpr (NT == 2) {
-            // ---- S: as rnn_state, the steps over eight waves
-            constexpr int rank = kRank;
-            const int nz = 2 * rank + a.d;
-            const float* s_prev = k & 1 ? c.S[0] : c.S[1];
-            const uint16_t* T_prev = k & 1 ? c.T[0] : c.T[1];
-            float* s_next = k & 1 ? c.S[1] : c.S[0];
-            uint16_t* T_next = k & 1 ? c.T[1] : c.T[0];
-            const int nj = rank / 16, ks_s = 3 * rank / 32, nst = ks_s + rank / 32;
-            constexpr int kPer = (4 * KS + kCoWaves - 1) / kCoWaves;  // steps per wave
-            for (int blk = b0; blk < nj * nrt; blk += Gt) {
-                const int j0 = blk % nj * 16, m0 = blk / nj * 16;
-                const int ra = min(m0 + lr, R - 1), j = j0 + lr;
-                const int st0 = (k > 1 ? 0 : ks_s) + wave;
-                float hpv[4][3], spv[4];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    const int rc = min(m0 + 4 * lq + e, R - 1);
-                    const float* hp = c.Hp + ((int64_t)wave * R * a.K + (int64_t)rc * a.K + (k - 1)) * (3 * rank) + j;
-#pragma unroll
-                    for (int q = 0; q < 3; ++q) hpv[e][q] = wave < c.hpz ? hp[q * rank] : 0.0f;
-                    spv[e] = wave == 0 && k > 1 ? ld_dev32(s_prev + (int64_t)rc * rank + j) : 0.0f;
-                }
-                uint4 av[kPer];
-                bf16x8 bv[kPer][3];
-#pragma unroll
-                for (int u = 0; u < kPer; ++u) {
-                    const int kk = 32 * min(st0 + kCoWaves * u, nst - 1) + 8 * lq;  // past the end: unused
-                    const bool state = kk < 3 * rank;                              // uniform over the wave
-                    av[u] = state ? ld_dev128(T_prev + (int64_t)ra * 3 * rank + kk)
-                                  : *(const uint4*)(a.W1 + (int64_t)max(stok[ra], 0) * rank + (kk - 3 * rank));
-                    const int col = state ? kk % rank : kk - 2 * rank;
-#pragma unroll
-                    for (int q = 0; q < 3; ++q) bv[u][q] = *(const bf16x8*)(a.Wrnn + (int64_t)(q * rank + j0 + lr) * nz + col);
-                }
-                f32x4 acc[3];
-#pragma unroll
-                for (int q = 0; q < 3; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int u = 0; u < kPer; ++u)
-                    if (st0 + kCoWaves * u < nst) {
-#pragma unroll
-                        for (int q = 0; q < 3; ++q)
-                            acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av[u]), bv[u][q],
-                                                                           acc[q], 0, 0, 0);
-                    }
-#pragma unroll
-                for (int q = 0; q < 3; ++q)
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) acc[q][e] += hpv[e][q];
-                if (wave > 0) {
-#pragma unroll
-                    for (int q = 0; q < 3; ++q) spart[wave - 1][q][lane] = acc[q];
-                }
-                __syncthreads();
-                if (wave == 0) {
-#pragma unroll
-                    for (int w = 0; w < kCoWaves - 1; ++w)
-#pragma unroll
-                        for (int q = 0; q < 3; ++q) acc[q] += spart[w][q][lane];
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        const int r = m0 + 4 * lq + e;
-                        if (r >= R) continue;
-                        const float g = 1.0f / (1.0f + expf(-acc[0][e]));
-                        const float sn = g * spv[e] + (1.0f - g) * tanhf(acc[1][e]);
-                        const float o = tanhf(acc[2][e]);
-                        st_dev32(s_next + (int64_t)r * rank + j, sn);
-                        uint16_t t3[3], t2[2];
-                        split3(sn, t3, 1);
-                        split2(o, t2, 1);
-#pragma unroll
-                        for (int q = 0; q < 3; ++q) st_dev16(T_next + (int64_t)r * 3 * rank + q * rank + j, t3[q]);
-#pragma unroll
-                        for (int q = 0; q < 2; ++q) st_dev16(c.E2 + (int64_t)r * 2 * rank + q * rank + j, t2[q]);
-                    }
-                }
-                __syncthreads();  // the partial sums are read
-            }
-            grid_barrier(c.sync, ++bar);
-        }
-
-        // ---- A: the B operand into LDS (rows past R are zero), products, statistics
-        if (nt > 0) {
-            constexpr int kECopy = (NT * kBkRows * kNch + kCoThreads - 1) / kCoThreads;
-#pragma unroll
-            for (int j = 0; j < kECopy; ++j) {
-                const int idx = tid + j * kCoThreads, t = idx / (NT * kNch), q = idx % (NT * kNch);
-                if (idx >= NT * kBkRows * kNch) break;
-                uint4 v = uint4{0u, 0u, 0u, 0u};
-                if (t < R)
-                    v = NT == 2 ? ld_dev128(c.E2 + (int64_t)t * 2 * kRank + 8 * q)
-                                : *(const uint4*)(a.W1 + (int64_t)max(stok[t], 0) * kRank + 8 * q);
-                *(uint4*)(se + ((q / kNch * kBkRows + t) * kNch + eslot(t, q % kNch, kNch)) * 8) = v;
-            }
-        }
-        lds_barrier();
-        f32x4 z[kCoTiles][kBkRT];
-#pragma unroll
-        for (int i = 0; i < kCoTiles; ++i) {
-            if (i >= nt) continue;
-            if (i > 0) load_tile(i, k);
-#pragma unroll
-            for (int rt = 0; rt < kBkRT; ++rt) {
-                z[i][rt] = f32x4{0.f, 0.f, 0.f, 0.f};
-                if (rt >= nrt) continue;
-                const int t = 16 * rt + lr;
-#pragma unroll
-                for (int n = 0; n < NT; ++n)
-#pragma unroll
-                    for (int ks = 0; ks < KS; ++ks)
-                        z[i][rt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-                            af[ks], *(const bf16x8*)(se + ((n * kBkRows + t) * kNch + eslot(t, 4 * ks + lq, kNch)) * 8),
-                            z[i][rt], 0, 0, 0);
-                const int vb = tile_of(i) * kTileV + 16 * wave + 4 * lq;
-                float m = -__builtin_huge_valf();
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    z[i][rt][e] = vb + e < a.V && t < R ? scale2 * (ub[rt][e] + z[i][rt][e]) : -__builtin_huge_valf();
-                    m = fmaxf(m, z[i][rt][e]);
-                }
-                m = quad_max(m);
-                float s = 0.0f;
-                if (m > -__builtin_huge_valf()) {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) s += __builtin_amdgcn_exp2f(z[i][rt][e] - m);
-                }
-                s = quad_sum(s);
-                if (lq == 0) sst[i][wave][t] = float2{m, s};
-            }
-        }
-        lds_barrier();
-        {
-            const int i = tid / kBkRows, r = tid % kBkRows;  // the first 128 threads: every (tile, request)
-            if (i < nt && r < R) {
-                float M = -__builtin_huge_valf();
-#pragma unroll
-                for (int w = 0; w < kCoWaves; ++w) M = fmaxf(M, sst[i][w][r].x);
-                float S = 0.0f;
-                if (M > -__builtin_huge_valf()) {
-#pragma unroll
-                    for (int w = 0; w < kCoWaves; ++w)
-                        if (sst[i][w][r].x > -__builtin_huge_valf()) S += sst[i][w][r].y * exp2f(sst[i][w][r].x - M);
-                }
-                st_f2<true>(c.stats + (int64_t)r * c.ntiles + tile_of(i), float2{M, S});
-            }
-        }
-        grid_barrier(c.sync, ++bar);
-
-        // ---- B: row maximum, total and draw tile of every request, one wave each
-        if (nt > 0)
-            for (int r = wave; r < R; r += kCoWaves) {
-                if (c.ntiles <= DSPARK_WAVE) row_stats<1, true, false>(a, c.stats, sinfo, c.ntiles, k, r, lane);
-                else if (c.ntiles <= 4 * DSPARK_WAVE) row_stats<4, true, false>(a, c.stats, sinfo, c.ntiles, k, r, lane);
-                else if (c.ntiles <= 8 * DSPARK_WAVE) row_stats<8, true, false>(a, c.stats, sinfo, c.ntiles, k, r, lane);
-                else row_stats<16, true, false>(a, c.stats, sinfo, c.ntiles, k, r, lane);
-            }
-        __syncthreads();
-        // ---- C: the draws of the tiles owned here
-        if (nt > 0 && tid < R) {
-            const int d = sinfo[tid].tile - b0;
-            if (d >= 0 && d % Gt == 0 && d / Gt < nt) sdraw[atomicAdd(&ndraw, 1)] = tid;
-        }
-        __syncthreads();
-        const int nd = ndraw;
-        for (int j0 = 0; j0 < nd; j0 += kCoWaves) {
-            for (int j = j0; j < min(nd, j0 + kCoWaves); ++j) {
-                const int rl = sdraw[j];
-                const int ti = (sinfo[rl].tile - b0) / Gt;
-                const float M = sinfo[rl].M;
-#pragma unroll
-                for (int i = 0; i < kCoTiles; ++i)
-#pragma unroll
-                    for (int rt = 0; rt < kBkRT; ++rt)
-                        if (i == ti && 16 * rt + lr == rl) {
-#pragma unroll
-                            for (int e = 0; e < 4; ++e)
-                                smass[j - j0][16 * wave + 4 * lq + e] = __builtin_amdgcn_exp2f(z[i][rt][e] - M);
-                        }
-            }
-            lds_barrier();
-            if (j0 + wave < nd) {  // wave w makes draw j0 + w
-                const int rl = sdraw[j0 + wave];
-                const RowInfo ri = sinfo[rl];
-                const double m0 = smass[wave][2 * lane], m1 = smass[wave][2 * lane + 1];
-                double incl = m0 + m1;
-#pragma unroll
-                for (int o = 1; o < DSPARK_WAVE; o <<= 1) {
-                    const double t = __shfl_up(incl, o, DSPARK_WAVE);
-                    if (lane >= o) incl += t;
-                }
-                const double before = incl - (m0 + m1);  // mass before entry 2 * lane
-                // first entry whose running mass passes thr (zero masses are never drawn)
-                const unsigned long long h0 = __ballot(before + m0 > ri.thr && m0 > 0.0);
-                const unsigned long long h1 = __ballot(incl > ri.thr && m1 > 0.0);
-                // rounding: the tile's last entry with mass
-                const unsigned long long l0 = __ballot(m0 > 0.0), l1 = __ballot(m1 > 0.0);
-                int at;
-                if (h0 | h1) {
-                    const int f0 = h0 ? 2 * (int)__builtin_ctzll(h0) : kTileV;
-                    const int f1 = h1 ? 2 * (int)__builtin_ctzll(h1) + 1 : kTileV;
-                    at = min(f0, f1);
-                } else {
-                    const int e0 = l0 ? 2 * (63 - (int)__builtin_clzll(l0)) : 0;
-                    const int e1 = l1 ? 2 * (63 - (int)__builtin_clzll(l1)) + 1 : 0;
-                    at = max(e0, e1);
-                }
-                const int x = stok[rl] >= 0 ? ri.tile * kTileV + at : -1;
-                if (lane == 0) {
-                    a.draft_tok[(int64_t)rl * a.K + (k - 1)] = x;
-                    st_dev64(c.tok + ((k + 1) & 1) * kBkRows + rl, (uint64_t)(uint32_t)x);
-                }
-                if (k < a.K) {
-                    const float sc = embed_dot(a, a.W1 + (int64_t)max(x, 0) * a.rank, lane) +
-                                     (c.sh ? c.sh[(int64_t)rl * a.K + k] : 0.0f);
-                    if (lane == 0)
-                        a.conf[(int64_t)rl * a.K + k] = x >= 0 ? confidence(a, sc, k + 1) : __builtin_nanf("");
-                }
-            }
-            if (j0 + kCoWaves < nd) lds_barrier();
-        }
-        if (k < a.K) grid_arrive(c.sync, ++bar);
-#pragma unroll
-        for (int rt = 0; rt < kBkRT; ++rt) {
-            const int r = 16 * rt + lr;
-            if (nt == 0 || r >= R) continue;
-            const float M = sinfo[r].M, inv = 1.0f / sinfo[r].S;
-            float* out = a.draft_p + ((int64_t)r * a.K + (k - 1)) * a.V;
-#pragma unroll
-            for (int i = 0; i < kCoTiles; ++i) {
-                if (i >= nt) continue;
-                const int vb = tile_of(i) * kTileV + 16 * wave + 4 * lq;
-                float4 p;
-                p.x = __builtin_amdgcn_exp2f(z[i][rt][0] - M) * inv;
-                p.y = __builtin_amdgcn_exp2f(z[i][rt][1] - M) * inv;
-                p.z = __builtin_amdgcn_exp2f(z[i][rt][2] - M) * inv;
-                p.w = __builtin_amdgcn_exp2f(z[i][rt][3] - M) * inv;
-                if (vec) {
-                    if (vb < a.V) *(float4*)(out + vb) = p;
-                } else {
-                    if (vb < a.V) out[vb] = p.x;
-                    if (vb + 1 < a.V) out[vb + 1] = p.y;
-                    if (vb + 2 < a.V) out[vb + 2] = p.z;
-                    if (vb + 3 < a.V) out[vb + 3] = p.w;
-                }
-            }
-        }
-    }
-}
-
-// Grid of md_block, or 0 where it does not apply: up to 32 requests, kBkStats tile
-// statistics and four tiles a workgroup.  A workgroup takes a CU's registers, so the
-// grid is at most 64 workgroups: blocks drafted on several streams at once (a process
-// has four hardware queues) are then all resident together, and none waits for a
-// workgroup that another one's waiting workgroups keep out.  Where the block would
-// otherwise run as md_coop (bf16 base logits, V % 4 == 0), which takes the whole part
-// by itself, the grid is up to 256.  64 workgroups lose where they have to take
-// several tiles or rows in turn (fp32, 32 requests: 537 us with 32768 entries and 322
-// with 3000, against 305 and 245 in three launches per position), so there it is at
-// most 64 tiles and a request per wave.
-// The RNN head takes it only in md_coop's place: its recurrence on 64 workgroups costs
-// more than the launches (8 requests x 8000, d = 4096: 403 against 336 us; 1 x 7360,
-// d = 0: 275 against 242).
-constexpr int kBkGrid = 64, kBkGridAlone = 256;
-template <int KS, int NT, bool BF16>
-int block_grid(const MarkovArgs& a, int ntiles, bool alone) {
-    const int most = alone ? kBkGridAlone : kBkGrid;
-    if (a.R > (alone ? kBkRows : kCoWaves) || ntiles > (alone ? kCoTiles * most : most) || (int64_t)a.R * ntiles > kBkStats) return 0;
-    constexpr int kMaxDevices = 64;
-    static int cache[kMaxDevices];  // workgroups held at once; 0: not yet asked, -1: none
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return 0;
-    if (cache[dev] == 0) {
-        int cus = 0, nb = 0;
-        const bool ok = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
-                        hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, md_block<KS, NT, BF16>, kCoThreads, 0) == hipSuccess;
-        cache[dev] = ok && nb * cus > 0 ? nb * cus : -1;
-    }
-    int G = ceil_div(ntiles, ceil_div(ntiles, most));
-    if (NT == 2) G = std::max(G, std::min(most, a.rank / 16 * ceil_div(a.R, 16)));  // the recurrence's blocks
-    return (alone ? G : 4 * G) <= cache[dev] ? G : 0;
-}
-
-template <int KS, int NT>
-bool launch_block(const BlockArgs& c, bool vec, hipStream_t s) {
-    const bool alone = coop_applies<KS, NT>(c.a, c.ntiles, vec);
-    if (c.a.base_bf16) {
-        if (NT == 2 && !alone) return false;
-        const int G = block_grid<KS, NT, true>(c.a, c.ntiles, alone);
-        if (G == 0) return false;
-        hipLaunchKernelGGL((md_block<KS, NT, true>), dim3(G), dim3(kCoThreads), 0, s, c, vec);
-    } else if constexpr (NT == 1) {
-        const int G = block_grid<KS, NT, false>(c.a, c.ntiles, alone);
-        if (G == 0) return false;
-        hipLaunchKernelGGL((md_block<KS, NT, false>), dim3(G), dim3(kCoThreads), 0, s, c, vec);
-    } else {
-        return false;
-    }
-    return true;
-}
-
 template <int KS>
 hipError_t launch_rnn_ks(const MarkovArgs& a, uint16_t* Ee, uint16_t* E2, float* S0, float* S1,
                          uint16_t* T0, uint16_t* T1, float* Hp, float2* stats, RowInfo* info,
-                         float* sh, unsigned* sync, uint64_t* tok, int ntiles, bool vec, hipStream_t s) {
+                         float* sh, unsigned* sync, int ntiles, bool vec, hipStream_t s) {
     const int64_t rows = (int64_t)a.R * a.K;
     int hpz = 0;  // parts of the backbone projection
     if (a.d > 0) {
@@ -1685,27 +1261,8 @@ hipError_t launch_rnn_ks(const MarkovArgs& a, uint16_t* Ee, uint16_t* E2, float*
     const float* shp = a.d > 0 ? sh : nullptr;
     const float* hpp = a.d > 0 ? Hp : nullptr;
     hipLaunchKernelGGL(md_first, dim3(ceil_div(a.R, kWaves)), dim3(kThreads), 0, s, a, shp, Ee, sync);
-    BlockArgs c;
-    c.a = a;
-    c.stats = stats;
-    c.sh = shp;
-    c.tok = tok;
-    c.sync = sync;
-    c.ntiles = ntiles;
-    c.Hp = hpp;
-    c.hpz = hpz;
-    c.S[0] = S0;
-    c.S[1] = S1;
-    c.T[0] = T0;
-    c.T[1] = T1;
-    c.E2 = E2;
-    // a small batch's positions in one launch; else the vocabulary product with the
-    // output's two terms: md_coop where it applies, else md_tile and md_norm
-    if (launch_block<KS, 2>(c, vec, s)) {
-        hipLaunchKernelGGL(md_check, dim3((unsigned)ceil_div((int)rows, kThreads)), dim3(kThreads), 0, s, a,
-                           (const unsigned*)sync);
-        return hipGetLastError();
-    }
+    // the vocabulary product with the output's two terms: md_coop where it applies, else
+    // md_tile and md_norm
     const bool coop = coop_applies<KS, 2>(a, ntiles, vec);
     unsigned launch = 0;
     for (int k = 1; k <= a.K; ++k) {
@@ -1728,25 +1285,13 @@ hipError_t launch_rnn_ks(const MarkovArgs& a, uint16_t* Ee, uint16_t* E2, float*
 
 template <int KS>
 hipError_t launch_ks(const MarkovArgs& a, uint16_t* E0, uint16_t* E1, float2* stats, RowInfo* info,
-                     float* sh, unsigned* sync, uint64_t* tok, int ntiles, bool vec, hipStream_t s) {
+                     float* sh, unsigned* sync, int ntiles, bool vec, hipStream_t s) {
     const int64_t rows = (int64_t)a.R * a.K;
     if (a.d > 0) hipLaunchKernelGGL(md_hidden, dim3((unsigned)ceil_div((int)rows, kWaves)), dim3(kThreads), 0, s, a, sh);
     const float* shp = a.d > 0 ? sh : nullptr;
     hipLaunchKernelGGL(md_first, dim3(ceil_div(a.R, kWaves)), dim3(kThreads), 0, s, a, shp, E0, sync);
-    BlockArgs c = {};
-    c.a = a;
-    c.stats = stats;
-    c.sh = shp;
-    c.tok = tok;
-    c.sync = sync;
-    c.ntiles = ntiles;
-    // a small batch's positions in one launch; else one md_coop launch per position
-    // and group of 128 requests where it applies, two launches per position otherwise
-    if (launch_block<KS, 1>(c, vec, s)) {
-        hipLaunchKernelGGL(md_check, dim3((unsigned)ceil_div((int)rows, kThreads)), dim3(kThreads), 0, s, a,
-                           (const unsigned*)sync);
-        return hipGetLastError();
-    }
+    // one md_coop launch per position and group of 128 requests where it applies, two
+    // launches per position otherwise
     const bool coop = coop_applies<KS, 1>(a, ntiles, vec);
     unsigned launch = 0;
     for (int k = 1; k <= a.K; ++k) {
@@ -1776,7 +1321,7 @@ WsLayout ws_layout(int R, int K, int V, int rank) {
     l.stats = align256((size_t)R * ntiles * sizeof(float2));
     l.info = align256((size_t)R * sizeof(mkd::RowInfo));
     l.sh = align256((size_t)R * K * sizeof(float));
-    l.sync = align256(mkd::kSyncWords * sizeof(unsigned)) + align256(mkd::kTokBytes);  // barrier words, tokens
+    l.sync = align256(mkd::kSyncWords * sizeof(unsigned));  // md_coop's barrier words
     l.total = 2 * l.e + l.stats + l.info + l.sh + l.sync;
     return l;
 }
@@ -1802,7 +1347,7 @@ RnnLayout rnn_layout(int R, int K, int V, int rank) {
     l.stats = align256((size_t)R * ntiles * sizeof(float2));
     l.info = align256((size_t)R * sizeof(mkd::RowInfo));
     l.sh = align256((size_t)R * K * sizeof(float));
-    l.sync = align256(mkd::kSyncWords * sizeof(unsigned)) + align256(mkd::kTokBytes);
+    l.sync = align256(mkd::kSyncWords * sizeof(unsigned));
     l.total = l.ee + l.e2 + 2 * l.st + 2 * l.st3 + l.hp + l.stats + l.info + l.sh + l.sync;
     return l;
 }
@@ -1825,19 +1370,20 @@ hipError_t launch_rnn(const MarkovArgs& a, void* ws, hipStream_t s) {
     mkd::RowInfo* info = (mkd::RowInfo*)p;       p += l.info;
     float* sh = (float*)p;                       p += l.sh;
     unsigned* sync = (unsigned*)p;
-    uint64_t* tok = (uint64_t*)(p + align256(mkd::kSyncWords * sizeof(unsigned)));
     const size_t eb = a.base_bf16 ? 2 : 4;
     const bool vec = a.V % 4 == 0 && a.ld % 4 == 0 && ((uintptr_t)a.base % (4 * eb)) == 0 &&
                      ((uintptr_t)a.draft_p % 16) == 0;
     switch (a.rank) {
-        case 32: return mkd::launch_rnn_ks<1>(a, Ee, E2, S0, S1, T0, T1, Hp, stats, info, sh, sync, tok, ntiles, vec, s);
-        case 64: return mkd::launch_rnn_ks<2>(a, Ee, E2, S0, S1, T0, T1, Hp, stats, info, sh, sync, tok, ntiles, vec, s);
-        case 128: return mkd::launch_rnn_ks<4>(a, Ee, E2, S0, S1, T0, T1, Hp, stats, info, sh, sync, tok, ntiles, vec, s);
-        default: return mkd::launch_rnn_ks<8>(a, Ee, E2, S0, S1, T0, T1, Hp, stats, info, sh, sync, tok, ntiles, vec, s);
+        case 32: return mkd::launch_rnn_ks<1>(a, Ee, E2, S0, S1, T0, T1, Hp, stats, info, sh, sync, ntiles, vec, s);
+        case 64: return mkd::launch_rnn_ks<2>(a, Ee, E2, S0, S1, T0, T1, Hp, stats, info, sh, sync, ntiles, vec, s);
+        case 128: return mkd::launch_rnn_ks<4>(a, Ee, E2, S0, S1, T0, T1, Hp, stats, info, sh, sync, ntiles, vec, s);
+        default: return mkd::launch_rnn_ks<8>(a, Ee, E2, S0, S1, T0, T1, Hp, stats, info, sh, sync, ntiles, vec, s);
     }
 }
 
 bool markov_rank_supported(int rank) { return rank == 32 || rank == 64 || rank == 128 || rank == 256; }
+
+int markov_coop_grid(int R, int V) { return mkd::coop_grid(R, mkd::ceil_div(V, mkd::kTileV), V); }
 
 int markov_max_vocab() { return DSPARK_WAVE * mkd::kStatsMaxPer * mkd::kTileV; }
 
@@ -1851,15 +1397,14 @@ hipError_t launch_markov(const MarkovArgs& a, void* ws, hipStream_t s) {
     mkd::RowInfo* info = (mkd::RowInfo*)(p + 2 * l.e + l.stats);
     float* sh = (float*)(p + 2 * l.e + l.stats + l.info);
     unsigned* sync = (unsigned*)(p + 2 * l.e + l.stats + l.info + l.sh);
-    uint64_t* tok = (uint64_t*)(p + 2 * l.e + l.stats + l.info + l.sh + align256(mkd::kSyncWords * sizeof(unsigned)));
     const size_t eb = a.base_bf16 ? 2 : 4;
     const bool vec = a.V % 4 == 0 && a.ld % 4 == 0 && ((uintptr_t)a.base % (4 * eb)) == 0 &&
                      ((uintptr_t)a.draft_p % 16) == 0;
     switch (a.rank) {
-        case 32: return mkd::launch_ks<1>(a, E0, E1, stats, info, sh, sync, tok, ntiles, vec, s);
-        case 64: return mkd::launch_ks<2>(a, E0, E1, stats, info, sh, sync, tok, ntiles, vec, s);
-        case 128: return mkd::launch_ks<4>(a, E0, E1, stats, info, sh, sync, tok, ntiles, vec, s);
-        default: return mkd::launch_ks<8>(a, E0, E1, stats, info, sh, sync, tok, ntiles, vec, s);
+        case 32: return mkd::launch_ks<1>(a, E0, E1, stats, info, sh, sync, ntiles, vec, s);
+        case 64: return mkd::launch_ks<2>(a, E0, E1, stats, info, sh, sync, ntiles, vec, s);
+        case 128: return mkd::launch_ks<4>(a, E0, E1, stats, info, sh, sync, ntiles, vec, s);
+        default: return mkd::launch_ks<8>(a, E0, E1, stats, info, sh, sync, ntiles, vec, s);
     }
 }
 

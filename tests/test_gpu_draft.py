@@ -90,13 +90,21 @@ def test_draft_other_ranks(rank):
 
 @pytest.mark.parametrize("R,K", [(150, 2), (300, 3)])
 def test_draft_several_request_chunks(R, K):
-    # more requests than one cooperative launch takes: groups of 128 (the last
-    # partial), one launch per group and position, their grid barriers
-    # numbered across the block (three groups x three positions: nine launches)
+    # more requests than one 32-request chunk of a tile's workgroup (the last partial)
     w = synth.scaled(synth.WORKLOADS["serving"], R=R, K=K, V=1024)
     case = guard.draft_case(w, 4, rank=64, d=8)
     tok, p, conf = _run_gpu(w, case, 64, 8)
     _compare(w, case, tok, p, conf, f"{R} requests")
+
+
+def test_draft_several_cooperative_groups():
+    # more requests than one cooperative launch takes (and enough logits for such launches):
+    # groups of 128, the last partial, one launch per group and position, their grid
+    # barriers numbered across the block (three groups x three positions: nine launches)
+    w = synth.scaled(synth.WORKLOADS["serving"], R=300, K=3, V=80000)
+    case = guard.draft_case(w, 4, rank=64, d=8, reqs=[0, 127, 128, 255, 256, 299])
+    tok, p, conf = _run_gpu(w, case, 64, 8)
+    _compare(w, case, tok, p, conf, "300 requests, cooperative")
 
 
 def test_draft_wide_vocabulary():
@@ -109,8 +117,8 @@ def test_draft_wide_vocabulary():
 
 
 def test_draft_wide_aligned_vocabulary():
-    # bf16 base logits and V % 4 == 0 but 1094 tiles: more than one
-    # cooperative grid holds, so each position takes the three-launch form
+    # bf16 base logits and V % 4 == 0 but 1094 tiles: more than a
+    # cooperative launch takes, so each position takes the two-launch form
     w = synth.scaled(synth.WORKLOADS["serving"], R=5, K=2, V=140000)
     case = guard.draft_case(w, 10, rank=128, d=16)
     tok, p, conf = _run_gpu(w, case, 128, 16)
@@ -158,9 +166,8 @@ def test_draft_degenerate_shapes(R, K, V):
         assert (tok == 0).all().item() and torch.equal(p, torch.ones_like(p))
 
 
-# the lines between the one-launch block and the launches per position: 8 / 9 requests and
-# 64 / 65 tiles (8192 / 8193 entries) where the vector path of bf16 logits does not apply,
-# 32 / 33 requests where it does; a tile, a ragged second one, and several per workgroup
+# small batches: eight / nine and 32 / 33 requests, a tile, a ragged second one, 64 and 65 of
+# them, of every way to read the base logits
 @pytest.mark.parametrize("R,K,V,dt", [
     (8, 3, 8192, "f32"), (9, 3, 8192, "f32"), (8, 3, 8193, "bf16"), (2, 3, 8189, "bf16"), (1, 16, 128, "bf16"),
     (32, 3, 1000, "bf16"), (33, 3, 1000, "bf16"), (17, 3, 2052, "bf16"), (3, 4, 65540, "bf16"), (1, 2, 5, "f32"),
@@ -172,10 +179,11 @@ def test_draft_block_edges(R, K, V, dt):
     _compare(w, case, tok, p, conf, f"edges {dt}")
 
 
-def test_draft_block_on_four_streams():
-    # four blocks at once, on streams of their own: each grid fits beside the
-    # others, so all finish and agree with a block drafted alone
-    w = synth.scaled(synth.WORKLOADS["serving"], R=8, K=16, V=8192, logit_dtype="f32")
+@pytest.mark.parametrize("V,dt", [(8192, "f32"), (16384, "bf16"), (32768, "bf16")])
+def test_draft_block_on_four_streams(V, dt):
+    # four blocks at once, on streams of their own: no small batch waits for workgroups
+    # that another one keeps out, so all finish and agree with a block drafted alone
+    w = synth.scaled(synth.WORKLOADS["serving"], R=8, K=16, V=V, logit_dtype=dt)
     case = guard.draft_case(w, 5, rank=64, d=8)
     inp = case.inp
     args = [to_dev(x) for x in (inp.anchor, inp.base, inp.W1, inp.W2t, inp.w_conf, inp.u)]

@@ -96,14 +96,21 @@ def test_rnn_draft_other_ranks(rank):
 
 @pytest.mark.parametrize("R,K", [(150, 2), (300, 3)])
 def test_rnn_draft_several_request_blocks(R, K):
-    # 150 requests: ten state blocks (the last one partial), two groups of the
-    # cooperative vocabulary product (128 + 22), 150 * 2 = 300 hidden rows (a
-    # partial 64-row block of the projection); 300 requests: three groups over
-    # three positions (nine launches, their barriers numbered across the block)
+    # 150 requests: ten state blocks (the last one partial), 150 * 2 = 300 hidden rows (a
+    # partial 64-row block of the projection)
     w = synth.scaled(synth.WORKLOADS["serving"], R=R, K=K, V=1024)
     case = guard.draft_case(w, 4, rank=64, d=8, head="rnn")
     tok, p, conf = _run_gpu(w, case, 8)
     _compare(w, case, tok, p, conf, f"{R} requests")
+
+
+def test_rnn_draft_several_cooperative_groups():
+    # enough logits for the cooperative vocabulary product: three groups over three
+    # positions (nine launches, their barriers numbered across the block)
+    w = synth.scaled(synth.WORKLOADS["serving"], R=300, K=3, V=80000)
+    case = guard.draft_case(w, 4, rank=64, d=8, reqs=[0, 127, 128, 255, 256, 299], head="rnn")
+    tok, p, conf = _run_gpu(w, case, 8)
+    _compare(w, case, tok, p, conf, "300 requests, cooperative")
 
 
 def test_rnn_draft_long_block():
@@ -162,8 +169,8 @@ def test_rnn_draft_degenerate_shapes(R, K, V):
         assert (tok == 0).all().item() and torch.equal(p, torch.ones_like(p))
 
 
-# one launch for the block (up to 32 requests of bf16 logits, V % 4 == 0) against
-# launches per position; the backbone projection in one part (d = 0 has none), a few and eight
+# small batches of either base type; the backbone projection in one part (d = 0 has none), a
+# few and eight
 @pytest.mark.parametrize("R,K,V,rank,d,dt", [
     (8, 3, 8192, 64, 256, "f32"), (9, 3, 8192, 64, 264, "f32"), (32, 3, 1000, 64, 2048, "bf16"),
     (33, 3, 1000, 32, 520, "bf16"), (17, 4, 2052, 256, 1024, "bf16"), (1, 5, 129, 32, 0, "f32"), (3, 3, 9000, 256, 8, "bf16"),
