@@ -1029,83 +1029,114 @@ bool coop_applies(const MarkovArgs& a, int ntiles, bool vec) {
 // The backbone part of the RNN head's projection (eq. rnn), once for every
 // (request, position) since it does not depend on the drawn tokens:
 // Hp[row, i] = sum_{j < d} Wrnn[i, 2 rank + j] h[row, j], row = r K + k - 1,
-// i < 3 rank.  v_mfma_f32_16x16x32_bf16; a workgroup computes 64 rows x 128
-// outputs.  Wave w owns rows 16 w .. 16 w + 15 and reads its hidden-state
-// fragments straight from memory, one step ahead; the 128 weight rows of each
-// 32-input step are staged once per workgroup in an LDS double buffer (row
-// pitch 80 bytes) and shared by the four waves.  d % 8 == 0, so a lane's 8
-// inputs are either all inside the row or all past its end.
-constexpr int kHpRows = 64, kHpCols = 128, kHpNt = kHpCols / 16, kHpPitch = 40;
-// The inputs are cut into gridDim.z parts, whose partial products (Hp + part * rows *
-// 3 rank) the readers add in order: a step is a load, a barrier and eight products,
-// so one workgroup for all 4096 inputs is a chain of 128 of them whatever the
-// number of rows (81 us for 512 rows and for 2048).  Parts: 18 us for 512 rows.
-__global__ __launch_bounds__(kThreads) void rnn_hproj(MarkovArgs a, float* Hp, int per) {
-    __shared__ __align__(16) uint16_t sb[2][kHpCols * kHpPitch];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+// i < 3 rank.  v_mfma_f32_16x16x32_bf16; a workgroup computes 16 RW rows x 16 NT
+// outputs.  A group of RW waves takes a contiguous run of the 32-input steps: wave w
+// owns rows 16 w .. 16 w + 15 and reads its hidden-state fragments straight from
+// memory; the weight rows of a step are staged once per group in an LDS double buffer
+// (row pitch 80 bytes) and shared by its waves.  d % 8 == 0, so a lane's 8 inputs are
+// either all inside the row or all past its end.
+// Bound by the chain of steps (a load, a barrier, NT products) and by what a CU loads:
+// one chain over 4096 inputs takes 81 us for 512 rows and for 2048.  So S groups share
+// the inputs, their sums added in group order through LDS, and small batches take small
+// tiles, for more workgroups.  Us per RNN block (K = 16, rank 256, d = 4096, 2000
+// entries), <2, 4, 8> / <2, 4, 4> / <4, 8, 2>: 512 rows 353 / 354 / 374, 1024 415 / 403 /
+// 415, 2048 523 / 505 / 502, 8192 1355 / 1260 / 1179 (one group: 398, 440, 528, 1168).
+constexpr int kHpPitch = 40;
+template <int RW, int NT, int S>
+__global__ __launch_bounds__(S * RW * DSPARK_WAVE) void rnn_hproj(MarkovArgs a, float* Hp) {
+    constexpr int kRows = 16 * RW, kCols = 16 * NT, kThr = RW * DSPARK_WAVE, kPieces = kCols * 4 / kThr;
+    constexpr int kTile = kCols * kHpPitch;  // of a step's weights, bf16
+    constexpr int kStageBytes = S * 2 * kTile * 2;
+    static_assert(S == 1 || NT * kThr * (int)sizeof(f32x4) <= kStageBytes, "a group's sums take the staged weights' place");
+    __shared__ __align__(16) unsigned char smem[kStageBytes];
+    const int grp = threadIdx.x / kThr, tid = threadIdx.x % kThr, lane = tid & 63, wave = tid >> 6;
+    uint16_t(*const sb)[kTile] = (uint16_t(*)[kTile])smem + 2 * grp;
     const int lr = lane & 15, lq = lane >> 4;
     const int nrows = a.R * a.K, ncols = 3 * a.rank, nz = 2 * a.rank + a.d;
-    const int m0 = blockIdx.x * kHpRows + 16 * wave;
-    const int n0 = blockIdx.y * kHpCols;
+    const int m0 = blockIdx.x * kRows + 16 * wave;
+    const int n0 = blockIdx.y * kCols;
     // row starts (hidden row; a weight row's hidden columns): a lane's 8 inputs
     // past the end of the row read the row's first 8 instead (always inside the
     // row, d >= 8) and are zeroed
     const uint16_t* arow = a.hidden + (int64_t)min(m0 + lr, nrows - 1) * a.d;
-    // this thread's two 16-byte pieces of a step's weight tile: piece c is row
+    // this thread's 16-byte pieces of a step's weight tile: piece c is row
     // c / 4, input chunk c % 4
-    const uint16_t* brow[2];
-    int bdst[2], bpart[2];
+    const uint16_t* brow[kPieces];
+    int bdst[kPieces], bpart[kPieces];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int c = tid + kThreads * i;
+    for (int i = 0; i < kPieces; ++i) {
+        const int c = tid + kThr * i;
         bpart[i] = c & 3;
         brow[i] = a.Wrnn + (int64_t)min(n0 + (c >> 2), ncols - 1) * nz + 2 * a.rank;
         bdst[i] = (c >> 2) * kHpPitch + 8 * bpart[i];
     }
-    const int first = blockIdx.z * per, nsteps = min(ceil_div(a.d, 32), first + per);
-    Hp += (int64_t)blockIdx.z * nrows * ncols;
+    // this group's steps (a run that reaches past the inputs' end adds zeros there)
+    const int per = ceil_div(ceil_div(a.d, 32), S), first = grp * per;
     auto load_a = [&](int st) {
-        const int kk = 32 * st + 8 * lq;
-        const bool in = st < nsteps && kk < a.d;
+        const int kk = 32 * (first + st) + 8 * lq;
+        const bool in = st < per && kk < a.d;
         const bf16x8 v = *(const bf16x8*)(arow + (in ? kk : 0));
         return in ? v : bf16x8{};
     };
     auto load_b = [&](int st, uint4* v) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const int kk = 32 * st + 8 * bpart[i];
-            const bool in = st < nsteps && kk < a.d;
+        for (int i = 0; i < kPieces; ++i) {
+            const int kk = 32 * (first + st) + 8 * bpart[i];
+            const bool in = st < per && kk < a.d;
             const uint4 w = *(const uint4*)(brow[i] + (in ? kk : 0));
             v[i] = in ? w : uint4{0u, 0u, 0u, 0u};
         }
     };
-    f32x4 acc[kHpNt];
+    f32x4 acc[NT];
 #pragma unroll
-    for (int nt = 0; nt < kHpNt; ++nt) acc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    uint4 vb[2];
-    load_b(first, vb);
-    bf16x8 a_cur = load_a(first), a_next = load_a(first + 1);
+    for (int nt = 0; nt < NT; ++nt) acc[nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // two steps ahead in registers, one in the other buffer; the barriers leave the loads
+    // in flight
+    uint4 vb[kPieces], vn[kPieces];
+    load_b(0, vb);
+    bf16x8 a_cur = load_a(0), a_next = load_a(1);
+    load_b(1, vn);
+    bf16x8 a_far = load_a(2);
 #pragma unroll
-    for (int i = 0; i < 2; ++i) *(uint4*)(&sb[first & 1][bdst[i]]) = vb[i];
-    __syncthreads();
-    for (int st = first; st < nsteps; ++st) {
-        load_b(st + 1, vb);  // the next step's tile stays in flight during the products
+    for (int i = 0; i < kPieces; ++i) *(uint4*)(&sb[0][bdst[i]]) = vb[i];
+    lds_barrier();
+    for (int st = 0; st < per; ++st) {
+        load_b(st + 2, vb);
         const uint16_t* cur = sb[st & 1];
 #pragma unroll
-        for (int nt = 0; nt < kHpNt; ++nt) {
+        for (int nt = 0; nt < NT; ++nt) {
             const bf16x8 bfrag = *(const bf16x8*)(cur + (16 * nt + lr) * kHpPitch + 8 * lq);
             acc[nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a_cur, bfrag, acc[nt], 0, 0, 0);
         }
         a_cur = a_next;
-        a_next = load_a(st + 2);
+        a_next = a_far;
+        a_far = load_a(st + 3);
         // the other buffer was last read in step st - 1, before the barrier that ended it
 #pragma unroll
-        for (int i = 0; i < 2; ++i) *(uint4*)(&sb[(st + 1) & 1][bdst[i]]) = vb[i];
+        for (int i = 0; i < kPieces; ++i) {
+            *(uint4*)(&sb[(st + 1) & 1][bdst[i]]) = vn[i];
+            vn[i] = vb[i];
+        }
+        lds_barrier();
+    }
+    f32x4(*const sum)[kThr] = (f32x4(*)[kThr])smem;
+#pragma unroll
+    for (int g = 1; g < S; ++g) {
+        if (grp == g) {
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) sum[nt][tid] = acc[nt];
+        }
+        __syncthreads();
+        if (grp == 0) {
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) acc[nt] += sum[nt][tid];
+        }
         __syncthreads();
     }
+    if (grp > 0) return;
     // lane holds rows m0 + 4 lq + e, output n0 + 16 nt + lr
 #pragma unroll
-    for (int nt = 0; nt < kHpNt; ++nt) {
+    for (int nt = 0; nt < NT; ++nt) {
         const int col = n0 + 16 * nt + lr;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -1115,12 +1146,10 @@ __global__ __launch_bounds__(kThreads) void rnn_hproj(MarkovArgs a, float* Hp, i
     }
 }
 
-// Parts of the backbone projection, at most: three workgroups per CU or so, and the
-// recurrence's waves add a part or two each to their products.
-constexpr int kHpParts = 8;
-inline int hp_parts(int R, int K, int rank) {
-    const int64_t wgs = (((int64_t)R * K + kHpRows - 1) / kHpRows) * ceil_div(3 * rank, kHpCols);
-    return (int)std::min<int64_t>(kHpParts, std::max<int64_t>(1, 768 / wgs));
+template <int RW, int NT, int S>
+void launch_hproj(const MarkovArgs& a, float* Hp, hipStream_t s) {
+    const dim3 g((unsigned)ceil_div(a.R * a.K, 16 * RW), ceil_div(3 * a.rank, 16 * NT));
+    hipLaunchKernelGGL((rnn_hproj<RW, NT, S>), g, dim3(S * RW * DSPARK_WAVE), 0, s, a, Hp);
 }
 
 // hi + mid (+ lo): each term the bf16 rounding of what the previous ones
@@ -1149,18 +1178,17 @@ __device__ __forceinline__ void split3(float v, uint16_t* dst, int stride) {
 // dim) and applies the gated update in registers: s_k = g s_{k-1} + (1 - g)
 // tanh(a_c) with g = sigmoid(a_g), written in fp32 and as three terms, and the
 // head's output o_k = tanh(a_o) as two terms (hi, mid) for the vocabulary
-// product.  A workgroup owns
-// 16 dims x 16 requests; its four waves take every fourth 32-input step (both
-// operands straight from memory, kStDepth steps ahead) and wave 0 adds the
-// four partial products in wave order (eight waves: 2 us a position more).  The state is double-buffered (others
-// may still read s_{k-1}); at k = 1 it is zero and its steps are skipped.
-constexpr int kStJ = 16, kStR = 16, kStDepth = 4, kStWaves = 4;
-static_assert(kHpParts <= 2 * kStWaves, "parts of the backbone projection per wave");
-__global__ __launch_bounds__(kStWaves * DSPARK_WAVE) void rnn_state(MarkovArgs a, const float* Hp, int hpz,
+// product.  A workgroup owns 16 dims x 16 requests; its four waves take every
+// fourth 32-input step (both operands straight from memory, kStDepth steps ahead)
+// and wave 0 adds the four partial products in wave order (eight waves: 2 us a
+// position more).  The state is double-buffered (others may still read s_{k-1});
+// at k = 1 it is zero and its steps are skipped.
+constexpr int kStJ = 16, kStR = 16, kStDepth = 4;
+__global__ __launch_bounds__(kThreads) void rnn_state(MarkovArgs a, const float* Hp,
                                                       const float* s_prev, const uint16_t* S3_prev,
                                                       float* s_next, uint16_t* S3_next,
                                                       const uint16_t* Ee, uint16_t* E2, int k) {
-    __shared__ f32x4 part[kStWaves - 1][3][DSPARK_WAVE];
+    __shared__ f32x4 part[kWaves - 1][3][DSPARK_WAVE];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int lr = lane & 15, lq = lane >> 4;
     const int rank = a.rank, nz = 2 * rank + a.d;
@@ -1171,7 +1199,7 @@ __global__ __launch_bounds__(kStWaves * DSPARK_WAVE) void rnn_state(MarkovArgs a
     const int st0 = (k > 1 ? 0 : ks_s) + wave;  // this wave's steps: st0, st0 + 4, ...
     bf16x8 af[kStDepth], bfr[kStDepth][3];
     auto load = [&](int i, int slot) {  // this wave's i-th step
-        const int kk = 32 * min(st0 + kStWaves * i, nst - 1) + 8 * lq;  // past the end: unused
+        const int kk = 32 * min(st0 + kWaves * i, nst - 1) + 8 * lq;  // past the end: unused
         const bool state = kk < 3 * rank;                            // uniform over the wave
         af[slot] = state ? *(const bf16x8*)(S3_prev + (int64_t)ra * 3 * rank + kk)
                          : *(const bf16x8*)(Ee + (int64_t)ra * rank + (kk - 3 * rank));
@@ -1180,23 +1208,21 @@ __global__ __launch_bounds__(kStWaves * DSPARK_WAVE) void rnn_state(MarkovArgs a
         for (int p = 0; p < 3; ++p)
             bfr[slot][p] = *(const bf16x8*)(a.Wrnn + (int64_t)(p * rank + j0 + lr) * nz + col);
     };
-    const int nmine = st0 < nst ? (nst - st0 + kStWaves - 1) / kStWaves : 0;
-    // the projection of the hidden states (wave w takes its parts w and w + 4) and, in
-    // wave 0, the previous state, of requests m0 + 4 lq + e, dim j0 + lr, do not depend on
-    // the products: they are loaded first (rows clamped, then masked)
+    const int nmine = st0 < nst ? (nst - st0 + kWaves - 1) / kWaves : 0;
+    // wave 0's epilogue inputs (the projection of the hidden states and the
+    // previous state of its requests m0 + 4 lq + e, dim j0 + lr) do not depend
+    // on the products: they are loaded first (rows clamped, then masked)
     const int j = j0 + lr;
-    float hpv[4][3], hpw[4][3], spv[4];
+    float hpv[4][3], spv[4];
+    if (wave == 0) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const int rc = min(m0 + 4 * lq + e, a.R - 1);
-        const int64_t all = (int64_t)a.R * a.K * 3 * rank;  // of a part
-        const float* hp = Hp + wave * all + ((int64_t)rc * a.K + (k - 1)) * (3 * rank) + j;
+        for (int e = 0; e < 4; ++e) {
+            const int rc = min(m0 + 4 * lq + e, a.R - 1);
+            const float* hp = Hp ? Hp + ((int64_t)rc * a.K + (k - 1)) * (3 * rank) : nullptr;
 #pragma unroll
-        for (int p = 0; p < 3; ++p) {
-            hpv[e][p] = wave < hpz ? hp[p * rank] : 0.0f;
-            hpw[e][p] = wave + kStWaves < hpz ? hp[kStWaves * all + p * rank] : 0.0f;
+            for (int p = 0; p < 3; ++p) hpv[e][p] = hp ? hp[p * rank + j] : 0.0f;
+            spv[e] = k > 1 ? s_prev[(int64_t)rc * rank + j] : 0.0f;
         }
-        spv[e] = wave == 0 && k > 1 ? s_prev[(int64_t)rc * rank + j] : 0.0f;
     }
     f32x4 acc[3];
 #pragma unroll
@@ -1214,10 +1240,6 @@ __global__ __launch_bounds__(kStWaves * DSPARK_WAVE) void rnn_state(MarkovArgs a
             load(i0 + kStDepth + u, u);
         }
     }
-#pragma unroll
-    for (int p = 0; p < 3; ++p)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) acc[p][e] += hpv[e][p] + hpw[e][p];
     if (wave > 0) {
 #pragma unroll
         for (int p = 0; p < 3; ++p) part[wave - 1][p][lane] = acc[p];
@@ -1225,7 +1247,7 @@ __global__ __launch_bounds__(kStWaves * DSPARK_WAVE) void rnn_state(MarkovArgs a
     __syncthreads();
     if (wave > 0) return;
 #pragma unroll
-    for (int w = 0; w < kStWaves - 1; ++w)
+    for (int w = 0; w < kWaves - 1; ++w)
 #pragma unroll
         for (int p = 0; p < 3; ++p) acc[p] += part[w][p][lane];
     // lane holds requests m0 + 4 lq + e, state dim j0 + lr
@@ -1233,7 +1255,12 @@ __global__ __launch_bounds__(kStWaves * DSPARK_WAVE) void rnn_state(MarkovArgs a
     for (int e = 0; e < 4; ++e) {
         const int r = m0 + 4 * lq + e;
         if (r >= a.R) continue;
-        const float ag = acc[0][e], ac = acc[1][e], ao = acc[2][e];
+        float ag = acc[0][e], ac = acc[1][e], ao = acc[2][e];
+        if (Hp) {
+            ag += hpv[e][0];
+            ac += hpv[e][1];
+            ao += hpv[e][2];
+        }
         const float g = 1.0f / (1.0f + expf(-ag));
         const float sp = spv[e];
         const float sn = g * sp + (1.0f - g) * tanhf(ac);
@@ -1248,15 +1275,12 @@ hipError_t launch_rnn_ks(const MarkovArgs& a, uint16_t* Ee, uint16_t* E2, float*
                          uint16_t* T0, uint16_t* T1, float* Hp, float2* stats, RowInfo* info,
                          float* sh, unsigned* sync, int ntiles, bool vec, hipStream_t s) {
     const int64_t rows = (int64_t)a.R * a.K;
-    int hpz = 0;  // parts of the backbone projection
     if (a.d > 0) {
         hipLaunchKernelGGL(md_hidden, dim3((unsigned)ceil_div((int)rows, kWaves)), dim3(kThreads), 0, s, a, sh);
-        // at least eight steps a part
-        const int nsteps = ceil_div(a.d, 32);
-        const int per = std::max(ceil_div(nsteps, hp_parts(a.R, a.K, a.rank)), 8);
-        hpz = ceil_div(nsteps, per);
-        hipLaunchKernelGGL(rnn_hproj, dim3((unsigned)ceil_div((int)rows, kHpRows), ceil_div(3 * a.rank, kHpCols), hpz),
-                           dim3(kThreads), 0, s, a, Hp, per);
+        const int64_t wgs = (rows + 31) / 32 * ceil_div(3 * a.rank, 64);
+        if (wgs <= 256) launch_hproj<2, 4, 8>(a, Hp, s);
+        else if (wgs <= 512) launch_hproj<2, 4, 4>(a, Hp, s);
+        else launch_hproj<4, 8, 2>(a, Hp, s);
     }
     const float* shp = a.d > 0 ? sh : nullptr;
     const float* hpp = a.d > 0 ? Hp : nullptr;
@@ -1271,8 +1295,8 @@ hipError_t launch_rnn_ks(const MarkovArgs& a, uint16_t* Ee, uint16_t* E2, float*
         float* sn = (k & 1) ? S0 : S1;
         const uint16_t* tp = (k & 1) ? T1 : T0;
         uint16_t* tn = (k & 1) ? T0 : T1;
-        hipLaunchKernelGGL(rnn_state, dim3(a.rank / kStJ, ceil_div(a.R, kStR)), dim3(kStWaves * DSPARK_WAVE), 0,
-                           s, a, hpp, hpz, sp, tp, sn, tn, (const uint16_t*)Ee, E2, k);
+        hipLaunchKernelGGL(rnn_state, dim3(a.rank / kStJ, ceil_div(a.R, kStR)), dim3(kThreads), 0, s, a, hpp,
+                           sp, tp, sn, tn, (const uint16_t*)Ee, E2, k);
         // the draw gathers W1[x_k] into Ee: the embedding input of position k + 1
         if (coop) coop_position<KS, 2>(a, E2, Ee, stats, info, shp, sync, ntiles, k, launch, s);
         else position<KS, 2>(a, E2, stats, Ee, shp, ntiles, k, vec, s);
@@ -1343,7 +1367,7 @@ RnnLayout rnn_layout(int R, int K, int V, int rank) {
     l.e2 = align256((size_t)R * 2 * rank * 2);
     l.st = align256((size_t)R * rank * 4);
     l.st3 = align256((size_t)R * 3 * rank * 2);
-    l.hp = align256((size_t)R * K * 3 * rank * 4 * mkd::hp_parts(R, K, rank));
+    l.hp = align256((size_t)R * K * 3 * rank * 4);
     l.stats = align256((size_t)R * ntiles * sizeof(float2));
     l.info = align256((size_t)R * sizeof(mkd::RowInfo));
     l.sh = align256((size_t)R * K * sizeof(float));

@@ -331,3 +331,32 @@ def test_binding_rejects_host_tensors():
     import torch
     with pytest.raises(dspark.DSparkError):
         dspark.dspark_schedule(torch.zeros(2, 3), torch.ones(20, dtype=torch.float64))
+
+
+@pytest.mark.parametrize("V,rank", [(1024, 64), (32768, 128), (129280, 256)])
+def test_workspaces_grow_with_the_batch(L, V, rank):
+    # a workspace sized once for the largest batch serves every smaller one
+    sizes = {
+        "schedule": lambda R, K: L.dspark_schedule_workspace_size(R, K),
+        "accept": lambda R, K: L.dspark_accept_workspace_size(R, K, V),
+        "markov": lambda R, K: L.dspark_markov_draft_workspace_size(R, K, V, rank),
+        "rnn": lambda R, K: L.dspark_rnn_draft_workspace_size(R, K, V, rank),
+    }
+    for name, size in sizes.items():
+        for K in range(1, 17):
+            prev = 0
+            for R in range(1, 300):
+                n = size(R, K)
+                assert n >= prev and (K == 1 or n >= size(R, K - 1)), (name, R, K)
+                prev = n
+
+
+@pytest.mark.parametrize("R,K", [(1, 1), (8, 16), (128, 8), (200, 16)])
+def test_rnn_draft_workspace_holds_one_projection(L, R, K):
+    # beside the Markov head's buffers: the two-term output, the state twice in fp32 and as
+    # three bf16 terms, less the second embedding, and one projection of the hidden states
+    V, rank = 32768, 256
+    up = lambda n: -(-n // 256) * 256  # noqa: E731
+    more = up(R * 2 * rank * 2) + 2 * up(R * rank * 4) + 2 * up(R * 3 * rank * 2) - up(R * rank * 2)
+    assert (L.dspark_rnn_draft_workspace_size(R, K, V, rank)
+            == L.dspark_markov_draft_workspace_size(R, K, V, rank) + more + up(R * K * 3 * rank * 4))

@@ -169,11 +169,13 @@ def test_rnn_draft_degenerate_shapes(R, K, V):
         assert (tok == 0).all().item() and torch.equal(p, torch.ones_like(p))
 
 
-# small batches of either base type; the backbone projection in one part (d = 0 has none), a
-# few and eight
+# either base type; the backbone projection's three tile shapes (by rows and rank: up to 256
+# workgroups of the small tile, up to 512, above), with inputs for some and for all of the
+# groups that share them, and none at all (d = 0)
 @pytest.mark.parametrize("R,K,V,rank,d,dt", [
     (8, 3, 8192, 64, 256, "f32"), (9, 3, 8192, 64, 264, "f32"), (32, 3, 1000, 64, 2048, "bf16"),
     (33, 3, 1000, 32, 520, "bf16"), (17, 4, 2052, 256, 1024, "bf16"), (1, 5, 129, 32, 0, "f32"), (3, 3, 9000, 256, 8, "bf16"),
+    (90, 8, 500, 256, 520, "bf16"), (90, 8, 500, 256, 24, "f32"), (171, 9, 300, 256, 72, "f32"),
 ])
 def test_rnn_draft_block_edges(R, K, V, rank, d, dt):
     w = synth.scaled(synth.WORKLOADS["serving"], R=R, K=K, V=V, logit_dtype=dt)
