@@ -210,6 +210,9 @@ dspark_status dspark_schedule_topk(const float* conf, int R, int K, const int32_
  *       q/k/v 16-byte and out 8-byte (bf16) or 16-byte (fp32) aligned: MFMA
  *       tiles, the probabilities at 32-bit accuracy, HBM-bound;
  *     - anything else: vector ALUs.
+ *   ws of dspark_verify_attn_workspace_size bytes, 256-aligned.  A smaller one is
+ *   refused only when no kernel for the call can do with it; kernels that write
+ *   less stand in for the fastest otherwise.
  *   On the matrix cores a non-finite value of a later verify token of a
  *   request can reach that request's earlier rows (0 times it).
  * ---------------------------------------------------------------------- */

@@ -49,7 +49,8 @@ constexpr int kMfWaves = 4;
 // Keys per split (the last split of a context holds the rest): kSplit, or a
 // smaller power of two down to kMinSplit when a batch's largest possible number
 // of work items at kSplit is below kTargetItems (three rounds of the 512
-// resident workgroups), so that a small batch still fills the part.
+// resident workgroups), so that a small batch still fills the part.  (Batches of
+// up to 32 KV heads get below 2048 only where their ranges' workspace is not there.)
 constexpr int kSplit = 4096;
 constexpr int kMinSplit = 512;
 constexpr int64_t kTargetItems = 1536;
@@ -133,13 +134,19 @@ static MfGeom mf_geom(const AttnArgs& a) {
     return g;
 }
 
-// What the path writes, and never less than the queue's: a call is refused for its
-// workspace alike whichever way its batch is cut.
+// A workspace of the queue's size serves every call; ranges that write more than that are
+// taken where it is larger (one request x 8 heads of up to 16384 keys: 8.5 MB through the
+// queue, 34 MB as ranges).
+static size_t mf_queue_bytes(const MfGeom& g) { return g.counter_bytes + g.list_bytes + g.mlist_bytes + g.part_bytes; }
+static size_t mf_range_bytes(const AttnArgs& a, const MfGeom& g) {
+    return g.direct ? 0 : range_head_bytes(a.R) + (size_t)g.workers * 2 * g.slot_floats * sizeof(float);
+}
+
+size_t attn_mfma_least(const AttnArgs& a) { return mf_queue_bytes(mf_geom(a)); }
+
 size_t attn_mfma_workspace(const AttnArgs& a) {
     const MfGeom g = mf_geom(a);
-    const size_t queue = g.counter_bytes + g.list_bytes + g.mlist_bytes + g.part_bytes;
-    if (g.direct || !g.ranges) return queue;
-    return std::max(queue, range_head_bytes(a.R) + (size_t)g.workers * 2 * g.slot_floats * sizeof(float));
+    return std::max(mf_queue_bytes(g), g.ranges ? mf_range_bytes(a, g) : 0);
 }
 
 struct MfParams {
@@ -726,7 +733,7 @@ __global__ __launch_bounds__(256) void attn_mfma_merge(MfParams p) {
     }
 }
 
-hipError_t launch_attn_mfma(const AttnArgs& a, void* ws, hipStream_t s) {
+hipError_t launch_attn_mfma(const AttnArgs& a, void* ws, size_t ws_bytes, hipStream_t s) {
     const MfGeom g = mf_geom(a);
     MfParams p;
     p.a = a;
@@ -747,7 +754,7 @@ hipError_t launch_attn_mfma(const AttnArgs& a, void* ws, hipStream_t s) {
     p.list = (int4*)((char*)ws + g.counter_bytes);
     p.mlist = (int4*)((char*)ws + g.counter_bytes + g.list_bytes);
     p.part = (float*)((char*)ws + g.counter_bytes + g.list_bytes + g.mlist_bytes);
-    if (g.ranges) {
+    if (g.ranges && ws_bytes >= mf_range_bytes(a, g)) {
         Ranges rg;
         rg.a = a;
         rg.group = g.group;

@@ -580,11 +580,9 @@ bool attn_stream_supported(const AttnArgs& a) {
            (uintptr_t)a.out % (a.bf16 ? 8 : 16) == 0;
 }
 
-// What the path writes, and never less than the vector-ALU path's: a shape is refused
-// for its workspace alike whatever the strides and the alignment.
 size_t attn_stream_workspace(const AttnArgs& a) {
     const stream::Geom g = stream::geom(a);
-    return std::max(attn_generic_workspace(a), g.direct ? 0 : range_head_bytes(a.R) + g.part_bytes);
+    return g.direct ? 0 : range_head_bytes(a.R) + g.part_bytes;
 }
 
 hipError_t launch_attn_stream(const AttnArgs& a, void* ws, hipStream_t s) {

@@ -321,19 +321,19 @@ dspark_status dspark_verify_attn(const void* q, const void* k_cache, const void*
                                    scale, dt, out, lse);
     // matrix-core paths first: GQA head dim 128, latent 576/512, any head size up to 256;
     // else vector ALUs
-    const int path = dspark::attn_mfma_supported(a)     ? 0
-                     : dspark::attn_mla_supported(a)    ? 1
-                     : dspark::attn_stream_supported(a) ? 2
-                                                        : 3;
-    const size_t need = path == 0   ? dspark::attn_mfma_workspace(a)
+    // (the last two take the same calls: a workspace too small for the third is for the
+    // vector ALUs, so a call is refused alike whatever its strides and alignment)
+    const int path = dspark::attn_mfma_supported(a)  ? 0
+                     : dspark::attn_mla_supported(a) ? 1
+                     : dspark::attn_stream_supported(a) && ws_bytes >= dspark::attn_stream_workspace(a) ? 2 : 3;
+    const size_t need = path == 0   ? dspark::attn_mfma_least(a)
                         : path == 1 ? dspark::attn_mla_workspace(a)
-                        : path == 2 ? dspark::attn_stream_workspace(a)
                                     : dspark::attn_generic_workspace(a);
     if (ws_bytes < need || (need > 0 && !ws) || !aligned(ws, 256))
         return fail(DSPARK_EWORKSPACE, "workspace of %zu bytes (256-aligned) needed, got %zu",
                     need, ws_bytes);
     hipStream_t s = (hipStream_t)stream;
-    return hip_status(path == 0   ? dspark::launch_attn_mfma(a, ws, s)
+    return hip_status(path == 0   ? dspark::launch_attn_mfma(a, ws, ws_bytes, s)
                       : path == 1 ? dspark::launch_attn_mla(a, ws, s)
                       : path == 2 ? dspark::launch_attn_stream(a, ws, s)
                                   : dspark::launch_attn_generic(a, ws, s),

@@ -37,7 +37,8 @@ struct AttnArgs {
 // The MFMA path handles bf16, Dqk == Dv == 128, page % 32 == 0.
 bool attn_mfma_supported(const AttnArgs& a);
 size_t attn_mfma_workspace(const AttnArgs& a);
-hipError_t launch_attn_mfma(const AttnArgs& a, void* ws, hipStream_t s);
+size_t attn_mfma_least(const AttnArgs& a);  // what it can do with
+hipError_t launch_attn_mfma(const AttnArgs& a, void* ws, size_t ws_bytes, hipStream_t s);
 bool attn_mla_shape_ok(const AttnArgs& a);   // shape only (workspace sizing)
 bool attn_mla_supported(const AttnArgs& a);  // shape, value aliasing and alignment
 size_t attn_mla_workspace(const AttnArgs& a);

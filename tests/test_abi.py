@@ -175,6 +175,25 @@ def test_verify_attn_workspace_sizes(L):
     assert f(0, 9, 8, 2, 64, 64, 8, 16, 0) == 0  # invalid shape -> 0
 
 
+# shapes whose fastest kernels write more than others that can do the call: what is refused
+# is a workspace too small for those (`least` bytes)
+@pytest.mark.parametrize("shape,least", [
+    # ranges, and the work queue: 8 x 32 splits of 512 keys, their 64 x (128 + 2) partials and lists
+    (dict(R=1, max_q=1, Hq=8, Hkv=8, max_pages=256), 256 + 256 * 32 + 64 * 32 + 256 * 64 * 130 * 4),
+    # any head size, and the vector ALUs' partials of one split
+    (dict(R=4, max_q=2, Hq=8, Hkv=8, page=16, max_pages=64, Dqk=64, Dv=64, dt=0), 4 * 2 * 8 * 66 * 4),
+])
+def test_verify_attn_least_workspace(L, shape, least):
+    a = dict(page=64, Dqk=128, Dv=128, dt=1)
+    a.update(shape)
+    strides = (C.c_int64 * 3)(a["Hkv"] * a["page"] * a["Dqk"], a["page"] * a["Dqk"], a["Dqk"])
+    full = L.dspark_verify_attn_workspace_size(a["R"], a["max_q"], a["Hq"], a["Hkv"], a["Dqk"], a["Dv"],
+                                               a["max_pages"], a["page"], a["dt"])
+    assert _attn(L, ks=strides, vs=strides, ws_bytes=0, **a) == EWORKSPACE
+    need = int(re.search(r"of (\d+) bytes", L.dspark_last_error().decode())[1])
+    assert need == least < full
+
+
 def _acc(L, **kw):
     a = dict(tok=FAKE, dp=FAKE, logits=FAKE, dt=1, ld=1024, u=FAKE, cu=FAKE, R=4, K=8, V=1024,
              it=1.0, acc=FAKE, nxt=FAKE, rate=None, ws=FAKE, ws_bytes=0)

@@ -440,3 +440,46 @@ def test_ranges_and_queue_agree(R, Hkv, q_len, kv_len):
         np.testing.assert_allclose(np.array([l[t, h] for t, h in rows]), ref_lse, rtol=0, atol=1e-4)
     # both round P to bf16 and the output once: each is within 2^-7 of a row
     assert row_rel_err(to_f64(out), to_f64(out2)).max() <= 2.0 ** -7
+
+
+@pytest.mark.parametrize("dtype,D,page,Hq,Hkv,q_len,kv_len", [
+    ("bf16", 128, 64, 32, 8, [1, 9, 4], [64, 1500, 700]),  # ranges: the queue
+    ("bf16", 64, 16, 8, 2, [1, 9, 4], [64, 1500, 700]),    # any head size: the vector ALUs
+    ("f32", 128, 64, 8, 2, [1, 9, 4], [64, 1500, 700]),
+])
+def test_smaller_workspace(dtype, D, page, Hq, Hkv, q_len, kv_len):
+    """A workspace too small for the fastest kernels and large enough for others: the call
+    goes to those; smaller than that it is refused, and nothing is written."""
+    import re
+
+    import torch
+    from paper_2607_05147_amd import dspark
+    from gpu_helpers import to_dev
+    w = synth.scaled(synth.WORKLOADS["tiny" if dtype == "f32" else "mid"], R=len(q_len), K=8, Hq=Hq, Hkv=Hkv, Dqk=D,
+                     Dv=D, page=page)
+    cu = oracle.cu_from_len(np.asarray(q_len) - 1)
+    kv = synth.paged_kv(w, 61, kv_len=np.asarray(kv_len, np.int32))
+    q = synth.query_rows(w, 61, synth.flat_keys(np.diff(cu)))
+    ref, _ = oracle.verify_attn(q, kv.k, kv.v, kv.k_strides, kv.v_strides, kv.block_table, kv.kv_len, cu, Hq, Hkv, D, D,
+                                page, w.scale, dtype)
+    dkv = DevKV(kv, dtype == "bf16")
+
+    def call(ws_bytes):
+        out = torch.full(q.shape, 7.0, dtype=dkv.k.dtype, device=dkv.k.device)
+        ws = torch.zeros(max(ws_bytes, 256), dtype=torch.uint8, device=dkv.k.device)[:ws_bytes]
+        dspark.dspark_verify_attn(to_dev(q, dtype == "bf16"), dkv.k, dkv.v, dkv.ks, dkv.vs, dkv.bt, dkv.kv_len, to_dev(cu),
+                                  w.max_q, Hkv, D, page, w.scale, out=out, ws=ws)
+        return out
+
+    full = dspark.dspark_verify_attn_workspace_size(w.R, w.max_q, Hq, Hkv, D, D, kv.block_table.shape[1], page,
+                                                    dkv.k.dtype)
+    with pytest.raises(dspark.DSparkError) as e:
+        call(0)
+    need = int(re.search(r"of (\d+) bytes", str(e.value))[1])
+    log(f"[attn] smaller workspace: {dtype} D={D}: {need} of {full} bytes")
+    assert need < full
+    with pytest.raises(dspark.DSparkError):
+        call(need - 1)
+    for n in (need, full - 1, full):
+        o = to_f64(call(n))
+        assert row_rel_err(o, ref).max() <= TOL[dtype]
