@@ -129,8 +129,8 @@ static MfGeom mf_geom(const AttnArgs& a) {
                (int64_t)a.R * a.Hkv < (int64_t)1 << 31;
     // (up to twice the keys when the chunks alone fill the part: 64 requests x 8
     // heads of 256-500 keys 30 against 34 us)
-    g.direct = g.ranges && (max_kv <= kDirectKeys || (max_kv <= 2 * kDirectKeys && slots >= 2 * kRangeCUs));
-    if (g.direct) g.workers = slots;
+    g.direct = g.ranges && g.rc_max <= kDirectChunks &&
+               (max_kv <= kDirectKeys || (max_kv <= 2 * kDirectKeys && slots >= 2 * kRangeCUs));
     return g;
 }
 
@@ -761,15 +761,13 @@ hipError_t launch_attn_mfma(const AttnArgs& a, void* ws, size_t ws_bytes, hipStr
         rg.chunk_rows = g.chunk_rows;
         rg.by_head = 1;
         rg.direct = g.direct;
-        rg.rc_max = g.rc_max;
         rg.resident = (int)g.resident;
         rg.min_units = kMfMinUnits;
         rg.head = (int64_t*)ws;
         rg.part = (float*)((char*)ws + range_head_bytes(a.R));
-        if (g.tpw == 2)
-            hipLaunchKernelGGL(attn_mfma_ranges<2>, dim3((unsigned)g.workers), dim3(kMfThreads), 0, s, p, rg);
-        else
-            hipLaunchKernelGGL(attn_mfma_ranges<1>, dim3((unsigned)g.workers), dim3(kMfThreads), 0, s, p, rg);
+        const dim3 grid = g.direct ? dim3((unsigned)(a.R * a.Hkv), (unsigned)g.rc_max) : dim3((unsigned)g.workers);
+        if (g.tpw == 2) hipLaunchKernelGGL(attn_mfma_ranges<2>, grid, dim3(kMfThreads), 0, s, p, rg);
+        else hipLaunchKernelGGL(attn_mfma_ranges<1>, grid, dim3(kMfThreads), 0, s, p, rg);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess || g.direct) return e;
         return g.tpw == 2 ? launch_merge<false, 16 * kMfWaves * 2, kD, kStepTok>(rg, s)

@@ -24,12 +24,16 @@ constexpr int kRangeCUs = 256;  // gfx950; sizes the grids and the partials
 // Batches whose contexts are bounded by this many keys take a worker per (request,
 // head, chunk): a worker's few steps cost less than the merge kernel would.
 constexpr int kDirectKeys = 256;
+// Their grid: (request, head) by chunk, the chunks last, so that what requests leave empty
+// of them is the grid's end (next to each other, every second workgroup of 192 requests x
+// 8 heads with two chunks was empty and half of the XCDs idle: 72 against 44 us).
+constexpr int kDirectChunks = 65535;  // a grid's second dimension, at most
 
 struct Ranges {
     AttnArgs a;
     int group, chunk_rows;    // query heads per KV head; rows of a chunk
     int by_head;              // every head is cut alike
-    int direct, rc_max;       // short contexts: a worker per (request, head, chunk), no cuts and no merge
+    int direct;               // short contexts: a worker per (request, head, chunk), no cuts and no merge
     int resident, min_units;  // ranges (per head with by_head), at most; units of a range, at least
     int64_t* head;            // [0] units per range, [32 + r] first unit of request r (written by the workers)
     float* part;              // [worker][2] {m[chunk_rows], l[chunk_rows], o[chunk_rows][Dp]}
@@ -108,10 +112,8 @@ __device__ __forceinline__ void range_walk(const Ranges& p, F f) {
     const AttnArgs& a = p.a;
     const int total_rows = range_total_rows(a);
     if (p.direct) {
-        int b = blockIdx.x, q0, ql, kv;
-        const int rc = b % p.rc_max;
-        b /= p.rc_max;
-        const int g = b % a.Hkv, r = b / a.Hkv;
+        const int rc = blockIdx.y, g = blockIdx.x % a.Hkv, r = blockIdx.x / a.Hkv;
+        int q0, ql, kv;
         if (!range_shape(a, r, total_rows, q0, ql, kv) || rc * p.chunk_rows >= ql * p.group) return;
         const int ns = (kv + STEP - 1) / STEP;
         f(r, g, rc, q0, ql, kv, 0, ns, ns, (int64_t)0);

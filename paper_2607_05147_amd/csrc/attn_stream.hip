@@ -537,7 +537,7 @@ static Geom geom(const AttnArgs& a) {
     g.ch = chunks_of(a);
     const int64_t rows = (int64_t)a.max_q * (a.Hq / a.Hkv);
     const int64_t max_kv = (int64_t)a.max_pages * a.page;
-    g.direct = max_kv <= kDirectKeys;
+    g.direct = max_kv <= kDirectKeys && (rows + 15) / 16 <= kDirectChunks;
     // row tiles per wave: as many as a request can fill, up to what the
     // registers hold without spilling (more tiles than that read the keys again,
     // from the last-level cache).  Short contexts have few waves and are bound
@@ -592,7 +592,6 @@ hipError_t launch_attn_stream(const AttnArgs& a, void* ws, hipStream_t s) {
     p.a = a;
     p.group = a.Hq / a.Hkv;
     p.chunk_rows = 16 * g.nt;
-    p.rc_max = g.rc_max;
     p.by_head = 0;
     p.resident = (int)g.resident;
     p.min_units = stream::kMinUnits;
@@ -612,7 +611,8 @@ hipError_t launch_attn_stream(const AttnArgs& a, void* ws, hipStream_t s) {
     return stream::with_cfg(a.bf16, g.ch, g.nt, [&](auto f32, auto ch, auto nt) {
         constexpr bool F = decltype(f32)::value;
         constexpr int CH = decltype(ch)::value, NT = decltype(nt)::value;
-        hipLaunchKernelGGL((stream::attn_stream_kernel<F, CH, NT>), dim3((unsigned)g.waves), dim3(DSPARK_WAVE), 0, s, p);
+        const dim3 grid = g.direct ? dim3((unsigned)(a.R * a.Hkv), (unsigned)g.rc_max) : dim3((unsigned)g.waves);
+        hipLaunchKernelGGL((stream::attn_stream_kernel<F, CH, NT>), grid, dim3(DSPARK_WAVE), 0, s, p);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess || g.direct) return e;
         return launch_merge<F, 16 * NT, stream::Cfg<F, CH>::Dp, stream::Cfg<F, CH>::Step>(p, s);

@@ -316,6 +316,8 @@ def test_rows_outside_the_batch_left_unwritten(name):
     ("mid", 8, 8, [1, 2, 5], [1, 2, 5]),
     # contexts one key past a page, and one key past a 4096-key split
     ("mid", 32, 8, [1, 3, 17], [64, 65, 4097]),
+    # a workgroup per (request, head, chunk), two chunks of 128 rows that a request fills in part
+    ("mid", 64, 8, [1, 17, 16, 15], [200, 256, 17, 15]),
     # latent: a single key; 4097 keys (one split, a partial last step)
     ("mla", 128, 1, [1, 2], [1, 4097]),
     # latent: one key past an 8192-key split, and a last split whose first key
