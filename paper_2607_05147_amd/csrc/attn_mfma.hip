@@ -55,14 +55,17 @@ constexpr int kSplit = 4096;
 constexpr int kMinSplit = 512;
 constexpr int64_t kTargetItems = 1536;
 static_assert(kSplit / 64 <= DSPARK_WAVE, "a split's page ids fit one per lane");
-// Batches of at most this many steps per resident workgroup (from the host's
+// Batches of at most kRangeUnits steps per resident workgroup (from the host's
 // bound on the contexts) are cut into equal ranges, without a plan kernel; larger
-// ones go through the queue, which evens out the workgroups' speeds.  Whole call,
-// ranges
-// against queue (us, 64/8 heads): 4 requests of 2K-16K keys 51 / 62, one 25 / 33, 8 of
-// 300-700 19 / 25, 32 of 1K-4K (32/8 heads) 80 / 88, 32 of 2K-16K 251 / 251, 64 of
-// them 246 / 237, 128 of about 4.6K 476 / 443.
+// ones go through the queue, which evens out the workgroups' speeds, and so do those
+// that have a (request, head) for every workgroup and splits of kLongSplit keys or more
+// (few partials, or none).  Whole call, ranges against queue (us): 64/8 heads, 4 requests
+// of 2K-16K keys 51 / 62, one 25 / 33, 8 of 300-700 19 / 25, 48 of 1K-3K 99 / 105, 32 of
+// 2K-16K 251 / 251, 128 of about 4.6K 476 / 443; 32/8 heads, 60 of 1K-3K 115 / 124, 100
+// 170 / 162, 192 of 64-1000 101 / 87, 300 of 1K-2K 358 / 330; 8/1 heads, 1000 of 300-1000
+// (splits of 512) 88 / 100, 8192 of 300-640 504 / 473.
 constexpr int kRangeUnits = 320;
+constexpr int kLongSplit = 2048;
 constexpr int kMfMinUnits = 4;  // steps of a range, at least
 constexpr int kStepTok = 32;   // keys per step
 constexpr int kRing = 4;       // LDS buffers; copies run kRing - 1 steps ahead
@@ -128,9 +131,11 @@ static MfGeom mf_geom(const AttnArgs& a) {
     g.ranges = units <= kRangeUnits * g.resident && g.rc_max * steps < (int64_t)1 << 31 &&
                (int64_t)a.R * a.Hkv < (int64_t)1 << 31;
     // (up to twice the keys when the chunks alone fill the part: 64 requests x 8
-    // heads of 256-500 keys 30 against 34 us)
+    // heads of 256-500 keys 24 against 32 us)
     g.direct = g.ranges && g.rc_max <= kDirectChunks &&
                (max_kv <= kDirectKeys || (max_kv <= 2 * kDirectKeys && slots >= 2 * kRangeCUs));
+    // a (request, head) or more for every workgroup and long items: the queue
+    if (!g.direct && g.split >= kLongSplit && (int64_t)a.R * a.Hkv >= 2 * kRangeCUs) g.ranges = 0;
     return g;
 }
 
