@@ -42,7 +42,12 @@ constexpr int kMaxChunks = 256;                // V <= 2^20
 // 20.4 / 22.0; with 8 chunks 64 x 32000 26.6 / 25.8, with 16 chunks 8 x 65000 29.7 /
 // 23.8; with entry loads (4 x 30001, fp32) 36.5 / 32.6.
 constexpr int kFuseChunks = 4;
-constexpr int kRateFuseChunks = 8;  // the same for the rate's sum per row
+// The same for the rate's sum per row.  Above four chunks, and with entry loads, only while
+// the rows' waves are few (us per call, fused against not: 256 x 32768 entries 98.0 / 96.4,
+// 64 x 32000 58.6 / 59.9; entry loads, 4 x 4001 39.1 / 47.5, fp32 400 x 4001 70.1 / 59.5 and
+// 100 x 8001 62.6 / 59.2).
+constexpr int kRateFuseChunks = 8;
+constexpr int64_t kRateFuseItems = 16384, kRateFuseSlow = 2048;  // (row, chunk) pairs, by the host's bound
 static_assert(kMaxChunks <= kBlk, "the draw loads one chunk mass per thread");
 constexpr float kLog2e = 1.4426950408889634f;
 
@@ -925,7 +930,9 @@ static hipError_t launch_typed(const AcceptArgs& a, void* ws, hipStream_t s) {
         DS_DRAW(false);
     }
 #undef DS_DRAW
-    if (a.accept_rate && nch <= kRateFuseChunks) {
+    const bool rate_rows = nch <= kRateFuseChunks &&
+                           (pdvec ? nch <= kWaves || wave_items <= kRateFuseItems : wave_items <= kRateFuseSlow);
+    if (a.accept_rate && rate_rows) {
         if (pdvec)
             hipLaunchKernelGGL((acc_rate_rows<BF16, true>), dim3(max_rows), blk, 0, s, a.draft_p, a.logits, a.ld,
                                a.cu_q, a.R, a.K, a.V, scale2, w.rows, a.accept_rate);

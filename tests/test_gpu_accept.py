@@ -111,6 +111,23 @@ def test_wide_vocabulary_rows_one_at_a_time():
     np.testing.assert_allclose(rate[:total][tested], rate_o[:total][tested], atol=2e-5)
 
 
+# the lines between the rate's launch per row and its two launches: entry loads up to 2048
+# (row, chunk) pairs of the host's bound, vector loads of five chunks up to 16384
+@pytest.mark.parametrize("R,K,V", [(120, 16, 1001), (121, 16, 1001), (60, 16, 8001), (61, 16, 8001),
+                                   (192, 16, 16896), (193, 16, 16896)])
+def test_rate_launch_lines(R, K, V):
+    w = synth.scaled(synth.WORKLOADS["mid"], R=R, K=K, V=V)
+    case = guard.build_case(w, 17, with_kv=False)
+    acc_o, nxt_o, _, rate_o = oracle.accept(case.drafts.draft_tok, case.drafts.draft_p, case.logits, w.logit_dtype,
+                                            case.cu_q, w.K, w.V, u=case.drafts.u, want_rate=True)
+    _, _, rate = gpu_accept(w, case.drafts, case.logits, case.cu_q, want_rate=True)
+    total = case.total_q
+    tested = rate_o[:total] >= 0
+    log(f"[accept] rate: R={R} V={V}, {tested.sum()} of {total} rows tested")
+    assert np.array_equal(rate[:total] < 0, ~tested)
+    np.testing.assert_allclose(rate[:total][tested], rate_o[:total][tested], atol=2e-5)
+
+
 def test_malformed_request_with_rate():
     """A request whose q_len exceeds K + 1 gets accepted_len = next_tok = -1
     and rate -1 on its rows; the others are unaffected (requests are
