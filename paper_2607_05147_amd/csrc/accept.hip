@@ -856,20 +856,21 @@ __global__ __launch_bounds__(kBlk) void acc_rate_rows(
 // Resident workgroups of a kernel on the whole device (persistent grids), asked
 // once per device: the query costs as much as a launch.
 template <typename F>
-static int resident_blocks(F fn, std::atomic<int>* cache) {
+static hipError_t resident_blocks(F fn, std::atomic<int>* cache, int* out) {
     constexpr int kMaxDevices = 64;
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return 0;
+    int dev = 0, cus = 0, per_cu = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return e;
     const bool keep = dev >= 0 && dev < kMaxDevices;
-    int n = keep ? cache[dev].load(std::memory_order_relaxed) : 0;
-    if (n == 0) {
-        int per_cu = 0, cus = 0;
-        if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kBlk, 0) != hipSuccess || per_cu < 1) per_cu = 1;
-        n = per_cu * cus;
-        if (keep) cache[dev].store(n, std::memory_order_relaxed);
-    }
-    return n;
+    *out = keep ? cache[dev].load(std::memory_order_relaxed) : 0;
+    if (*out > 0) return hipSuccess;
+    e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    if (e != hipSuccess) return e;
+    // (an answer that is none serves this call and is asked for again)
+    const bool ok = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, kBlk, 0) == hipSuccess && per_cu > 0;
+    *out = (ok ? per_cu : 1) * cus;
+    if (keep && ok) cache[dev].store(*out, std::memory_order_relaxed);
+    return hipSuccess;
 }
 
 template <bool BF16>
@@ -891,8 +892,8 @@ static hipError_t launch_typed(const AcceptArgs& a, void* ws, hipStream_t s) {
 #define DS_ROWPASS(G, VV)                                                                              \
     do {                                                                                               \
         static std::atomic<int> cache[64];                                                             \
-        const int most = resident_blocks(acc_rowpass<BF16, G, VV>, cache);                             \
-        if (most == 0) return hipErrorInvalidDevice;                                                   \
+        int most = 0;                                                                                  \
+        if ((e = resident_blocks(acc_rowpass<BF16, G, VV>, cache, &most)) != hipSuccess) return e;     \
         const int pgrid = (int)std::max<int64_t>(1, std::min<int64_t>((wave_items + kWaves - 1) / kWaves, most)); \
         hipLaunchKernelGGL((acc_rowpass<BF16, G, VV>), dim3(pgrid), blk, 0, s, a.logits, a.ld, a.cu_q, a.R, a.V, \
                            max_rows, scale2, w.stats, w.rows);                                         \

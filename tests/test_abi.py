@@ -3,20 +3,21 @@
 The library must load on a host without a GPU, export every function that
 include/dspark.h declares, and reject bad arguments with the documented
 status before it touches HIP (every call here fails validation, so nothing is
-launched).
+launched; the one that passes it is made only where there is no device).
 """
 import ctypes as C
 import os
 import re
 
 import pytest
+import torch
 
 from paper_2607_05147_amd import dspark
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 HEADER = os.path.join(ROOT, "include", "dspark.h")
 
-EINVAL, ESHAPE, EDTYPE, EUNSUPPORTED, EWORKSPACE = 1, 2, 3, 4, 5
+EINVAL, ESHAPE, EDTYPE, EUNSUPPORTED, EWORKSPACE, EHIP = 1, 2, 3, 4, 5, 6
 FAKE = C.c_void_p(1 << 20)  # aligned, never dereferenced: validation fails first
 
 
@@ -201,6 +202,13 @@ def _acc(L, **kw):
     return L.dspark_accept(a["tok"], a["dp"], a["logits"], a["dt"], a["ld"], a["u"], a["cu"],
                            a["R"], a["K"], a["V"], a["it"], a["acc"], a["nxt"], a["rate"], a["ws"],
                            a["ws_bytes"], None)
+
+
+@pytest.mark.skipif(torch.cuda.is_available(), reason="the call would be launched")
+def test_accept_reports_the_device_error(L):
+    n = L.dspark_accept_workspace_size(4, 8, 1024)
+    assert _acc(L, ws=FAKE, ws_bytes=n) == EHIP
+    assert "no ROCm-capable device" in L.dspark_last_error().decode()
 
 
 def test_accept_validation(L):
