@@ -398,7 +398,7 @@ __device__ __forceinline__ RowInfo ld_info(const RowInfo* p) {
     return v;
 }
 
-// SC: the statistics are read and the row's RowInfo written device-coherently.
+// SC: the statistics are read and the row's record (*info) written device-coherently.
 template <int P, bool SC>
 __device__ __forceinline__ void row_stats(const MarkovArgs& a, const float2* stats, RowInfo* info, int ntiles,
                                           int k, int r, int lane) {
@@ -463,13 +463,13 @@ __device__ __forceinline__ void row_stats(const MarkovArgs& a, const float2* sta
                 ri.tile = lastpos;
                 ri.thr = __builtin_huge_val();
             }
-            st_info<SC>(info + r, ri);
+            st_info<SC>(info, ri);
         }
     } else if (lane == 0) {
         // rounding pushed u * total past the end: the row's last tile with mass
         ri.tile = max(last, 0);
         ri.thr = __builtin_huge_val();
-        st_info<SC>(info + r, ri);
+        st_info<SC>(info, ri);
     }
 }
 
@@ -511,7 +511,7 @@ __global__ __launch_bounds__(kThreads) void md_norm(MarkovArgs a, const float2* 
 #pragma unroll
         for (int i = 0; i < 4 * kNormIt; ++i) zs[i] = p[min(s0 + tid + i * kThreads, s1 - 1)];
     }
-    if (tid < DSPARK_WAVE) row_stats<P, false>(a, stats, &s_ri - r, ntiles, k, r, lane);
+    if (tid < DSPARK_WAVE) row_stats<P, false>(a, stats, &s_ri, ntiles, k, r, lane);
     __syncthreads();
     const RowInfo ri = s_ri;
     const float inv = 1.0f / ri.S;
@@ -849,7 +849,7 @@ __global__ __launch_bounds__(kCoThreads) void md_coop(CoopArgs c) {
 
     // ---- B: row statistics, one wave per request
     for (int r = blockIdx.x + (int)G * wave; r < R; r += (int)G * kCoWaves)
-        row_stats<16, true>(a, c.stats, c.info, c.ntiles, k, g0 + r, lane);
+        row_stats<16, true>(a, c.stats, c.info + g0 + r, c.ntiles, k, g0 + r, lane);
     grid_barrier(c.sync, 2u * c.launch + 2u);
 #pragma unroll
     for (int i = 0; i < kCoTiles; ++i)
