@@ -31,6 +31,7 @@
 // The positions of a block are sequential by definition (x_k feeds position
 // k + 1).
 #include <algorithm>
+#include <atomic>
 #include <math.h>
 
 #include "device_common.h"
@@ -965,16 +966,18 @@ __global__ __launch_bounds__(kThreads) void md_check(MarkovArgs a, const unsigne
 template <int KS, int NT>
 int coop_grid_limit() {
     constexpr int kMaxDevices = 64;
-    static int cache[kMaxDevices];  // 0: not yet asked, -1: none
+    static std::atomic<int> cache[kMaxDevices];  // 0: not yet asked, -1: none
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return 0;
-    if (cache[dev] == 0) {
+    int n = cache[dev].load(std::memory_order_relaxed);
+    if (n == 0) {
         int cus = 0, nb = 0;
         const bool ok = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess &&
                         hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, md_coop<KS, NT>, kCoThreads, 0) == hipSuccess;
-        cache[dev] = ok && nb * cus > 0 ? nb * cus : -1;
+        n = ok && nb * cus > 0 ? nb * cus : -1;
+        cache[dev].store(n, std::memory_order_relaxed);
     }
-    return cache[dev] > 0 ? cache[dev] : 0;
+    return n > 0 ? n : 0;
 }
 
 // Workgroups of md_coop, 0 for batches that the launches per position draft: at most 1024
