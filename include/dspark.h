@@ -208,13 +208,14 @@ dspark_status dspark_schedule_topk(const float* conf, int R, int K, const int32_
  *     - head sizes up to 256, bf16 or fp32, any page: strides multiples of 16
  *       bytes (page stride below 2^30 elements, token stride below 2^24),
  *       q/k/v 16-byte and out 8-byte (bf16) or 16-byte (fp32) aligned: MFMA
- *       tiles, the probabilities at 32-bit accuracy, HBM-bound;
+ *       tiles, bf16 probabilities as two bf16 terms (to within 2^-17), HBM-bound;
  *     - anything else: vector ALUs.
  *   ws of dspark_verify_attn_workspace_size bytes, 256-aligned.  A smaller one is
  *   refused only when no kernel for the call can do with it; kernels that write
  *   less stand in for the fastest otherwise.
- *   On the matrix cores a non-finite value of a later verify token of a
- *   request can reach that request's earlier rows (0 times it).
+ *   A non-finite key or value reaches only the rows that see it, except on the
+ *   first two paths, where a value of a later verify token of a request can
+ *   reach that request's earlier rows (0 times it).
  * ---------------------------------------------------------------------- */
 size_t dspark_verify_attn_workspace_size(int R, int max_q, int Hq, int Hkv, int Dqk, int Dv,
                                          int max_pages, int page_size, dspark_dtype dt);

@@ -17,13 +17,16 @@
 //     offsets that never change.  Rows are 16 * CH bytes (padded head sizes are
 //     filled from a zero block), chunks XOR-swizzled by the copy so that the
 //     operand reads are free of bank conflicts.
-//   * bf16: S^T = K Q^T and O^T += V^T P^T on v_mfma_f32_16x16x32_bf16.  P keeps
-//     32-bit accuracy: it enters its product as two bf16 terms (p to within
-//     2^-17), as the fp32 products that this replaces had it.
+//   * bf16: S^T = K Q^T and O^T += V^T P^T on v_mfma_f32_16x16x32_bf16.  P enters
+//     its product as two bf16 terms, p to within 2^-17 (its sum adds p itself):
+//     the output's rounding is 2^-9, and the errors against 64 bits are those of
+//     the vector-ALU kernels, whose p is fp32.
 //   * fp32: v_mfma_f32_16x16x4_f32 throughout; the score accumulator (keys
 //     4 lq + e) is already the B operand of the value product over those keys.
 //   * softmax online in exp2 units, the running maximum moved only when it
-//     grows by more than 2^8 (exact after the final normalisation).
+//     grows by more than 2^8 (exact after the final normalisation);
+//   * a worker that finds a sum non-finite computes its rows again key by key
+//     (attend_rows), so that a non-finite value reaches only the rows that see it.
 //
 // Measured (GPU time of the whole call) against the vector-ALU kernels:
 //   64 requests, 32/8 heads of 64, 16-key token-major pages, 512-4096 keys, bf16:
@@ -125,10 +128,81 @@ __device__ __forceinline__ void wait_copies() {
 
 __device__ __forceinline__ void wait_lds() { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
 
-// Steps [s0, s1) of the ns steps of one (request, head, chunk).  `slot`: where
-// the partial goes when they are not all of them.
+// The rows of a chunk over the same steps key by key on the vector ALUs, where the
+// products above came out non-finite: a product over 16 rows and 32 keys also multiplies
+// the keys that a row does not see, by a probability of 0, and 0 times a non-finite value
+// is NaN, as is an infinity times the second term of a probability.  Every row takes only
+// its own keys here, as the vector-ALU kernels do.
 template <bool F32, int CH, int NT>
-__device__ __forceinline__ void attend(const Params& p, const uint32_t lds0, const int r, const int g, const int rc,
+__device__ __forceinline__ void attend_rows(const Params& p, const int r, const int g, const int rc, const int q0,
+                                            const int ql, const int kv, const int s0, const int s1, const int ns,
+                                            const int64_t slot) {
+    typedef Cfg<F32, CH> C;
+    typedef typename std::conditional<F32, float, uint16_t>::type T;
+    constexpr int kPer = (C::Dp + DSPARK_WAVE - 1) / DSPARK_WAVE;  // value dims per lane
+    const AttnArgs& a = p.a;
+    // (values in vector registers: the scalar ones that this would add to the kernel's
+    // are spilled into vector registers that the step loop then lacks)
+    int z = 0;
+    asm volatile("" : "+v"(z));
+    const int lane = threadIdx.x, page = a.page + z, group = p.group + z, gv = g + z;
+    const int row0 = (rc + z) * (16 * NT), nrows = min(16 * NT, ql * group - row0);
+    const int32_t* bt = a.block_table + (int64_t)(r + z) * a.max_pages;
+    const T* kc = (const T*)a.k + gv * a.ks[1];
+    const T* vc = (const T*)a.v + gv * a.vs[1];
+    const bool whole = s0 + z == 0 && s1 == ns;
+    float* part = p.part + (slot + z) * ((int64_t)(16 * NT) * (C::Dp + 2));
+    for (int rr = 0; rr < nrows; ++rr) {
+        const int row = row0 + rr, t = row / group;
+        const int64_t orow = (int64_t)(q0 + t) * a.Hq + gv * group + (row - t * group);
+        const int end = min(kv - ql + t + 1, s1 * C::Step);
+        float m = -__builtin_huge_valf(), l = 0.0f, o[kPer];
+#pragma unroll
+        for (int e = 0; e < kPer; ++e) o[e] = 0.0f;
+        for (int k0 = (s0 + z) * C::Step; k0 < end; k0 += DSPARK_WAVE) {
+            const int key = min(k0 + lane, end - 1);
+            const T* kr = kc + (int64_t)bt[key / page] * a.ks[0] + (int64_t)(key % page) * a.ks[2];
+            float sc = 0.0f;
+            for (int d = 0; d < a.Dqk + z; ++d)
+                sc += Elem<T>::load((const T*)a.q, orow * a.Dqk + d) * p.scale2 * Elem<T>::load(kr, d);
+            if (k0 + lane >= end) sc = -__builtin_huge_valf();
+            const float mn = fmaxf(m, wave_max(sc));
+            const float alpha = m == -__builtin_huge_valf() ? 0.0f : exp2f(m - mn);
+            const float pr = sc == -__builtin_huge_valf() ? 0.0f : exp2f(sc - (mn == -__builtin_huge_valf() ? 0.0f : mn));
+            l = l * alpha + wave_sum(pr);
+            m = mn;
+#pragma unroll
+            for (int e = 0; e < kPer; ++e) o[e] *= alpha;
+            for (int j = 0; j < min(DSPARK_WAVE, end - k0); ++j) {
+                const T* vr = vc + (int64_t)bt[(k0 + j) / page] * a.vs[0] + (int64_t)((k0 + j) % page) * a.vs[2];
+                const float pj = __shfl(pr, j, DSPARK_WAVE);
+#pragma unroll
+                for (int e = 0; e < kPer; ++e) {
+                    const int d = lane + e * DSPARK_WAVE;
+                    if (d < a.Dv) o[e] += pj * Elem<T>::load(vr, d);
+                }
+            }
+        }
+        if (lane == 0) {
+            if (!whole) part[rr] = m, part[16 * NT + rr] = l;
+            else if (a.lse) a.lse[orow] = (m + log2f(l)) * kLn2;
+        }
+        const float inv = 1.0f / l;
+#pragma unroll
+        for (int e = 0; e < kPer; ++e) {
+            const int d = lane + e * DSPARK_WAVE;
+            if (d >= a.Dv) continue;
+            if (whole) Elem<T>::store((T*)a.out, orow * a.Dv + d, o[e] * inv);
+            else part[2 * 16 * NT + rr * C::Dp + d] = o[e];
+        }
+    }
+}
+
+// Steps [s0, s1) of the ns steps of one (request, head, chunk).  `slot`: where
+// the partial goes when they are not all of them.  Returns whether a sum of its rows is
+// not finite (what is written is then not yet the result).
+template <bool F32, int CH, int NT>
+__device__ __forceinline__ bool attend(const Params& p, const uint32_t lds0, const int r, const int g, const int rc,
                                        const int q0, const int ql, const int kv, const int s0, const int s1,
                                        const int ns, const int64_t slot) {
     typedef Cfg<F32, CH> C;
@@ -444,12 +518,18 @@ __device__ __forceinline__ void attend(const Params& p, const uint32_t lds0, con
     // ---- rows: total l over the four lanes of a row
     const bool whole = s0 == 0 && s1 == ns;
     float* part = p.part + slot * ((int64_t)(16 * NT) * (C::Dp + 2));
+    float zero = 0.0f;  // NaN if a sum is not finite
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
         lsum[j] += __shfl_xor(lsum[j], 16, 64);
         lsum[j] += __shfl_xor(lsum[j], 32, 64);
         const int rr = 16 * j + lr, row = row0 + rr;
         if (row >= rows) continue;
+        zero = __builtin_fmaf(lsum[j], 0.0f, zero);
+#pragma unroll
+        for (int d = 0; d < C::DB; ++d)
+#pragma unroll
+            for (int x = 0; x < 4; ++x) zero = __builtin_fmaf(acc[j][d][x], 0.0f, zero);
         const int t = row / p.group;
         const int64_t orow = (int64_t)(q0 + t) * a.Hq + g * p.group + (row - t * p.group);
         const float inv = 1.0f / lsum[j];
@@ -482,6 +562,7 @@ __device__ __forceinline__ void attend(const Params& p, const uint32_t lds0, con
             }
         }
     }
+    return __builtin_amdgcn_ballot_w64(zero != 0.0f) != 0;
 }
 
 template <bool F32, int CH, int NT>
@@ -491,8 +572,15 @@ void attn_stream_kernel(Params p) {
     __shared__ __align__(16) unsigned char lds[2 * C::TileB];
     uint32_t lds0 = (uint32_t)(uintptr_t)&lds[0];
     asm volatile("" : "+s"(lds0));
+    bool again = false;
     range_walk<C::Step>(p, [&](int r, int g, int rc, int q0, int ql, int kv, int s0, int s1, int ns, int64_t slot) {
-        attend<F32, CH, NT>(p, lds0, r, g, rc, q0, ql, kv, s0, s1, ns, slot);
+        again |= attend<F32, CH, NT>(p, lds0, r, g, rc, q0, ql, kv, s0, s1, ns, slot);
+    });
+    if (!again) return;
+    // (a walk of its own, so that the step loop above holds none of its registers)
+    __syncthreads();  // what the lanes of the wave wrote above comes before what others write below
+    range_walk<C::Step>(p, [&](int r, int g, int rc, int q0, int ql, int kv, int s0, int s1, int ns, int64_t slot) {
+        attend_rows<F32, CH, NT>(p, r, g, rc, q0, ql, kv, s0, s1, ns, slot);
     });
 }
 

@@ -485,3 +485,46 @@ def test_smaller_workspace(dtype, D, page, Hq, Hkv, q_len, kv_len):
     for n in (need, full - 1, full):
         o = to_f64(call(n))
         assert row_rel_err(o, ref).max() <= TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype,D,Dv,page,Hq,Hkv,q_len,kv_len", [
+    ("bf16", 64, 64, 16, 8, 2, [4, 3, 9, 1], [40, 33, 256, 17]),      # one wave per chunk, no merge
+    ("f32", 64, 64, 16, 8, 2, [4, 3, 9, 1], [40, 33, 250, 17]),
+    ("bf16", 64, 64, 16, 32, 2, [4, 3, 9, 1], [500, 33, 2100, 260]),  # ranges, several row tiles
+    ("f32", 128, 128, 64, 8, 2, [4, 3, 9, 1], [500, 33, 1100, 260]),
+    ("bf16", 192, 128, 16, 4, 2, [4, 3, 9, 1], [500, 33, 1100, 260]),
+    ("f32", 72, 40, 48, 5, 1, [4, 3, 9, 1], [500, 33, 1100, 260]),
+])
+def test_non_finite_keys_and_values(dtype, D, Dv, page, Hq, Hkv, q_len, kv_len):
+    """A non-finite key or value reaches the rows that see it, as in the oracle, and no other:
+    not the request's earlier verify tokens, whose products share its operands."""
+    K = max(q_len) - 1
+    w = synth.scaled(synth.WORKLOADS["tiny" if dtype == "f32" else "mid"], R=len(q_len), K=K, Hq=Hq, Hkv=Hkv, Dqk=D, Dv=Dv,
+                     page=page)
+    cu = oracle.cu_from_len(np.asarray(q_len) - 1)
+    kv = synth.paged_kv(w, 71, kv_len=np.asarray(kv_len, np.int32))
+    q = synth.query_rows(w, 71, synth.flat_keys(np.diff(cu)))
+    bf16 = dtype == "bf16"
+    inf, neg, nan = (0x7f80, 0xff80, 0x7fc0) if bf16 else (np.inf, -np.inf, np.nan)
+
+    def put(cache, r, token, dim, x):
+        cache[kv.block_table[r, token // page], :, token % page, dim] = x
+
+    put(kv.v, 0, kv_len[0] - 1, 0, inf)     # the last verify token: infinities and a NaN, each in a dim
+    put(kv.v, 0, kv_len[0] - 1, 1, neg)
+    put(kv.v, 0, kv_len[0] - 2, 5, nan)     # the one before
+    put(kv.k, 1, kv_len[1] - 1, 3, nan)     # a key: its row is NaN
+    put(kv.v, 2, 7, 2, inf)                 # a value that every row sees
+    put(kv.v, 2, kv_len[2] - 4, 6, nan)
+    ref, ref_lse = oracle.verify_attn(q, kv.k, kv.v, kv.k_strides, kv.v_strides, kv.block_table, kv.kv_len, cu, Hq, Hkv, D,
+                                      Dv, page, w.scale, dtype)
+    assert np.isfinite(ref[0]).all() and np.isfinite(ref[cu[1]]).all() and not np.isfinite(ref).all()
+    out, lse = gpu_attention(w, DevKV(kv, bf16), q, cu)
+    o, l = to_f64(out), to_f64(lse)
+    log(f"[attn] non-finite: {dtype} D={D}/{Dv} page={page}: {(~np.isfinite(ref)).sum()} entries")
+    fin = np.isfinite(ref)
+    np.testing.assert_array_equal(np.isnan(o), np.isnan(ref))
+    np.testing.assert_array_equal(np.where(np.isinf(ref), ref, 0.0), np.where(np.isinf(o), o, 0.0))
+    assert row_rel_err(np.where(fin, o, 0.0), np.where(fin, ref, 0.0)).max() <= TOL[dtype]
+    np.testing.assert_array_equal(np.isnan(l), np.isnan(ref_lse))
+    np.testing.assert_allclose(l, ref_lse, rtol=0, atol=1e-4 if bf16 else 1e-5)
