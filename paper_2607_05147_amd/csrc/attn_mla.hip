@@ -744,7 +744,9 @@ __device__ __forceinline__ void value_item(const Params& p, const int r, const i
 // Spilled registers lie in the queue's scratch memory, where waves are as far apart as
 // the largest kernel run on it has asked for.  With this kernel's 244 bytes a lane that is
 // 16 KB, and the spills of the drafter's kernels met in few cache sets: a Markov block of
-// 128 x 129280 after any latent call took 1058 us against 1000.  With `pad` it is 18 KB.
+// 128 x 129280 after any latent call took 1058 us against 1000.  With `pad` it is 18 KB
+// (how many spills there are is up to the compiler: a test reads the size from the built
+// code).
 __global__ __launch_bounds__(kThreads) void mla_kernel(Params p) {
     volatile int pad[8];
     pad[threadIdx.x & 7] = 0;

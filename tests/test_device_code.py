@@ -5,6 +5,9 @@ compiler inserts no wait states, so what the hardware asks for has to hold in th
 code as built: one between a scalar write of m0 and the copy that reads it, and five
 between a vector instruction's write of a scalar register and the copy that takes its
 address from there.
+
+The latent attention kernel keeps a few bytes of scratch memory that it does not use, for
+the sake of what runs after it on the queue; how many it has is up to the compiler.
 """
 import os
 import re
@@ -96,3 +99,24 @@ def test_copies_into_lds_wait_for_m0(copies):
 def test_copies_into_lds_wait_for_their_address(copies):
     _, address, n = copies
     assert not address, f"{len(address)} of {n}: " + "; ".join(address[:3])
+
+
+def _scratch_bytes(co):
+    """Scratch bytes per lane of every kernel."""
+    text = subprocess.run([f"{LLVM}/llvm-readelf", "--notes", co], check=True, capture_output=True, text=True).stdout
+    names = re.findall(r"\.name: +(_Z\w+)", text)
+    sizes = re.findall(r"\.private_segment_fixed_size: +(\d+)", text)
+    assert len(names) == len(sizes) > 0
+    return dict(zip(names, map(int, sizes)))
+
+
+def test_latent_scratch_is_no_multiple_of_4_kb(tmp_path):
+    # waves' scratch lies as far apart as the largest kernel run on the queue asked for, in
+    # whole kilobytes; a multiple of 4 KB puts the spills of the drafter's kernels into few
+    # cache sets
+    sizes = _scratch_bytes(_code_object(os.path.join(build.CSRC, "attn_mla.hip"), tmp_path))
+    (latent,) = [n for name, n in sizes.items() if "mla_kernel" in name]
+    stride = -(-latent * 64 // 1024) * 1024
+    assert stride % 4096, f"{latent} bytes a lane, {stride} a wave"
+    drafter = _scratch_bytes(_code_object(os.path.join(build.CSRC, "markov.hip"), tmp_path))
+    assert max(drafter.values()) < latent  # else the drafter's own size decides, and the bytes are for nothing
