@@ -359,6 +359,9 @@ def test_edge_context_lengths(name, Hq, Hkv, q_len, kv_len):
     ("f32", 256, 256, 32, 16, 2, [9, 5], [300, 700]),
     ("bf16", 128, 128, 16, 64, 8, [17, 1], [2300, 260]),
     ("bf16", 96, 96, 16, 32, 1, [5, 2], [5000, 400]),
+    # more requests than a wave scans at once
+    ("bf16", 64, 64, 16, 8, 2, [1, 4, 2] * 50, [300, 17, 700] * 50),
+    ("f32", 64, 64, 16, 8, 2, [1, 4, 2] * 50, [300, 17, 260] * 50),
 ])
 def test_any_head_size_and_page(dtype, Dqk, Dv, page, Hq, Hkv, q_len, kv_len):
     """Head sizes up to 256 on any page: against the oracle, against the same
@@ -415,6 +418,7 @@ def test_any_head_size_and_page(dtype, Dqk, Dv, page, Hq, Hkv, q_len, kv_len):
     (3, 8, [1, 5, 17], [257, 4097, 2000]),          # several workgroups per context
     (2, 1, [17, 3], [8192, 8193]),                  # more than a window of 64 pages
     (5, 3, [1, 2, 9, 4, 3], [40, 900, 33, 65, 1]),  # a head count that does not divide the part
+    (150, 8, [2, 1, 5], [600, 33, 900, 300]),       # more requests than a wave scans at once
 ])
 def test_ranges_and_queue_agree(R, Hkv, q_len, kv_len):
     """The cut of a batch into ranges against the work queue: the same inputs
