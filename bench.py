@@ -109,16 +109,18 @@ CSRC = os.path.join(HERE, "paper_2607_05147_amd", "csrc")
 ATTN_PATHS = {
     "gqa": {"src": "attn_mfma.hip", "kernels": ("mf_plan", "attn_mfma_kernel", "attn_mfma_merge"),
             "bound": "hbm"},
+    "gqa_ranges": {"src": "attn_mfma.hip", "kernels": ("attn_merge", "attn_mfma_ranges"), "bound": "hbm"},
     "latent": {"src": "attn_mla.hip", "kernels": ("mla_plan", "mla_kernel", "mla_merge"),
                "bound": "mfma"},
+    "stream": {"src": "attn_stream.hip", "kernels": ("attn_merge", "attn_stream_kernel"), "bound": "hbm"},
     "generic": {"src": "attn_generic.hip", "kernels": ("attn_generic_kernel", "attn_generic_merge"),
                 "bound": "hbm"},
     # not attention: the draft blocks' launches
     "draft": {"src": "markov.hip", "kernels": ("md_hidden", "md_first", "md_coop", "md_check", "md_tile",
-                                              "md_stats", "md_norm"),
+                                              "md_norm"),
               "bound": "hbm"},
     "rnn_draft": {"src": "markov.hip", "kernels": ("md_hidden", "rnn_hproj", "md_first", "rnn_state",
-                                                   "md_coop", "md_check", "md_tile", "md_stats", "md_norm"),
+                                                   "md_coop", "md_check", "md_tile", "md_norm"),
                   "bound": "hbm"},
     # not attention: the acceptance launches of one dspark_accept call (the
     # resolve kernel runs once per call)
@@ -132,10 +134,16 @@ def attn_path(w, bf16: bool) -> str:
     own dispatch conditions; the bench's V aliases K on latent shapes)."""
     pow2 = w.page >= 64 and (w.page & (w.page - 1)) == 0
     if bf16 and w.Dqk == 128 and w.Dv == 128 and pow2:
-        return "gqa"
+        # equal ranges: few steps per resident workgroup (by the bound on the contexts) and
+        # fewer (request, KV head) pairs than workgroups; else the queue.  (No workload has
+        # contexts of 512 keys and less, or many pairs in splits below 2048 keys.)
+        rows = w.max_q * w.Hq // w.Hkv
+        chunks = -(-rows // (128 if rows > 64 else 64))
+        steps = -(-w.kv_dist[-1] // 32)
+        return "gqa_ranges" if w.R * chunks * steps <= 320 * (512 // w.Hkv) and w.R * w.Hkv < 512 else "gqa"
     if bf16 and w.mla and w.Dqk == 576 and w.Dv == 512 and pow2:
         return "latent"
-    return "generic"
+    return "stream" if max(w.Dqk, w.Dv) <= 256 else "generic"
 
 
 def path_of_workload(name: str) -> str:

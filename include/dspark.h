@@ -347,7 +347,7 @@ dspark_status dspark_markov_draft(const int32_t* anchor, const void* base_logits
  *   aligned when d > 0 (the backbone part of the projection, Wrnn[:, 2 rank:]
  *   h_k, runs on the matrix cores once for every position).  The state and
  *   the head's output are fp32; the output enters the bf16 vocabulary product
- *   as three bf16 terms whose sum is its fp32 value.
+ *   as two bf16 terms (to within 2^-16).
  *   ws    dspark_rnn_draft_workspace_size(R, K, V, rank) bytes, 256-aligned.
  * ---------------------------------------------------------------------- */
 size_t dspark_rnn_draft_workspace_size(int R, int K, int V, int rank);
