@@ -30,8 +30,8 @@
 //
 // Measured (GPU time of the whole call) against the vector-ALU kernels:
 //   64 requests, 32/8 heads of 64, 16-key token-major pages, 512-4096 keys, bf16:
-//   1690 -> 74 us (303 MB, 4.1 TB/s; four times the requests: 4.65 TB/s);
-//   16 requests, 32/8 heads of 128, 64-key pages, 512-2048 keys, fp32: 1150 -> 60 us (170 MB, 2.8 TB/s;
+//   1690 -> 73-75 us (303 MB, 4.1 TB/s; four times the requests: 4.65 TB/s);
+//   16 requests, 32/8 heads of 128, 64-key pages, 512-2048 keys, fp32: 1150 -> 64 us (170 MB, 2.7 TB/s;
 //   four times the requests: 4.0 TB/s).
 #include <algorithm>
 #include <type_traits>
@@ -627,9 +627,9 @@ static Geom geom(const AttnArgs& a) {
     const int64_t max_kv = (int64_t)a.max_pages * a.page;
     g.direct = max_kv <= kDirectKeys && (rows + 15) / 16 <= kDirectChunks;
     // row tiles per wave: as many as a request can fill, up to what the
-    // registers hold without spilling (more tiles than that read the keys again,
-    // from the last-level cache).  Short contexts have few waves and are bound
-    // by a wave's own chain of steps, so each takes one tile.
+    // registers hold (fp32 heads of 65-128 spill 16 with two tiles; more tiles than
+    // these read the keys again, from the last-level cache).  Short contexts have few
+    // waves and are bound by a wave's own chain of steps, so each takes one tile.
     const int most = a.bf16 ? (g.ch <= 12 ? 4 : g.ch <= 24 ? 2 : 1) : (g.ch <= 16 ? 4 : g.ch <= 32 ? 2 : 1);
     g.nt = g.direct ? 1 : (int)std::min<int64_t>(rows <= 16 ? 1 : rows <= 32 ? 2 : 4, most);
     g.rc_max = (int)((rows + 16 * g.nt - 1) / (16 * g.nt));
