@@ -129,7 +129,7 @@ static MfGeom mf_geom(const AttnArgs& a) {
     g.resident = std::max(1, 2 * kRangeCUs / a.Hkv);
     g.workers = a.Hkv * std::min<int64_t>(g.resident, (units + kMfMinUnits - 1) / kMfMinUnits);
     g.ranges = units <= kRangeUnits * g.resident && g.rc_max * steps < (int64_t)1 << 31 &&
-               (int64_t)a.R * a.Hkv < (int64_t)1 << 31;
+               (int64_t)a.R * a.Hkv < kRangePairs;
     // (up to twice the keys when the chunks alone fill the part: 64 requests x 8
     // heads of 256-500 keys 24 against 32 us)
     g.direct = g.ranges && g.rc_max <= kDirectChunks &&

@@ -28,6 +28,9 @@ constexpr int kDirectKeys = 256;
 // of them is the grid's end (next to each other, every second workgroup of 192 requests x
 // 8 heads with two chunks was empty and half of the XCDs idle: 72 against 44 us).
 constexpr int kDirectChunks = 65535;  // a grid's second dimension, at most
+// (request, head) pairs, fewer than: the grids over them are of 256 threads each, and a
+// launch takes fewer than 2^32 threads a dimension.
+constexpr int64_t kRangePairs = (int64_t)1 << 24;
 
 struct Ranges {
     AttnArgs a;

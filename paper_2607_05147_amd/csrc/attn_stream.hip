@@ -653,7 +653,7 @@ bool attn_stream_shape_ok(const AttnArgs& a) {
     const stream::Geom g = stream::geom(a);
     // a request's units and the grid fit 32 bits
     return (int64_t)a.Hkv * g.rc_max * (((int64_t)a.max_pages * a.page + 15) / 16) < (int64_t)1 << 31 &&
-           g.waves < (int64_t)1 << 31 && (int64_t)a.R * a.Hkv < (int64_t)1 << 31;
+           g.waves < (int64_t)1 << 31 && (int64_t)a.R * a.Hkv < kRangePairs;
 }
 
 bool attn_stream_supported(const AttnArgs& a) {
